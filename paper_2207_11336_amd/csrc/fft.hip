@@ -15,6 +15,7 @@
 // For N' = 4096 and 8192 each column's points stay in registers (a few lanes
 // per column, see k_colpass_a_reg); for the other sizes a stripe of CW
 // columns is transformed in LDS by Stockham passes.
+#include <type_traits>
 #include <utility>
 
 #include "ri_internal.h"
@@ -24,7 +25,7 @@ namespace ri {
 namespace {
 
 // exp(-2 pi i k / 16), k = 0..15 (exact constants of the 16th roots of unity)
-__device__ __constant__ double kRoot16[16][2] = {
+__device__ constexpr double kRoot16[16][2] = {
     {1.0, 0.0},
     {0.92387953251128675613, -0.38268343236508977173},
     {0.70710678118654752440, -0.70710678118654752440},
@@ -202,11 +203,29 @@ __device__ __forceinline__ void row_fft(cx<T> *s, int logL, const cx<T> *__restr
     }
 }
 
-// Z then the row DFT of image row iy (blockIdx.x), written to grid row (iy - N/2) mod N'.
+// Zero the output grid, the work counter and the partial sums, spread over the launch.
+template <typename T>
+__device__ __forceinline__ void clear_share(const Clear<T> &z) {
+    const int64_t step = (int64_t)gridDim.x * blockDim.x, i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    uint4 *g = reinterpret_cast<uint4 *>(z.grid);
+    const int64_t n16 = z.n * (int64_t)sizeof(cx<T>) / 16;
+    for (int64_t i = i0; i < n16; i += step) g[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (i0 == 0 && z.counter) *z.counter = 0;
+    for (int64_t i = i0; i < z.npart; i += step) z.part[i] = 0.0;
+}
+
+template <typename T>
+__global__ void k_clear(Clear<T> z) {
+    clear_share<T>(z);
+}
+
+// Z then the row DFT of image row iy (blockIdx.x), written to row (iy - N/2) & rowmask
+// (N' - 1: the grid row; N - 1: the N rows packed).
 // With a w-stack's phase screen (chirp != NULL) the padded image is x c_s.
 template <typename T, bool PAD>
-__global__ void k_zpad_rowfft(const T *__restrict__ x, cx<T> *__restrict__ grid, const T *__restrict__ icorr,
-                              const cx<T> *__restrict__ tw, int N, int logNp, const cx<T> *__restrict__ chirp) {
+__global__ void __launch_bounds__(512) k_zpad_rowfft(const T *__restrict__ x, cx<T> *__restrict__ grid, const T *__restrict__ icorr,
+                              const cx<T> *__restrict__ tw, int N, int logNp, const cx<T> *__restrict__ chirp,
+                              int rowmask, Clear<T> z) {
     extern __shared__ unsigned char smem_raw[];
     cx<T> *s = reinterpret_cast<cx<T> *>(smem_raw);
     const int Np = 1 << logNp;
@@ -224,8 +243,9 @@ __global__ void k_zpad_rowfft(const T *__restrict__ x, cx<T> *__restrict__ grid,
         }
         return mk<T>(a, (T)0);
     };
-    cx<T> *row = grid + (size_t)((iy - N / 2) & (Np - 1)) * Np;
+    cx<T> *row = grid + (size_t)((iy - N / 2) & rowmask) * Np;
     row_fft<T, PAD>(s, logNp, tw, false, ld, [&](int k, cx<T> v) { row[k] = v; });
+    clear_share<T>(z);
 }
 
 // Inverse row DFT of grid row (iy - N/2) mod N', then crop, correction, real part:
@@ -233,7 +253,7 @@ __global__ void k_zpad_rowfft(const T *__restrict__ x, cx<T> *__restrict__ grid,
 // w-stack's phase screen the value is Re{conj(c_s) row[...]} (Z_s^dagger), added
 // to out when accumulate != 0 (the sum over stacks).
 template <typename T, bool PAD>
-__global__ void k_irowfft_crop(const cx<T> *__restrict__ grid, T *__restrict__ out, const T *__restrict__ icorr,
+__global__ void __launch_bounds__(512) k_irowfft_crop(const cx<T> *__restrict__ grid, T *__restrict__ out, const T *__restrict__ icorr,
                                const cx<T> *__restrict__ tw, int N, int logNp, const cx<T> *__restrict__ chirp,
                                int accumulate) {
     extern __shared__ unsigned char smem_raw[];
@@ -285,9 +305,10 @@ __global__ void k_colpass_a(cx<T> *__restrict__ grid, const cx<T> *__restrict__ 
     }
 }
 
-// Four-step pass B (out of place): rows N2*k1 + n2 -> rows k1 + N1*k2.
+// Four-step pass B: rows N2*k1 + n2 -> rows k1 + N1*k2, or, in place
+// (out == in), -> rows N2*k1 + k2 (a workgroup's own rows).
 template <typename T>
-__global__ void k_colpass_b(const cx<T> *__restrict__ in, cx<T> *__restrict__ out, const cx<T> *__restrict__ tw,
+__global__ void k_colpass_b(const cx<T> *in, cx<T> *out, const cx<T> *__restrict__ tw,
                             int N, int logNp, int logN1, int logN2, int logCW, int band_out, int inv) {
     extern __shared__ unsigned char smem_raw[];
     cx<T> *s = reinterpret_cast<cx<T> *>(smem_raw);
@@ -302,7 +323,7 @@ __global__ void k_colpass_b(const cx<T> *__restrict__ in, cx<T> *__restrict__ ou
     fft_lds<T, false>(s, logN2, logCW, tw, Np >> logN2, inv != 0);
     for (int e = threadIdx.x; e < nel; e += blockDim.x) {
         const int k2 = e >> logCW, c = e & (CW - 1);
-        const int r = k1 + N1 * k2;
+        const int r = out == in ? N2 * k1 + k2 : k1 + N1 * k2;
         if (!band_out || in_band(r, N, Np)) out[(size_t)r * Np + x0 + c] = s[e];
     }
 }
@@ -402,9 +423,42 @@ __global__ void __launch_bounds__(64) k_colpass_a_reg(cx<T> *__restrict__ grid, 
     });
 }
 
-// Pass B: rows L k1 + n2 (L = N2) -> L-point transforms over n2 -> rows k1 + N1 k2.
+// Pass A of a 128-point column whose band input has 64 non-zero points (image
+// side N = N'/2: points 32..95 are zero): the first radix-2 stage only selects
+// and twists, so a lane holds one 64-point half, the even or (blockIdx.z = 1)
+// the odd frequencies, and no value crosses lanes (the two halves write rows that
+// the other reads, hence out of place, from the N packed band rows). The stage's
+// products are those of fft_lanes<T, 128, 2>. At N' = 8192 in FP32: 231 us, against
+// 321 us with two lanes per column (average of both directions).
+template <typename T>
+__global__ void __launch_bounds__(64) k_colpass_a_band(const cx<T> *in, cx<T> *out, const cx<T> *__restrict__ tw,
+                                                       int logNp) {
+    const int Np = 1 << logNp, N2 = Np / 128;
+    const int c = blockIdx.x * 64 + threadIdx.x, n2 = blockIdx.y, odd = blockIdx.z;
+    cx<T> v[64];
+    static_for<64>([&](auto I) {
+        constexpr int i = decltype(I)::value;
+        v[i] = in[(size_t)(n2 + N2 * i) * Np + c];
+    });
+    if (odd)
+        static_for<64>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            cx<T> d = i < 32 ? v[i] : mk<T>(-v[i].x, -v[i].y);
+            if constexpr (i != 0) d = d * tw[i * (Np / 128)];
+            v[i] = d;
+        });
+    fftp_reg<T, 64>(v, tw, Np / 64, false);
+    static_for<64>([&](auto I) {
+        constexpr int i = decltype(I)::value;
+        const int k1 = brev(i, 6) * 2 + odd;
+        out[(size_t)(n2 + N2 * k1) * Np + c] = v[i] * tw[n2 * k1];
+    });
+}
+
+// Pass B: rows L k1 + n2 (L = N2) -> L-point transforms over n2 -> rows k1 + N1 k2, or, in place
+// (out == in), -> rows L k1 + k2. The wave has loaded all its points before it stores one.
 template <typename T, int L, int Q>
-__global__ void __launch_bounds__(64) k_colpass_b_reg(const cx<T> *__restrict__ in, cx<T> *__restrict__ out,
+__global__ void __launch_bounds__(64) k_colpass_b_reg(const cx<T> *in, cx<T> *out,
                                                       const cx<T> *__restrict__ tw, int N, int logNp, int band_out,
                                                       int inv) {
     constexpr int P = L / Q, CPB = 64 / Q;
@@ -416,9 +470,323 @@ __global__ void __launch_bounds__(64) k_colpass_b_reg(const cx<T> *__restrict__ 
     const int hb = brev(h, ilog2(Q));
     static_for<P>([&](auto I) {
         constexpr int i = decltype(I)::value;
-        const int r = k1 + N1 * (brev(i, ilog2(P)) * Q + hb);
+        const int k2 = brev(i, ilog2(P)) * Q + hb, r = out == in ? L * k1 + k2 : k1 + N1 * k2;
         if (!band_out || in_band(r, N, Np)) out[(size_t)r * Np + c] = v[i];
     });
+}
+
+// ---------------------------------------------------------------------------
+// Half-plane transforms of a real image. F Z x is Hermitian, so only the
+// columns kx = 0 .. N of the grid are formed, and on the way out only those
+// carry the (mirrored) visibilities.
+//
+// Rows: two image rows a, b ride through one complex transform as a + i b and
+// are separated by their symmetry. The columns kx = 0 and kx = N of the row
+// spectra are real; the scratch holds them as one complex column 0.
+//
+// Columns: of the 2N grid rows only N are non-zero (forward) or wanted
+// (adjoint), so the even and the odd ky of a column are N-point transforms
+// of the same N inputs, the odd ones twisted by exp(-+ i pi n / N):
+//   X[2k + p] = sum_n (w^{pn} x[n]) W_N^{nk},   x[n] = sum_p w^{-pn} (IDFT_N Y[2k + p])[n].
+// One workgroup holds CW adjacent whole columns in LDS: one read of the
+// scratch per parity and one write of the grid forward, one read of the grid
+// and one write of the scratch back. Bound by memory latency and bandwidth; the
+// adjoint's columns and rows take 59 + 26 us at N' = 4096 in FP32 (whole plane,
+// two column passes: about 150), 189 + 119 at 8192 (about 680), and the FP64
+// forward ones 13 + 19 at 2048 (about 130).
+// ---------------------------------------------------------------------------
+inline __device__ __host__ int scratch_pitch(int N) { return N >= 64 ? N + 16 : N; }
+
+// Image rows 2 b and 2 b + 1 -> rows of the scratch (row index n mod N).
+template <typename T, bool PAD>
+__global__ void __launch_bounds__(512) k_half_rows(const T *__restrict__ x, cx<T> *__restrict__ scr, const T *__restrict__ icorr,
+                            const cx<T> *__restrict__ tw, int N, int logNp, Clear<T> z) {
+    extern __shared__ unsigned char smem_raw[];
+    cx<T> *s = reinterpret_cast<cx<T> *>(smem_raw);
+    const int Np = 1 << logNp, iy = 2 * blockIdx.x;
+    const T ca = icorr[iy], cb = icorr[iy + 1];
+    const T *xa = x + (size_t)iy * N, *xb = xa + N;
+    row_first_pass<T, PAD>(s, Np, false, [&](int gx) -> cx<T> {
+        const int ix = (gx + N / 2) & (Np - 1);
+        if (ix >= N) return mk<T>((T)0, (T)0);
+        const T c = icorr[ix];
+        return mk<T>(xa[ix] * c * ca, xb[ix] * c * cb);
+    });
+    int Ns = 16, rem = logNp - 4;
+    while (rem > 0) {
+        if (rem >= 4) { stockham_pass<T, 16, PAD>(s, Np, 0, Ns, tw, 1, false); Ns <<= 4; rem -= 4; }
+        else if (rem == 3) { stockham_pass<T, 8, PAD>(s, Np, 0, Ns, tw, 1, false); Ns <<= 3; rem -= 3; }
+        else if (rem == 2) { stockham_pass<T, 4, PAD>(s, Np, 0, Ns, tw, 1, false); Ns <<= 2; rem -= 2; }
+        else { stockham_pass<T, 2, PAD>(s, Np, 0, Ns, tw, 1, false); Ns <<= 1; rem -= 1; }
+    }
+    cx<T> *ra = scr + (size_t)((iy - N / 2) & (N - 1)) * scratch_pitch(N);
+    cx<T> *rb = ra + scratch_pitch(N);   // n and n + 1 are neighbours: n is even
+    for (int k = threadIdx.x; k < N; k += blockDim.x) {
+        const cx<T> p = s[pidx<PAD>(k)], q = s[pidx<PAD>(k == 0 ? N : Np - k)];
+        if (k == 0) {
+            ra[0] = mk<T>(p.x, q.x);
+            rb[0] = mk<T>(p.y, q.y);
+        } else {
+            ra[k] = mk<T>((T)0.5 * (p.x + q.x), (T)0.5 * (p.y - q.y));
+            rb[k] = mk<T>((T)0.5 * (p.y + q.y), (T)0.5 * (q.x - p.x));
+        }
+    }
+    clear_share<T>(z);
+}
+
+// Rows of the scratch -> image rows 2 b and 2 b + 1: the real inverse row
+// transforms of both half spectra as one complex one, cropped and corrected.
+template <typename T, bool PAD>
+__global__ void __launch_bounds__(512) k_half_irows(const cx<T> *__restrict__ scr, T *__restrict__ out, const T *__restrict__ icorr,
+                             const cx<T> *__restrict__ tw, int N, int logNp) {
+    extern __shared__ unsigned char smem_raw[];
+    cx<T> *s = reinterpret_cast<cx<T> *>(smem_raw);
+    const int Np = 1 << logNp, iy = 2 * blockIdx.x;
+    const cx<T> *ra = scr + (size_t)((iy - N / 2) & (N - 1)) * scratch_pitch(N);
+    const cx<T> *rb = ra + scratch_pitch(N);
+    const T ca = icorr[iy], cb = icorr[iy + 1];
+    T *oa = out + (size_t)iy * N, *ob = oa + N;
+    auto ld = [&](int k) -> cx<T> {
+        if (k == 0) return mk<T>(ra[0].x, rb[0].x);
+        if (k == N) return mk<T>(ra[0].y, rb[0].y);
+        const bool up = k > N;
+        cx<T> a = ra[up ? Np - k : k], b = rb[up ? Np - k : k];
+        if (up) {
+            a.y = -a.y;
+            b.y = -b.y;
+        }
+        return mk<T>((T)0.5 * (a.x - b.y), (T)0.5 * (a.y + b.x));
+    };
+    row_fft<T, PAD>(s, logNp, tw, true, ld, [&](int gx, cx<T> v) {
+        const int ix = (gx + N / 2) & (Np - 1);
+        if (ix >= N) return;
+        const T c = icorr[ix];
+        oa[ix] = v.x * c * ca;
+        ob[ix] = v.y * c * cb;
+    });
+}
+
+// base[i] through a 32-bit byte offset (one address register instead of two).
+template <typename T>
+__device__ __forceinline__ T &at32(T *base, unsigned i) {
+    using B = std::conditional_t<std::is_const<T>::value, const char, char>;
+    return *reinterpret_cast<T *>(reinterpret_cast<B *>(base) + (size_t)(i * (unsigned)sizeof(T)));
+}
+
+// The same value, opaque to the compiler: addresses formed from it are
+// computed again instead of being kept in registers from one transform to the next.
+__device__ __forceinline__ int fresh(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
+// log2 of the columns per workgroup. FP32: 8 up to N = 512 (small images want
+// wide row segments: 8.9 against 11.1 us for the adjoint pass at N = 128), 4 above
+// (two workgroups per CU: 19 against 22.7 us at N = 1024, 59 against 61 at 2048,
+// 192 with 4 against 234 with 2 at 4096). FP64: 4 (10.2 against 15.8 us at
+// N = 256 and 22 + 13 against 21 + 17 us for both passes at 1024 with 2), and 2
+// at N = 4096, whose columns then fill 139 KB of LDS.
+template <typename T>
+constexpr int half_log_cw(int logN) { return sizeof(T) == 4 ? (logN <= 9 ? 3 : 2) : (logN <= 11 ? 2 : 1); }
+template <typename T>
+constexpr int half_threads(int logN) {
+    const int n = 1 << (logN + half_log_cw<T>(logN) - 4);
+    return n < 64 ? 64 : n;
+}
+
+// Whole-column transforms: N = 2^LOGN points, CW columns in LDS.
+template <typename T, int LOGN>
+struct ColFft {
+    static constexpr int N = 1 << LOGN, LCW = half_log_cw<T>(LOGN), CW = 1 << LCW, NT = half_threads<T>(LOGN);
+    static constexpr int RL = LOGN == 4 ? 16 : 1 << (((LOGN - 1) & 3) + 1);   // last pass's radix
+    static constexpr int SP = N >= 64 ? N + 16 : N;                           // scratch pitch
+    static constexpr size_t LDS = sizeof(cx<T>) * ((size_t)(N + N / 16) * CW);
+
+    // LDS element of point i of column col: CW elements of padding per 16
+    // points, so that the first pass's stores (16 points apart per lane) spread
+    // over the banks.
+    static __device__ __forceinline__ int cidx(int i, int col) { return (i + (i >> 4)) * CW + col; }
+
+    // One Stockham radix-R pass (Ns = points per finished sub-transform); LAST
+    // leaves the outputs in v: output j + r N/R of group g = (j, col),
+    // g = tid + i NT, in v[i R + r].
+    template <int R, int NS, bool LAST>
+    static __device__ __forceinline__ void pass(cx<T> *s, const cx<T> *__restrict__ tw2, bool inv, int tid, cx<T> (&v)[16]) {
+        constexpr int G = 16 / R, ng = (N / R) * CW;
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            const int g = tid + i * NT;
+            if (G * NT > ng && g >= ng) continue;
+            const int col = g & (CW - 1), j = g >> LCW, jm = j & (NS - 1);
+#pragma unroll
+            for (int r = 0; r < R; ++r) v[i * R + r] = s[cidx(j + r * (N / R), col)];
+            const int step = 2 * jm * (N / (NS * R));
+#pragma unroll
+            for (int r = 1; r < R; ++r) {
+                cx<T> w = at32(tw2, (unsigned)(step * r));
+                if (inv) w.y = -w.y;
+                v[i * R + r] = v[i * R + r] * w;
+            }
+            dft_reg<T, R>(v + i * R, inv);
+        }
+        __syncthreads();
+        if (LAST) return;
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            const int g = tid + i * NT;
+            if (G * NT > ng && g >= ng) continue;
+            const int col = g & (CW - 1), j = g >> LCW, jm = j & (NS - 1);
+#pragma unroll
+            for (int r = 0; r < R; ++r) s[cidx((j - jm) * R + jm + r * NS, col)] = v[i * R + r];
+        }
+        __syncthreads();
+    }
+
+    // v: inputs j + r N/16 of group (j, col) = tid on entry, the last
+    // pass's outputs on return (read them with visit). s is free on entry and
+    // on return.
+    static __device__ __forceinline__ void run(cx<T> *s, const cx<T> *__restrict__ tw2, bool inv, int tid, cx<T> (&v)[16]) {
+        dft_reg<T, 16>(v, inv);
+        if constexpr (LOGN > 4) {
+            const int g = tid, col = g & (CW - 1), j = g >> LCW;
+            if (j < N / 16) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) s[cidx(16 * j + r, col)] = v[r];
+            }
+            __syncthreads();
+            if constexpr (LOGN > 8) pass<16, 16, false>(s, tw2, inv, tid, v);
+            pass<RL, N / RL, true>(s, tw2, inv, tid, v);
+        }
+    }
+
+    // f(k, col, integral_constant<register>) for the thread's outputs.
+    template <typename F>
+    static __device__ __forceinline__ void visit(int tid, F &&f) {
+        constexpr int ng = (N / RL) * CW;
+        static_for<16 / RL>([&](auto I) {
+            const int g = tid + decltype(I)::value * NT;
+            if (16 / RL * NT > ng && g >= ng) return;
+            static_for<RL>([&](auto Q) {
+                f((g >> LCW) + decltype(Q)::value * (N / RL), g & (CW - 1),
+                  std::integral_constant<int, decltype(I)::value * RL + decltype(Q)::value>{});
+            });
+        });
+    }
+
+    // exp(-2 pi i n / (2N)) of the row with index i = n mod N, n in [-N/2, N/2).
+    static __device__ __forceinline__ cx<T> twist(const cx<T> *__restrict__ tw2, int i) {
+        return at32(tw2, (unsigned)((i < N / 2 ? i : i + N) & (2 * N - 1)));
+    }
+};
+
+// Scratch -> grid columns x0 .. x0 + CW - 1, the ky of one parity per workgroup.
+// The two parities of a stripe and its neighbours run on one XCD (workgroups
+// are dealt to the 8 XCDs in turn), whose L2 then holds the scratch lines they
+// share. Stripe 0 also writes column kx = N.
+template <typename T, int LOGN>
+__global__ void __launch_bounds__((half_threads<T>(LOGN)))
+k_half_cols(const cx<T> *__restrict__ scr, cx<T> *__restrict__ X, const cx<T> *__restrict__ tw2, int pitch) {
+    using C = ColFft<T, LOGN>;
+    extern __shared__ unsigned char smem_raw[];
+    cx<T> *s = reinterpret_cast<cx<T> *>(smem_raw);
+    constexpr int N = C::N;
+    const int nb = gridDim.x, b = (nb & 7) ? (int)blockIdx.x : (int)(blockIdx.x & 7) * (nb >> 3) + (blockIdx.x >> 3);
+    const int p = b & 1, x0 = (b >> 1) * C::CW, g = threadIdx.x, col0 = g & (C::CW - 1), j0 = g >> C::LCW;
+    const bool live = j0 < N / 16;
+    cx<T> v[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+        v[r] = live ? at32(scr, (unsigned)((j0 + r * (N / 16)) * C::SP + x0 + col0)) : mk<T>((T)0, (T)0);
+    if (p && live) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) v[r] = v[r] * C::twist(tw2, j0 + r * (N / 16));
+    }
+    C::run(s, tw2, false, g, v);
+    cx<T> *Xp = X + (size_t)p * pitch;
+    if (x0 == 0) {
+        // column 0 carries kx = 0 and kx = N (their row spectra are real)
+        C::visit(g, [&](int k, int col, auto q) {
+            if (col != 0) at32(Xp, (unsigned)(2 * k * pitch + col)) = v[q];
+            else s[k] = v[q];
+        });
+        __syncthreads();
+        for (int k = g; k < N; k += C::NT) {
+            const cx<T> a = s[k], c = s[(N - k - p) & (N - 1)];
+            at32(Xp, (unsigned)(2 * k * pitch)) = mk<T>((T)0.5 * (a.x + c.x), (T)0.5 * (a.y - c.y));
+            at32(Xp, (unsigned)(2 * k * pitch + N)) = mk<T>((T)0.5 * (a.y + c.y), (T)0.5 * (c.x - a.x));
+        }
+    } else {
+        C::visit(g, [&](int k, int col, auto q) { at32(Xp, (unsigned)(2 * k * pitch + x0 + col)) = v[q]; });
+    }
+}
+
+// Grid columns -> scratch: the adjoint of k_half_cols. Column 0 takes the
+// Hermitian parts of kx = 0 and kx = N (only the image's real part is wanted).
+template <typename T, int LOGN>
+__global__ void __launch_bounds__((half_threads<T>(LOGN)))
+k_half_icols(const cx<T> *__restrict__ Y, cx<T> *__restrict__ scr, const cx<T> *__restrict__ tw2, int pitch) {
+    using C = ColFft<T, LOGN>;
+    extern __shared__ unsigned char smem_raw[];
+    cx<T> *s = reinterpret_cast<cx<T> *>(smem_raw);
+    constexpr int N = C::N;
+    const int nb = gridDim.x, b = (nb & 7) ? (int)blockIdx.x : (int)(blockIdx.x & 7) * (nb >> 3) + (blockIdx.x >> 3);
+    const int x0 = b * C::CW, g = threadIdx.x, col0 = g & (C::CW - 1), j0 = g >> C::LCW;
+    const bool live = j0 < N / 16;
+    auto load = [&](int p, cx<T>(&a)[16]) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int ky = 2 * (j0 + r * (N / 16)) + p;
+            a[r] = live ? at32(Y, (unsigned)(ky * pitch + x0 + col0)) : mk<T>((T)0, (T)0);
+        }
+        if (live && x0 + col0 == 0) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int ky = 2 * (j0 + r * (N / 16)) + p, km = (2 * N - ky) & (2 * N - 1);
+                const cx<T> m = Y[(size_t)km * pitch], b = Y[(size_t)ky * pitch + N], bm = Y[(size_t)km * pitch + N];
+                const cx<T> h0 = mk<T>((T)0.5 * (a[r].x + m.x), (T)0.5 * (a[r].y - m.y));
+                const cx<T> hn = mk<T>((T)0.5 * (b.x + bm.x), (T)0.5 * (b.y - bm.y));
+                a[r] = mk<T>(h0.x - hn.y, h0.y + hn.x);
+            }
+        }
+    };
+    cx<T> ev[16], od[16];
+    load(0, ev);
+    load(1, od);
+    C::run(s, tw2, true, g, ev);
+    const int g2 = fresh(g);
+    C::run(s, tw2, true, g2, od);
+    C::visit(fresh(g2), [&](int i, int col, auto q) {
+        at32(scr, (unsigned)(i * C::SP + x0 + col)) = ev[q] + mulc(od[q], C::twist(tw2, i));
+    });
+}
+
+// The two column launches of image side N = 2^logN (16 .. 4096).
+template <typename T, int LOGN>
+void half_cols_launch(ri_ctx *c, Prec<T> &p, const cx<T> *in, cx<T> *out, bool inv, hipStream_t s) {
+    using C = ColFft<T, LOGN>;
+    const int stripes = C::N / C::CW, pitch = half_pitch(C::N);
+    if (inv)
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_half_icols<T, LOGN>), dim3(stripes), dim3(C::NT), C::LDS, s, in, out, p.tw,
+                           pitch);
+    else
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_half_cols<T, LOGN>), dim3(2 * stripes), dim3(C::NT), C::LDS, s, in, out,
+                           p.tw, pitch);
+}
+
+template <typename T>
+void half_cols(ri_ctx *c, Prec<T> &p, const cx<T> *in, cx<T> *out, bool inv, hipStream_t s) {
+    switch (c->logNp - 1) {
+        case 4: return half_cols_launch<T, 4>(c, p, in, out, inv, s);
+        case 5: return half_cols_launch<T, 5>(c, p, in, out, inv, s);
+        case 6: return half_cols_launch<T, 6>(c, p, in, out, inv, s);
+        case 7: return half_cols_launch<T, 7>(c, p, in, out, inv, s);
+        case 8: return half_cols_launch<T, 8>(c, p, in, out, inv, s);
+        case 9: return half_cols_launch<T, 9>(c, p, in, out, inv, s);
+        case 10: return half_cols_launch<T, 10>(c, p, in, out, inv, s);
+        case 11: return half_cols_launch<T, 11>(c, p, in, out, inv, s);
+        case 12: return half_cols_launch<T, 12>(c, p, in, out, inv, s);
+        default: throw Error(RI_EUNSUPPORTED, "image side outside 16 .. 4096");
+    }
 }
 
 template <typename T, int L>
@@ -426,11 +794,14 @@ constexpr int lanes_per_column() { return (L * (int)sizeof(cx<T>)) / 512 < 1 ? 1
 
 int threads_for(int L, int CW) { return L * CW / 16 < 64 ? 64 : L * CW / 16; }
 
+// Column transforms of grid_io (scratch) into grid_out; grid_out == grid_io
+// leaves the second pass in place (permuted rows). band: the N packed band rows
+// when they are the input (N' = 8192 in FP32, forward), else NULL.
 template <typename T>
 void colfft(ri_ctx *c, cx<T> *grid_io, cx<T> *grid_out, const cx<T> *tw, bool inv, bool band_in, bool band_out,
-            hipStream_t s) {
+            hipStream_t s, const cx<T> *band = nullptr) {
     const int logNp = c->logNp, Np = c->Np;
-    const int logN1 = (logNp + 1) / 2, logN2 = logNp / 2;
+    const int logN1 = full_log_n1(logNp), logN2 = logNp - logN1;
     if (logNp == 12 || logNp == 13) {
         // 4096 = 64 x 64 and 8192 = 128 x 64: both column passes in registers,
         // at most 64 complex FP32 (32 FP64) points per lane
@@ -439,6 +810,9 @@ void colfft(ri_ctx *c, cx<T> *grid_io, cx<T> *grid_out, const cx<T> *tw, bool in
         if (logNp == 12)
             hipLaunchKernelGGL(HIP_KERNEL_NAME(k_colpass_a_reg<T, 64, QA4>), dim3(Np / (64 / QA4), 64), dim3(64), 0,
                                s, grid_io, tw, c->N, logNp, band_in ? 1 : 0, inv ? 1 : 0);
+        else if (band != nullptr)
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_colpass_a_band<T>), dim3(Np / 64, 64, 2), dim3(64), 0, s, band,
+                               grid_io, tw, logNp);
         else
             hipLaunchKernelGGL(HIP_KERNEL_NAME(k_colpass_a_reg<T, 128, QA8>), dim3(Np / (64 / QA8), 64), dim3(64), 0,
                                s, grid_io, tw, c->N, logNp, band_in ? 1 : 0, inv ? 1 : 0);
@@ -467,8 +841,6 @@ void colfft(ri_ctx *c, cx<T> *grid_io, cx<T> *grid_out, const cx<T> *tw, bool in
 
 }  // namespace
 
-// x (N x N) -> F Z_s x in p.gridB[s] for every w-stack s (row FFT into gridA band rows,
-// columns A in place, B into gridB[s])
 // Row transforms pad LDS by one element per 32 (fewer bank conflicts) when it fits.
 template <typename T>
 bool row_pad(ri_ctx *c) { return sizeof(cx<T>) * (size_t)(c->Np + c->Np / 32) <= (size_t)c->dev.lds_per_block; }
@@ -476,21 +848,35 @@ bool row_pad(ri_ctx *c) { return sizeof(cx<T>) * (size_t)(c->Np + c->Np / 32) <=
 template <typename T>
 size_t row_lds(ri_ctx *c) { return sizeof(cx<T>) * (size_t)(row_pad<T>(c) ? c->Np + c->Np / 32 : c->Np); }
 
+// Z and the row FFTs of x into dst (rows as k_zpad_rowfft places them).
+template <typename T>
+void launch_zpad_rows(ri_ctx *c, Prec<T> &p, const T *x, cx<T> *dst, const cx<T> *chirp, int rowmask,
+                      const Clear<T> &z, hipStream_t s) {
+    if (row_pad<T>(c))
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_zpad_rowfft<T, true>), dim3(c->N), dim3(threads_for(c->Np, 1)),
+                           row_lds<T>(c), s, x, dst, p.icorr, p.tw, c->N, c->logNp, chirp, rowmask, z);
+    else
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_zpad_rowfft<T, false>), dim3(c->N), dim3(threads_for(c->Np, 1)),
+                           row_lds<T>(c), s, x, dst, p.icorr, p.tw, c->N, c->logNp, chirp, rowmask, z);
+}
+
+template <typename T>
+void require_row_fits(ri_ctx *c) {
+    if (sizeof(cx<T>) * (size_t)c->Np > (size_t)c->dev.lds_per_block)
+        throw Error(RI_EUNSUPPORTED, "grid row does not fit the workgroup LDS");
+}
+
+// x (N x N) -> F Z_s x in p.gridB[s] for every w-stack s (row FFT into gridA band rows,
+// columns A in place, B into gridB[s])
 template <typename T>
 void fwd_zpad_fft(ri_ctx *c, Prec<T> &p, const T *x, hipStream_t s) {
     const int Np = c->Np;
     ProfScope prof(c, PROF_FFT, s);
-    if (sizeof(cx<T>) * (size_t)Np > (size_t)c->dev.lds_per_block)
-        throw Error(RI_EUNSUPPORTED, "grid row does not fit the workgroup LDS");
+    require_row_fits<T>(c);
     // one FFT per w-stack (a single one without stacking); gridA is the scratch
     for (int st = 0; st < c->P; ++st) {
-        const cx<T> *ch = c->P > 1 ? p.chirp + (size_t)st * c->N * c->N : nullptr;
-        if (row_pad<T>(c))
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_zpad_rowfft<T, true>), dim3(c->N), dim3(threads_for(Np, 1)),
-                               row_lds<T>(c), s, x, p.gridA, p.icorr, p.tw, c->N, c->logNp, ch);
-        else
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_zpad_rowfft<T, false>), dim3(c->N), dim3(threads_for(Np, 1)),
-                               row_lds<T>(c), s, x, p.gridA, p.icorr, p.tw, c->N, c->logNp, ch);
+        launch_zpad_rows<T>(c, p, x, p.gridA, c->P > 1 ? p.chirp + (size_t)st * c->N * c->N : nullptr, Np - 1,
+                            Clear<T>(), s);
         colfft<T>(c, p.gridA, p.gridB + (size_t)st * Np * Np, p.tw, false, true, false, s);
     }
 }
@@ -513,6 +899,96 @@ void adj_fft_crop(ri_ctx *c, Prec<T> &p, T *x, hipStream_t s) {
     }
 }
 
+template <typename T>
+Clear<T> pass_clear(ri_ctx *c, Prec<T> &p, bool with_grid, int32_t *counter, double *part) {
+    Clear<T> z;
+    z.grid = p.gridA;
+    if (with_grid) z.n = c->P == 1 ? (int64_t)c->Np * half_pitch(c->N) : (int64_t)c->P * c->Np * c->Np;
+    z.counter = counter;
+    z.part = part;
+    z.npart = part ? c->n_partials : 0;
+    return z;
+}
+
+template <typename T>
+void clear(const Clear<T> &z, hipStream_t s) {
+    const int64_t n = std::max<int64_t>(z.n * (int64_t)sizeof(cx<T>) / 16, z.npart);
+    hipLaunchKernelGGL(k_clear<T>, dim3((int)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 4096))),
+                       dim3(256), 0, s, z);
+}
+
+// The scratch lies in gridB behind the half-plane grid: N'(pitch) + N sp <= N'^2 cells.
+template <typename T>
+cx<T> *half_scratch(ri_ctx *c, Prec<T> &p) { return p.gridB + (size_t)c->Np * half_pitch(c->N); }
+
+template <typename T>
+void fwd_half_fft(ri_ctx *c, Prec<T> &p, const T *x, const Clear<T> &z, hipStream_t s) {
+    const int N = c->N, Np = c->Np;
+    ProfScope prof(c, PROF_FFT, s);
+    cx<T> *scr = half_scratch<T>(c, p);
+    if (row_pad<T>(c))
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_half_rows<T, true>), dim3(N / 2), dim3(threads_for(Np, 1)), row_lds<T>(c),
+                           s, x, scr, p.icorr, p.tw, N, c->logNp, z);
+    else
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_half_rows<T, false>), dim3(N / 2), dim3(threads_for(Np, 1)),
+                           row_lds<T>(c), s, x, scr, p.icorr, p.tw, N, c->logNp, z);
+    half_cols<T>(c, p, scr, p.gridB, false, s);
+}
+
+template <typename T>
+void adj_half_fft(ri_ctx *c, Prec<T> &p, T *x, hipStream_t s) {
+    const int N = c->N, Np = c->Np;
+    ProfScope prof(c, PROF_FFT, s);
+    cx<T> *scr = half_scratch<T>(c, p);
+    half_cols<T>(c, p, p.gridA, scr, true, s);
+    if (row_pad<T>(c))
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_half_irows<T, true>), dim3(N / 2), dim3(threads_for(Np, 1)),
+                           row_lds<T>(c), s, scr, x, p.icorr, p.tw, N, c->logNp);
+    else
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_half_irows<T, false>), dim3(N / 2), dim3(threads_for(Np, 1)),
+                           row_lds<T>(c), s, scr, x, p.icorr, p.tw, N, c->logNp);
+}
+
+// Whole plane of one real image into gridB, all passes in place there (rows
+// end permuted, see full_log_n1), which leaves gridA to be cleared by the row launch. At
+// N' = 8192 in FP32 the row spectra pass through the part of gridA behind the
+// half-plane output grid (k_colpass_a_band works out of place).
+template <typename T>
+void fwd_full_fft(ri_ctx *c, Prec<T> &p, const T *x, const Clear<T> &z, hipStream_t s) {
+    ProfScope prof(c, PROF_FFT, s);
+    cx<T> *band = nullptr;
+    if (sizeof(T) == 4 && c->logNp == 13) band = p.gridA + (size_t)c->Np * half_pitch(c->N);
+    launch_zpad_rows<T>(c, p, x, band ? band : p.gridB, nullptr, band ? c->N - 1 : c->Np - 1, z, s);
+    colfft<T>(c, p.gridB, p.gridB, p.tw, false, true, false, s, band);
+}
+
+template <typename T>
+void operator_fft(ri_ctx *c, Prec<T> &p, bool folded, const T *x, const Clear<T> &z, hipStream_t s) {
+    require_row_fits<T>(c);
+    if (c->P > 1) {   // each stack's image is complex (its phase screen)
+        fwd_zpad_fft<T>(c, p, x, s);
+        clear<T>(z, s);
+    } else if (folded) {
+        fwd_half_fft<T>(c, p, x, z, s);
+    } else {
+        fwd_full_fft<T>(c, p, x, z, s);
+    }
+}
+
+template <typename T>
+void operator_adj_fft(ri_ctx *c, Prec<T> &p, T *x, hipStream_t s) {
+    if (c->P == 1) adj_half_fft<T>(c, p, x, s);
+    else adj_fft_crop<T>(c, p, x, s);
+}
+
+template Clear<float> pass_clear<float>(ri_ctx *, Prec<float> &, bool, int32_t *, double *);
+template Clear<double> pass_clear<double>(ri_ctx *, Prec<double> &, bool, int32_t *, double *);
+template void clear<float>(const Clear<float> &, hipStream_t);
+template void clear<double>(const Clear<double> &, hipStream_t);
+template void operator_fft<float>(ri_ctx *, Prec<float> &, bool, const float *, const Clear<float> &, hipStream_t);
+template void operator_fft<double>(ri_ctx *, Prec<double> &, bool, const double *, const Clear<double> &, hipStream_t);
+template void operator_adj_fft<float>(ri_ctx *, Prec<float> &, float *, hipStream_t);
+template void operator_adj_fft<double>(ri_ctx *, Prec<double> &, double *, hipStream_t);
 template void fwd_zpad_fft<float>(ri_ctx *, Prec<float> &, const float *, hipStream_t);
 template void fwd_zpad_fft<double>(ri_ctx *, Prec<double> &, const double *, hipStream_t);
 template void adj_fft_crop<float>(ri_ctx *, Prec<float> &, float *, hipStream_t);

@@ -58,6 +58,9 @@ struct TileArgs {
     int n_items;
     int *counter;
     int tile, H, W, logNp, hmax, kb_terms;
+    int Nh;                        // half-plane grids hold columns 0 .. Nh
+    int xhalf, xpitch, xr1, xr2;   // X: half plane?, row pitch, row ky at (ky mod 2^xr1) << xr2 | ky >> xr1
+    int yhalf, ypitch;             // Y
     T kbc[KB_TERMS_MAX];           // kappa(t) = sum_k kbc[k] z^k, z = 1 - (2t/7)^2
     const uint2 *rec;              // per visibility: (cell, plane | h << 16 | w-stack << 20)
     const T *frac;
@@ -190,16 +193,26 @@ __device__ __forceinline__ void global_add(T *p, T v) {
     __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Tap l (0 .. 2h) of plane pl; of a mirrored visibility the conjugate of tap 2h - l.
+template <typename T>
+__device__ __forceinline__ cx<T> wtap(const TileArgs<T> &a, int pl, int h, int l, bool mir) {
+    cx<T> w = a.wtaps[(size_t)pl * (2 * a.hmax + 1) + a.hmax + (mir ? h - l : l - h)];
+    if (mir) w.y = -w.y;
+    return w;
+}
+
 // Axis weights of one G row into gg[0..S) (u) and gg[18..18+S) (v) by the 16
 // lanes of a group: KB taps into kbg, the plane's w-taps into wk, then
 //   g[a] = sum_q k_w[q] kappa(f - (a - h - 3) - q).
+// mir: the taps of a mirrored visibility, conj k_w[-q]. fs = -1 undoes the
+// mirroring of the stored fraction (with mir false).
 template <typename T>
 __device__ __forceinline__ void axis_weights(const TileArgs<T> &a, int m, int pl, int h, int S, int lane, T *kbg,
-                                             cx<T> *wk, cx<T> *gg) {
-    const T fu = a.frac[2 * (size_t)m], fv = a.frac[2 * (size_t)m + 1];
+                                             cx<T> *wk, cx<T> *gg, bool mir, T fs = (T)1) {
+    const T fu = fs * a.frac[2 * (size_t)m], fv = fs * a.frac[2 * (size_t)m + 1];
     if (lane < 7) kbg[lane] = kb_weight<T>(fu - (T)(lane - 3), a);
     else if (lane >= 8 && lane < 15) kbg[lane] = kb_weight<T>(fv - (T)(lane - 11), a);
-    if (lane <= 2 * h) wk[lane] = a.wtaps[(size_t)pl * (2 * a.hmax + 1) + a.hmax - h + lane];
+    if (lane <= 2 * h) wk[lane] = wtap(a, pl, h, lane, mir);
     wave_sync();
     for (int idx = lane; idx < 2 * S; idx += 16) {
         const int axis = idx < S ? 0 : 1;
@@ -285,13 +298,43 @@ k_tiles(TileArgs<T> a) {
         const TileItem item = a.items[it];
         const int y0 = item.ty0 - a.H, x0 = item.tx0 - a.H;
         // all of an item's visibilities belong to one w-stack, whose grids follow
-        const size_t goff = (size_t)(a.rec[item.vb].y >> 20) << (2 * a.logNp);
+        const size_t goff = (size_t)((a.rec[item.vb].y >> 20) & 0x7FFu) << (2 * a.logNp);
         const cx<T> *Xg = a.X + goff;
         cx<T> *Yg = a.Y + goff;
+        // row ky and column of subgrid cell (r, cc): wrapped round the plane; on a
+        // half plane a cell at kx > N is the conjugate of cell (-ky, -kx)
+        const bool inner = x0 >= 0 && x0 + W <= a.Nh + 1;
+        auto cell_at = [&](int r, int cc, bool half, int &y, int &x) -> bool {
+            y = y0 + r;
+            x = x0 + cc;
+            bool cj = false;
+            if (!inner) {
+                x &= Npm;
+                if (half && x > a.Nh) {
+                    x = Npm + 1 - x;
+                    y = -y;
+                    cj = true;
+                }
+            }
+            y &= Npm;
+            return cj;
+        };
+        auto flush = [&](int r, int cc, T re, T im) {
+            int y, x;
+            const bool cj = cell_at(r, cc, a.yhalf, y, x);
+            cx<T> *dst = Yg + ((unsigned)y * (unsigned)a.ypitch + (unsigned)x);
+            global_add(&dst->x, re);
+            global_add(&dst->y, cj ? -im : im);
+        };
         if (OP & OP_DEGRID) {
             for (int e = tid; e < WW; e += blockDim.x) {
                 const int r = e / W, cc = e - r * W;
-                Xs[r * XS + cc] = Xg[((size_t)((y0 + r) & Npm) << a.logNp) + ((x0 + cc) & Npm)];
+                int y, x;
+                const bool cj = cell_at(r, cc, a.xhalf, y, x);
+                const int row = ((y & ((1 << a.xr1) - 1)) << a.xr2) | (y >> a.xr1);
+                cx<T> xv = Xg[(unsigned)row * (unsigned)a.xpitch + (unsigned)x];
+                if (cj) xv.y = -xv.y;
+                Xs[r * XS + cc] = xv;
             }
         }
         if (!GA && (OP & OP_GRID)) {
@@ -319,10 +362,15 @@ k_tiles(TileArgs<T> a) {
         // the data value is issued with the row instead, which keeps that
         // kernel's registers within four waves
         auto ydata = [&](int mm) -> cx<T> {
-            if (OP == OP_GRID) return a.yuser[a.perm[mm]];
+            if (OP == OP_GRID) return data_at(a.yuser, a.perm[mm]);
             if (a.ysorted) return a.ysorted[mm];
-            if (a.yuser) return a.yuser[a.perm[mm]];
+            if (a.yuser) return data_at(a.yuser, a.perm[mm]);
             return mk<T>((T)0, (T)0);
+        };
+        auto put_vis = [&](cx<T> v, int mm) {
+            const int32_t p = a.perm[mm];
+            if (p < 0) v.y = -v.y;
+            a.yout[p & PERM_INDEX] = v;
         };
         uint2 rec_n = make_uint2(0u, 0u);
         T f_n = (T)0;
@@ -379,7 +427,7 @@ k_tiles(TileArgs<T> a) {
                 // the plane's w-taps first, then the next visibility's record and
                 // fraction (loads complete in order, so waiting for the taps
                 // leaves the prefetch in flight)
-                if (lane <= 2 * h) wk[lane] = a.wtaps[(size_t)pl * (2 * a.hmax + 1) + a.hmax - h + lane];
+                if (lane <= 2 * h) wk[lane] = wtap(a, pl, h, lane, (rec.y & REC_MIRROR) != 0);
                 if (vi + GROUPS < item.vc) {
                     rec_n = a.rec[m + GROUPS];
                     if (OP & OP_GRID) y_n = ydata(m + GROUPS);
@@ -442,7 +490,7 @@ k_tiles(TileArgs<T> a) {
                     acc.y = sum16(acc.y);
                 }
                 if (OP == OP_DEGRID) {
-                    if (lane == 0) a.yout[a.perm[m]] = acc;
+                    if (lane == 0) put_vis(acc, m);
                 } else if (OP == OP_FUSED) {
                     r = acc - yv;
                     if (lane == 0) r2 += (double)r.x * (double)r.x + (double)r.y * (double)r.y;
@@ -521,7 +569,7 @@ k_tiles(TileArgs<T> a) {
                     acc.y = sum16(acc.y);
                 }
                 if (OP == OP_DEGRID) {
-                    if (lane == 0) a.yout[a.perm[m]] = acc;
+                    if (lane == 0) put_vis(acc, m);
                 } else if (OP == OP_FUSED) {
                     r = acc - ydv;
                     if (lane == 0) r2 += (double)r.x * (double)r.x + (double)r.y * (double)r.y;
@@ -674,20 +722,16 @@ k_tiles(TileArgs<T> a) {
             for (int e = tid; e < WW; e += blockDim.x) {
                 const cx<T> v = Xs[e] + slot[e];
                 if (v.x != (T)0 || v.y != (T)0) {
-                    const int r = e / W, cc = e - r * W;
-                    cx<T> *dst = Yg + ((size_t)((y0 + r) & Npm) << a.logNp) + ((x0 + cc) & Npm);
-                    global_add(&dst->x, v.x);
-                    global_add(&dst->y, v.y);
+                    const int r = e / W;
+                    flush(r, e - r * W, v.x, v.y);
                 }
             }
         } else if constexpr ((OP & OP_GRID) != 0) {
             for (int e = tid; e < WW; e += blockDim.x) {
                 const double vr = Yr[e], vi = Yi[e];
                 if (vr != 0.0 || vi != 0.0) {
-                    const int r = e / W, cc = e - r * W;
-                    cx<T> *dst = Yg + ((size_t)((y0 + r) & Npm) << a.logNp) + ((x0 + cc) & Npm);
-                    global_add(&dst->x, (T)vr);
-                    global_add(&dst->y, (T)vi);
+                    const int r = e / W;
+                    flush(r, e - r * W, (T)vr, (T)vi);
                 }
             }
         }
@@ -716,7 +760,7 @@ __global__ void __launch_bounds__(256) k_fill_csr(TileArgs<double> a, int64_t M,
         const uint2 rec = a.rec[m];
         const int pl = (int)(rec.y & 0xFFFFu), h = (int)((rec.y >> 16) & 0xFu);
         const int S = 2 * h + 7, SS = S * S;
-        axis_weights<double>(a, (int)m, pl, h, S, lane, kbg, wk, gg);
+        axis_weights<double>(a, (int)m, pl, h, S, lane, kbg, wk, gg, (rec.y & REC_MIRROR) != 0);
         const int64_t rp = rowptr[m];
         for (int t = lane; t < SS; t += 16) {
             const int ay = t / S, ax = t - ay * S;
@@ -742,7 +786,7 @@ __global__ void __launch_bounds__(256) k_fill_sep(TileArgs<double> a, int64_t M,
         const uint2 rec = a.rec[m];
         const int pl = (int)(rec.y & 0xFFFFu), h = (int)((rec.y >> 16) & 0xFu);
         const int S = 2 * h + 7;
-        axis_weights<double>(a, (int)m, pl, h, S, lane, kbg, wk, gg);
+        axis_weights<double>(a, (int)m, pl, h, S, lane, kbg, wk, gg, (rec.y & REC_MIRROR) != 0);
         cx<T> *o = out + (size_t)m * 34;
         for (int cidx = lane; cidx < 17; cidx += 16) {
             const cx<double> u = cidx < S ? gg[cidx] : mk<double>(0.0, 0.0);
@@ -778,10 +822,13 @@ __global__ void __launch_bounds__(256) k_fill_holo(TileArgs<double> a, int64_t M
     for (int64_t i = (int64_t)blockIdx.x * GROUPS + grp; i < M; i += (int64_t)gridDim.x * GROUPS) {
         const int64_t m = (int64_t)((uint64_t)i * (uint64_t)stride % (uint64_t)M);   // M < 2^31
         const uint2 rec = a.rec[m];
-        const int cu = (int)(rec.x & 0xFFFFu), cv = (int)(rec.x >> 16);
+        // H is the full-plane operator: a mirrored visibility is turned back
+        const bool mir = (rec.y & REC_MIRROR) != 0;
+        const int cu = mir ? (Npm + 1 - (int)(rec.x & 0xFFFFu)) & Npm : (int)(rec.x & 0xFFFFu);
+        const int cv = mir ? (Npm + 1 - (int)(rec.x >> 16)) & Npm : (int)(rec.x >> 16);
         const int pl = (int)(rec.y & 0xFFFFu), h = (int)((rec.y >> 16) & 0xFu);
         const int S = 2 * h + 7;
-        axis_weights<double>(a, (int)m, pl, h, S, lane, kbg, wk, gg);
+        axis_weights<double>(a, (int)m, pl, h, S, lane, kbg, wk, gg, false, mir ? -1.0 : 1.0);
         for (int ay = 0; ay < S; ++ay) {
             const int ky = (cv + ay - h - 3) & Npm;
             const int trow = (ky >> 5) * ntx, cyl = (ky & 31) * 32;
@@ -818,6 +865,15 @@ TileArgs<T> make_args(ri_ctx *c, const View &v, Prec<T> &p) {
     a.W = v.tile + 2 * c->H;
     a.logNp = c->logNp;
     a.hmax = c->hmax;
+    a.Nh = c->N;
+    a.xhalf = v.folded;
+    a.xpitch = v.folded ? half_pitch(c->N) : c->Np;
+    if (c->P == 1 && !v.folded) {
+        a.xr1 = full_log_n1(c->logNp);
+        a.xr2 = c->logNp - a.xr1;
+    }
+    a.yhalf = c->P == 1;
+    a.ypitch = a.yhalf ? half_pitch(c->N) : c->Np;
     // Horner coefficients of the KB kernel as a power series in z (FP64)
     double i0b = 1.0, t = 1.0, q = 0.25 * c->beta * c->beta;
     for (int k = 1; k < 500; ++k) { t = t * q / ((double)k * k); i0b += t; if (t < 1e-17 * i0b) break; }
@@ -864,7 +920,6 @@ void launch_op_gb(ri_ctx *c, TileArgs<T> &a, hipStream_t s) {
     int nwg = std::min(c->dev.cu_count * per_cu, std::max(1, a.n_items));
     if (nwg > c->n_partials) nwg = c->n_partials;
     hipLaunchKernelGGL(HIP_KERNEL_NAME(k_tiles<T, OP, GM, GB>), dim3(nwg), dim3(256), lds, s, a);
-    if (OP == OP_FUSED && nwg < c->n_partials) fill_zero_f64(a.r2part + nwg, c->n_partials - nwg, s);
 }
 
 // Gridding through separable rows in FP32 takes the gather form when the
@@ -895,10 +950,7 @@ void launch_mode(ri_ctx *c, TileArgs<T> &a, int op, hipStream_t s) {
 template <typename T>
 void launch_tiles(ri_ctx *c, const View &v, Prec<T> &p, int op, int gm, const cx<T> *y_sorted,
                   const cx<T> *y_user, cx<T> *y_out_user, double *r2_partials, hipStream_t s, int32_t *counter) {
-    if (c->M == 0 || v.n_items == 0) {
-        if (op == OP_FUSED && r2_partials) fill_zero_f64(r2_partials, c->n_partials, s);
-        return;
-    }
+    if (c->M == 0 || v.n_items == 0) return;
     TileArgs<T> a = make_args<T>(c, v, p);
     a.X = p.gridB;
     a.Y = p.gridA;
@@ -916,7 +968,6 @@ void launch_tiles(ri_ctx *c, const View &v, Prec<T> &p, int op, int gm, const cx
             throw Error(RI_EINVAL, "no stored axis factors of this precision");
         a.sepw = (const cx<T> *)c->sep.w;
     }
-    fill_zero_i32(a.counter, 1, s);
     ProfScope prof(c, PROF_TILES, s);
     if (gm == RI_G_OTF) launch_mode<T, RI_G_OTF>(c, a, op, s);
     else if (gm == RI_G_SEP) launch_mode<T, RI_G_SEP>(c, a, op, s);

@@ -21,7 +21,27 @@ template <typename T>
 __global__ void k_permute(const cx<T> *__restrict__ yu, cx<T> *__restrict__ yi, const int32_t *__restrict__ perm,
                           int64_t M) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < M; i += (int64_t)gridDim.x * blockDim.x)
-        yi[i] = yu[perm[i]];
+        yi[i] = data_at(yu, perm[i]);
+}
+
+// Sums of two sets of partials: block k < count_a forms out_a[k], the rest out_b (fixed order).
+__global__ void __launch_bounds__(1024) k_reduce2(const double *pa, int na, int sa, int ca, double *oa,
+                                                  const double *pb, int nb, int sb, double *ob) {
+    __shared__ double s_red[16];
+    const bool first = (int)blockIdx.x < ca;
+    const int k = first ? (int)blockIdx.x : (int)blockIdx.x - ca;
+    const double *p = first ? pa : pb;
+    const int n = first ? na : nb, stride = first ? sa : sb;
+    double acc = 0.0;
+    for (int i = threadIdx.x; i < n; i += blockDim.x) acc += p[(size_t)i * stride + k];
+    for (int o = 32; o >= 1; o >>= 1) acc += __shfl_xor(acc, o);
+    if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double t = 0.0;
+        for (int w = 0; w < 16; ++w) t += s_red[w];
+        (first ? oa : ob)[k] = t;
+    }
 }
 
 __device__ __forceinline__ double block_sum(double v, double *s_red) {
@@ -214,10 +234,6 @@ void fill_real(T *p, int64_t n, T v, hipStream_t s) {
 template void fill_real<float>(float *, int64_t, float, hipStream_t);
 template void fill_real<double>(double *, int64_t, double, hipStream_t);
 
-void fill_zero_i32(int32_t *p, int64_t n, hipStream_t s) {
-    if (n <= 0) return;
-    hipLaunchKernelGGL(k_fill<int32_t>, dim3(grid_for(n)), dim3(256), 0, s, p, n, 0);
-}
 void fill_zero_f64(double *p, int64_t n, hipStream_t s) {
     if (n <= 0) return;
     hipLaunchKernelGGL(k_fill<double>, dim3(grid_for(n)), dim3(256), 0, s, p, n, 0.0);
@@ -246,6 +262,12 @@ void haar_prox(ri_ctx *c, const T *x_in, const T *g, T gamma, const T *z_direct,
 
 void reduce_partials(const double *partials, int n, int stride, int count, double *out, hipStream_t s) {
     hipLaunchKernelGGL(k_reduce, dim3(1), dim3(256), 0, s, partials, n, stride, count, out);
+}
+
+void reduce_partials2(const double *part_a, int n_a, int stride_a, int count_a, double *out_a, const double *part_b,
+                      int n_b, int stride_b, int count_b, double *out_b, hipStream_t s) {
+    hipLaunchKernelGGL(k_reduce2, dim3(count_a + count_b), dim3(1024), 0, s, part_a, n_a, stride_a, count_a, out_a,
+                       part_b, n_b, stride_b, out_b);
 }
 
 template <typename T>

@@ -53,11 +53,10 @@ void gradient_in_workspace(ri_ctx *c, unsigned char *ws, const T *x, const void 
     } else if (y != RI_NO_DATA) {
         y_user = static_cast<const cx<T> *>(y);
     }
-    fwd_zpad_fft<T>(c, p, x, s);
-    fill_zero<T>(p.gridA, (int64_t)c->P * c->Np * c->Np, s);
+    operator_fft<T>(c, p, c->view.folded, x, pass_clear<T>(c, p, true, counter, part), s);
     launch_tiles<T>(c, c->view, p, OP_FUSED, c->d.g_mode, y_sorted, y_user, nullptr, part, s,
                     counter);
-    adj_fft_crop<T>(c, p, g, s);
+    operator_adj_fft<T>(c, p, g, s);
     if (r2) reduce_partials(part, c->n_partials, 1, 1, r2, s);
 }
 

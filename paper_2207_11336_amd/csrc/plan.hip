@@ -271,13 +271,19 @@ void build_plan(ri_ctx *c, const double *uvw) {
 // cut each (block, tile) run into work items and sort the items by decreasing
 // work so the persistent launch hands out the largest first.
 // ---------------------------------------------------------------------------
-void build_view(ri_ctx *c, View &v, int tile, int frac_bytes) {
+void build_view(ri_ctx *c, View &v, int tile, int frac_bytes, bool fold) {
     const int64_t M = c->M;
     const int Np = c->Np, nta = Np / tile;
     const int64_t ntiles = (int64_t)nta * nta;
     const int nb = (int)c->block_offsets.size() - 1;
     v.tile = tile;
     v.frac_bytes = frac_bytes;
+
+    // window centres of the view, mirrored into c_u <= N when folded
+    v.folded = fold && c->P == 1;
+    auto mirrored = [&](int64_t m) { return v.folded && c->cu[m] > c->N; };
+    auto view_cu = [&](int64_t m) { return mirrored(m) ? Np - c->cu[m] : c->cu[m]; };
+    auto view_cv = [&](int64_t m) { return mirrored(m) ? (Np - c->cv[m]) & (Np - 1) : c->cv[m]; };
 
     // Counting sort by (block, w-stack), then, inside each such segment, by uv
     // tile (the tile counters are reset only where a segment touched them, so
@@ -304,7 +310,7 @@ void build_view(ri_ctx *c, View &v, int tile, int frac_bytes) {
     for (int64_t k = 0; k < nk1; ++k) {
         const int64_t s0 = c1[k], e0 = c1[k + 1];
         if (s0 == e0) continue;
-        auto tile_of = [&](int64_t m) { return (int64_t)(c->cv[m] / tile) * nta + c->cu[m] / tile; };
+        auto tile_of = [&](int64_t m) { return (int64_t)(view_cv(m) / tile) * nta + view_cu(m) / tile; };
         for (int64_t i = s0; i < e0; ++i) ct[tile_of(ord1[i]) + 1]++;
         // prefix over the touched tiles only, in tile order
         std::vector<int64_t> touched;
@@ -382,11 +388,14 @@ void build_view(ri_ctx *c, View &v, int tile, int frac_bytes) {
     if (frac_bytes == 4) f32.resize(2 * M); else f64.resize(2 * M);
     for (int64_t i = 0; i < M; ++i) {
         int64_t m = order[i];
-        perm[i] = (int32_t)m;
-        rec[i].x = ((uint32_t)c->cv[m] << 16) | (uint32_t)c->cu[m];
-        rec[i].y = (uint32_t)c->plane[m] | ((uint32_t)c->plane_h[c->plane[m]] << 16) | ((uint32_t)c->stack[m] << 20);
+        const bool mir = mirrored(m);
+        perm[i] = (int32_t)m | (mir ? ~PERM_INDEX : 0);
+        rec[i].x = ((uint32_t)view_cv(m) << 16) | (uint32_t)view_cu(m);
+        rec[i].y = (uint32_t)c->plane[m] | ((uint32_t)c->plane_h[c->plane[m]] << 16) |
+                   ((uint32_t)c->stack[m] << 20) | (mir ? REC_MIRROR : 0u);
         double fu = c->pu[m] - std::floor(c->pu[m] + 0.5);
         double fv = c->pv[m] - std::floor(c->pv[m] + 0.5);
+        if (mir) { fu = -fu; fv = -fv; }
         if (frac_bytes == 4) { f32[2 * i] = (float)fu; f32[2 * i + 1] = (float)fv; }
         else { f64[2 * i] = fu; f64[2 * i + 1] = fv; }
     }
@@ -424,7 +433,9 @@ void ensure_prec(ri_ctx *c, Prec<T> &p) {
     for (size_t i = 0; i < nt; ++i) wt[i] = mk<T>((T)c->wtaps64[2 * i], (T)c->wtaps64[2 * i + 1]);
     p.wtaps = upload(c, wt.data(), nt);
     const size_t ng = (size_t)c->P * Np * Np;
-    p.gridA = (cx<T> *)dev_alloc(c, sizeof(cx<T>) * ng);
+    // half-plane grid and the N packed band rows of the forward transform (N' = 8192)
+    const size_t behind = sizeof(T) == 4 && c->P == 1 && c->logNp == 13 ? (size_t)16 * Np : 0;
+    p.gridA = (cx<T> *)dev_alloc(c, sizeof(cx<T>) * (ng + behind));
     p.gridB = (cx<T> *)dev_alloc(c, sizeof(cx<T>) * ng);
     if (c->P > 1) {
         // phase screens c_s(n) = exp(-2 pi i w_s (sqrt(1 - l^2 - m^2) - 1)), FP64 arithmetic

@@ -66,7 +66,7 @@ const View &view_fp64(ri_ctx *c) {
     if (!c->view64.items) {
         int t = c->view.tile > 0 ? c->view.tile : 16;
         while (t > 8 && lds_for_tile(t, c->H, 16) > (size_t)c->dev.lds_per_block) t /= 2;
-        build_view(c, c->view64, pick_tile(c, t, 16), 8);
+        build_view(c, c->view64, pick_tile(c, t, 16), 8, true);
     }
     return c->view64;
 }
@@ -81,26 +81,25 @@ Prec<double> &prec<double>(ri_ctx *c) { return c->p64; }
 template <typename T>
 void do_forward(ri_ctx *c, const T *x, cx<T> *y, hipStream_t s) {
     Prec<T> &p = prec<T>(c);
-    fwd_zpad_fft<T>(c, p, x, s);
+    operator_fft<T>(c, p, c->view.folded, x, pass_clear<T>(c, p, false, c->d_counter, nullptr), s);
     launch_tiles<T>(c, c->view, p, OP_DEGRID, c->d.g_mode, nullptr, nullptr, y, nullptr, s);
 }
 
 template <typename T>
 void do_adjoint(ri_ctx *c, const cx<T> *y, T *x, hipStream_t s) {
     Prec<T> &p = prec<T>(c);
-    fill_zero<T>(p.gridA, (int64_t)c->P * c->Np * c->Np, s);
+    clear<T>(pass_clear<T>(c, p, true, c->d_counter, nullptr), s);
     launch_tiles<T>(c, c->view, p, OP_GRID, c->d.g_mode, nullptr, y, nullptr, nullptr, s);
-    adj_fft_crop<T>(c, p, x, s);
+    operator_adj_fft<T>(c, p, x, s);
 }
 
 // g = Re{Phi^dagger (Phi x - y)} with y in internal order (or none); r2 partials in tile_part.
 template <typename T>
 void do_gradient(ri_ctx *c, const View &v, int gm, const T *x, const cx<T> *y_sorted, T *g, hipStream_t s) {
     Prec<T> &p = prec<T>(c);
-    fwd_zpad_fft<T>(c, p, x, s);
-    fill_zero<T>(p.gridA, (int64_t)c->P * c->Np * c->Np, s);
+    operator_fft<T>(c, p, v.folded, x, pass_clear<T>(c, p, true, c->d_counter, tile_part(c)), s);
     launch_tiles<T>(c, v, p, OP_FUSED, gm, y_sorted, nullptr, nullptr, tile_part(c), s);
-    adj_fft_crop<T>(c, p, g, s);
+    operator_adj_fft<T>(c, p, g, s);
 }
 
 template <typename T>
@@ -145,10 +144,9 @@ void fb_step_sorted(ri_ctx *c, const T *x_in, const cx<T> *ys, double gamma, int
     if (kind == RI_PROX_HAAR) {
         const int nwg = ((c->N / 16) * (c->N / 16) + 3) / 4;
         haar_prox<T>(c, x_in, p.img0, (T)gamma, nullptr, (T)param, x_out, img_part(c), s);
-        if (norms) {
-            reduce_partials(img_part(c), nwg, 2, 2, norms, s);
-            if (!holo) reduce_partials(tile_part(c), tiles_partials(c), 1, 1, norms + 2, s);
-        }
+        if (norms)
+            reduce_partials2(img_part(c), nwg, 2, 2, norms, tile_part(c), tiles_partials(c), 1, holo ? 0 : 1,
+                             norms + 2, s);
     } else {
         // z = x - gamma g, x_out = D(z): the CNN facet by facet (PnP step) or
         // uSARA's sub-iterative prox
@@ -183,7 +181,9 @@ void do_fb_step(ri_ctx *c, const T *x_in, const void *y, double gamma, int kind,
     fb_step_sorted<T>(c, x_in, ys, gamma, kind, param, x_out, norms, nullptr, 1.0, s);
 }
 
-// Main view at tile T (FP64 fractions when G is stored or the context is
+// Main view at tile T (folded in FP64; in FP32 the forward transform of the
+// whole plane and each visibility's own side of it are kept, so that Phi x and
+// ||Phi x - y||^2 come out of the same roundings on every path; FP64 fractions when G is stored or the context is
 // FP64), plus the CSR G in that view's order. The holographic matrix and the
 // SARA state are grid- and image-level and do not depend on the view's
 // visibility order, so they are kept.
@@ -199,7 +199,7 @@ void build_main_view(ri_ctx *c, int tile) {
         dev_free(c, c->sep.w);
         c->sep = Sep();
     }
-    build_view(c, c->view, tile, f64frac ? 8 : 4);
+    build_view(c, c->view, tile, f64frac ? 8 : 4, c->d.precision == 64);
     if (c->d.g_mode == RI_G_CSR) {
         if (c->d.precision == 32) fill_csr<float>(c, nullptr);
         else fill_csr<double>(c, nullptr);

@@ -48,13 +48,30 @@ struct View {
     int tile = 0;                 // T
     int n_items = 0;
     int64_t max_item_vis = 0;
-    int32_t *perm = nullptr;      // internal -> caller index
-    uint2 *rec = nullptr;         // per visibility: ((c_v << 16) | c_u, plane | h << 16 | stack << 20)
+    // A folded view uses that the image is real, so that Phi at (-u, -v, -w) is
+    // the conjugate of Phi at (u, v, w): a visibility whose window centre lies
+    // in the upper half of the u axis (c_u > N) is held mirrored, with its cell
+    // and fraction negated, its w-taps conjugated and reversed and its data
+    // conjugated, so that every window centre has c_u <= N and F Z x is needed
+    // on half the plane only. REC_MIRROR marks it.
+    bool folded = false;
+    int32_t *perm = nullptr;      // internal -> caller index | PERM_MIRROR when mirrored
+    uint2 *rec = nullptr;         // per visibility: ((c_v << 16) | c_u, plane | h << 16 | stack << 20 | REC_MIRROR)
     void *frac = nullptr;         // float[2] or double[2] per visibility (f_u, f_v)
     int frac_bytes = 0;           // 4 or 8
     TileItem *items = nullptr;
     std::vector<int64_t> perm_host;  // kept for tests (caller index of each internal slot)
 };
+
+constexpr uint32_t REC_MIRROR = 1u << 31;    // in rec.y
+constexpr int32_t PERM_INDEX = 0x7FFFFFFF;   // perm & PERM_INDEX: the caller's index; negative: mirrored
+
+// The caller's data value of permutation entry p (conjugated when mirrored).
+template <typename T> __device__ __forceinline__ cx<T> data_at(const cx<T> *y, int32_t p) {
+    cx<T> v = y[p & PERM_INDEX];
+    if (p < 0) v.y = -v.y;
+    return v;
+}
 
 // Stored G: row m (internal order) holds the S x S values of its window in
 // row-major window order; the columns follow from the row's window (centre
@@ -212,13 +229,43 @@ void dev_free(ri_ctx *c, void *p);
 
 // plan.cpp
 void build_plan(ri_ctx *c, const double *uvw);
-void build_view(ri_ctx *c, View &v, int tile, int frac_bytes);
+// fold: mirror the visibilities of the upper half plane (ignored with w-stacking).
+void build_view(ri_ctx *c, View &v, int tile, int frac_bytes, bool fold);
 void free_view(ri_ctx *c, View &v);
 template <typename T> void ensure_prec(ri_ctx *c, Prec<T> &p);
 
+// Memory that a gradient pass needs zeroed before its tile launch: the output
+// grid, the launch's work counter and the FP64 partial sums of ||r||^2.
+template <typename T> struct Clear {
+    cx<T> *grid = nullptr;
+    int64_t n = 0;               // grid cells (even)
+    int32_t *counter = nullptr;
+    double *part = nullptr;
+    int npart = 0;
+};
+
 // fft.hip
+// Full-plane transforms: the grids of every w-stack, or of the holographic
+// product (arbitrary complex grids, N' x N').
 template <typename T> void fwd_zpad_fft(ri_ctx *c, Prec<T> &p, const T *x, hipStream_t s);
 template <typename T> void adj_fft_crop(ri_ctx *c, Prec<T> &p, T *x, hipStream_t s);
+// Row pitch of a half-plane grid (columns kx = 0 .. N) of a real image.
+inline int half_pitch(int N) { return N >= 32 ? N + 16 : N + 8; }
+// What the tile launch of one pass needs zeroed: the output grid of p.gridA
+// (with_grid), the counter, the partial sums (part, or none).
+template <typename T> Clear<T> pass_clear(ri_ctx *c, Prec<T> &p, bool with_grid, int32_t *counter, double *part);
+template <typename T> void clear(const Clear<T> &z, hipStream_t s);
+// F Z x into p.gridB as the tile launch over a view reads it, and z cleared:
+// half the plane for a folded view; the whole plane with permuted rows
+// (see full_log_n1) without w-stacking; the plain planes of all w-stacks with it.
+template <typename T> void operator_fft(ri_ctx *c, Prec<T> &p, bool folded, const T *x, const Clear<T> &z,
+                                        hipStream_t s);
+// p.gridA (half the plane without w-stacking) -> Re{Z^dagger F^dagger Y} into x.
+template <typename T> void operator_adj_fft(ri_ctx *c, Prec<T> &p, T *x, hipStream_t s);
+// Grid row ky = k1 + N1 k2 of the whole plane without w-stacking is stored at
+// N2 k1 + k2 (N' = N1 N2), where the column transform's second pass leaves it
+// when it works in place.
+inline int full_log_n1(int logNp) { return (logNp + 1) / 2; }
 
 // gridding.hip
 enum { OP_DEGRID = 1, OP_GRID = 2, OP_FUSED = 3 };
@@ -226,7 +273,8 @@ enum { OP_DEGRID = 1, OP_GRID = 2, OP_FUSED = 3 };
 // RI_G_SEP; the stored forms must exist in T). OP_FUSED subtracts y_sorted (internal order)
 // or else y_user (caller's order, read through the view's permutation), or
 // nothing when both are NULL. counter: the launch's work counter (NULL: the
-// context's).
+// context's). The counter, the output grid and the partial sums must have been
+// cleared (pass_clear).
 template <typename T> void launch_tiles(ri_ctx *c, const View &v, Prec<T> &p, int op, int g_mode,
                                         const cx<T> *y_sorted, const cx<T> *y_user,
                                         cx<T> *y_out_user, double *r2_partials, hipStream_t s,
@@ -266,7 +314,6 @@ size_t noalloc_scratch_bytes(const ri_ctx *c); // workspace bytes the context's 
 // image.hip
 template <typename T> void fill_zero(cx<T> *p, int64_t n, hipStream_t s);
 template <typename T> void fill_real(T *p, int64_t n, T v, hipStream_t s);
-void fill_zero_i32(int32_t *p, int64_t n, hipStream_t s);
 void fill_zero_f64(double *p, int64_t n, hipStream_t s);
 template <typename T> void permute_to_internal(const cx<T> *y_user, cx<T> *y_int, const int32_t *perm,
                                                int64_t M, hipStream_t s);
@@ -274,6 +321,9 @@ template <typename T> void haar_prox(ri_ctx *c, const T *x_in, const T *g, T gam
                                      T thr, T *out, double *norm_partials, hipStream_t s);
 int image_partials(ri_ctx *c);
 void reduce_partials(const double *partials, int n, int stride, int count, double *out, hipStream_t s);
+// Two sets of partial sums in one launch: out_a[k] for k < count_a, out_b[k] for k < count_b.
+void reduce_partials2(const double *part_a, int n_a, int stride_a, int count_a, double *out_a, const double *part_b,
+                      int n_b, int stride_b, int count_b, double *out_b, hipStream_t s);
 template <typename T> void dot_partials(const T *a, const T *b, int64_t n, double *partials, hipStream_t s);
 template <typename T> void diff2_partials(const T *a, T alpha, const T *b, int64_t n, double *partials,
                                           hipStream_t s);
