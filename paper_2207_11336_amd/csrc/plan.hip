@@ -271,6 +271,22 @@ void build_plan(ri_ctx *c, const double *uvw) {
 // cut each (block, tile) run into work items and sort the items by decreasing
 // work so the persistent launch hands out the largest first.
 // ---------------------------------------------------------------------------
+//
+// Visibilities per item: a workgroup walks its item's visibilities one after
+// another, so with few visibilities the densest tiles' items set the launch's
+// time, while every item pays for staging and flushing its subgrid. Measured per
+// step (us) at 64 / 128 / 256 / 512 / 1024 / 2048 per item, one side of the line
+// against the other: M = 11,640 (128^2) 66 / 68 / 76 / 91 / 93 / 92;
+// 65,472 (256^2, FP64) 88 / 80 / 84 / 110 / 168 / 226; 100,003 (256^2) 122 / 107 /
+// 95 / 108 / 135 / 155; 300,001 (512^2) 212 / 193 / 184 / 171 / 204 / 204;
+// 1.2 M (1024^2, stored G, both ways) 1080 / 1029 / 1018 / 1001 / 995 / 1119;
+// 16.8 M (2048^2) 2.15 ms at 1024, 2.13 at 2048.
+static int64_t default_item_vis(int64_t M, int cu_count) {
+    if (M >= (int64_t)1 << 23) return 2048;
+    const int64_t v = (M / (2 * cu_count) + 15) / 16 * 16;
+    return std::min<int64_t>(1024, std::max<int64_t>(64, v));
+}
+
 void build_view(ri_ctx *c, View &v, int tile, int frac_bytes, bool fold) {
     const int64_t M = c->M;
     const int Np = c->Np, nta = Np / tile;
@@ -349,7 +365,7 @@ void build_view(ri_ctx *c, View &v, int tile, int frac_bytes, bool fold) {
     });
 
     // work items (one bucket = one block, one stack, one uv tile; chunks of VMAX)
-    const int64_t VMAX = c->d.item_vis > 0 ? c->d.item_vis : 2048;
+    const int64_t VMAX = c->d.item_vis > 0 ? c->d.item_vis : default_item_vis(M, c->dev.cu_count);
     std::vector<TileItem> items;
     std::vector<int64_t> work;
     for (const Bucket &bk : buckets) {
