@@ -17,9 +17,8 @@
 // neighbouring blocks (which share halo rows) meet in the same L2.
 // The same kernel computes the backward data pass with the weights flipped in
 // space and transposed in channels, and a ReLU-mask epilogue.
-// Weight gradients: MFMA with K = pixels; the output gradient and the input
-// activations are staged transposed in LDS (the activations in three copies
-// shifted by one column so every 16-byte read is aligned).
+// Weight gradients: MFMA with K = pixels; both operands are staged in LDS as they
+// lie in memory and transposed by the LDS read (ds_read_b64_tr_b16).
 // First and last layers (1 -> 64, 64 -> 1) are FP32 VALU kernels; the last is
 // fused with the residual subtraction.
 #include <algorithm>
@@ -40,8 +39,6 @@ constexpr int CH = 64;
 constexpr int PADC = 72;                 // LDS channel stride of a pixel (144 B)
 constexpr int WPK = 9 * 2 * 4 * 64;      // 16-byte chunks of one packed 64x64x3x3 layer
 constexpr int PATCH_CHUNKS = 18 * 18 * 8;   // 16-byte chunks of an 18 x 18 x 64 patch
-constexpr int DT_STRIDE = 256 + 8;       // LDS stride of one channel in the transposed gradient block
-constexpr int AT_STRIDE = 18 * 16 + 8;   // LDS stride of one channel in a shifted activation copy
 constexpr int N_XCD = 8;
 
 __device__ __forceinline__ uint16_t f2bf(float f) {
@@ -126,6 +123,14 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t item_rsrc(const uint16_t *base
 }
 // Byte offset of channel c of pixel p (p < 2^25) in an item.
 __device__ __forceinline__ unsigned px_off(int p, int c) { return (unsigned)p * (CH * 2u) + (unsigned)c * 2u; }
+
+// 16 bytes per lane from the buffer to LDS at base + 16 lane (base the same for the
+// whole wave); past-the-end offsets store zeros. lds_dma_wait before the barrier
+// that hands the data over.
+__device__ __forceinline__ void lds_dma16(__amdgpu_buffer_rsrc_t rs, unsigned char *base, unsigned off) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)base, 16, off, 0, 0, 0);
+}
+__device__ __forceinline__ void lds_dma_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 constexpr int CNW = 8;                                   // waves per workgroup (2 per SIMD)
 constexpr int CNT = 64 * CNW;                             // threads per workgroup
@@ -494,10 +499,22 @@ __global__ void k_l1(const float *__restrict__ D, const float *__restrict__ u, f
     if (threadIdx.x == 0) part[blockIdx.x] = s_red[0] + s_red[1] + s_red[2] + s_red[3];
 }
 
+// Sum over the four waves of part[wave * count + e], e < count, into out[e] (fixed order).
+__device__ __forceinline__ void sum_waves(const float *part, int count, float *__restrict__ out, int tid) {
+    for (int e = tid; e < count; e += 256)
+        out[e] = (part[e] + part[count + e]) + (part[2 * count + e] + part[3 * count + e]);
+}
+
 // Backward of the last layer. dpre[p][c] = [mask[p][c] > 0] sum_t bf16(W[0][c][t]) g[p - (t - centre)]
 // with mask = mask_act if given, else act;
 // this block's share of dW[c][t] = sum_p act[p + (t - centre)][c] g[p] and db = sum_p g[p] goes to
 // row `block` of part (577 floats), summed over blocks by k_reduce_rows.
+// dpre: thread t takes channels 8 (t % 8) .. +7 (their weights in registers) of one
+// pixel, 32 pixels a pass, so a wave stores eight whole pixels. dW: lane c of
+// wave w takes channel c over its patch rows, each activation read once for
+// all nine taps against a 3 x 3 window of g that slides along the row. Bound by
+// VALU and LDS: 30 us for 16 x 128^2 pixels (82 with one (c, t) pair per
+// thread, which re-read the patch for every tap).
 __global__ void __launch_bounds__(256) k_out_backward(const float *__restrict__ g, const uint16_t *__restrict__ act,
                                                       const float *__restrict__ wl_, uint16_t *__restrict__ dpre,
                                                       float *__restrict__ part, int H, int W,
@@ -505,157 +522,263 @@ __global__ void __launch_bounds__(256) k_out_backward(const float *__restrict__ 
     extern __shared__ uint4 smem4[];
     uint16_t *patch = reinterpret_cast<uint16_t *>(smem4);          // act patch [18*18][PADC]
     float *gp = reinterpret_cast<float *>(patch + 18 * 18 * PADC);  // g patch [18][18]
-    float *ws = gp + 18 * 18;                                       // [64][9]
-    float *red = ws + CH * 9;                                       // [4]
+    float *gz = gp + 18 * 18;                                       // g of the block, two zeros around it [20][20]
+    float *ws = gz + 20 * 20;                                       // [64][9]
+    float *red = reinterpret_cast<float *>(smem4);                  // at the end, over the patch: the waves' dW [4][577]
     const int b = blockIdx.z, y0 = blockIdx.y * 16, x0 = blockIdx.x * 16, tid = threadIdx.x;
     const size_t img = (size_t)b * H * W;
     float *prow = part + ((size_t)(blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * (CH * 9 + 1);
     load_patch_lds(patch, act, img, y0, x0, H, W, tid);
-    for (int e = tid; e < 18 * 18; e += 256) {
-        const int py = e / 18, px = e - py * 18, y = y0 - 1 + py, x = x0 - 1 + px;
-        gp[e] = (y >= 0 && y < H && x >= 0 && x < W) ? g[img + (size_t)y * W + x] : 0.f;
+    for (int e = tid; e < 20 * 20; e += 256) {
+        const int py = e / 20 - 1, px = e % 20 - 1, y = y0 - 1 + py, x = x0 - 1 + px;
+        const bool in = (unsigned)py < 18u && (unsigned)px < 18u && (unsigned)y < (unsigned)H && (unsigned)x < (unsigned)W;
+        const float v = in ? g[img + (size_t)y * W + x] : 0.f;
+        if ((unsigned)py < 18u && (unsigned)px < 18u) gp[py * 18 + px] = v;
+        gz[e] = (py >= 1 && py < 17 && px >= 1 && px < 17) ? v : 0.f;
     }
     for (int e = tid; e < CH * 9; e += 256) ws[e] = bfround(wl_[e]);
     __syncthreads();
-    const int ty = tid >> 4, tx = tid & 15;
-    float gg[9];
+    {
+        const int q = tid & 7;
+        float wr[8][9];
 #pragma unroll
-    for (int t = 0; t < 9; ++t) gg[t] = gp[(ty + 2 - t / 3) * 18 + tx + 2 - t % 3];
-    // the ReLU mask comes from mask_act (the activations at z) when the layer
-    // input act is a tangent, else from act itself
-    const uint16_t *ac = mask_act ? mask_act + (img + (size_t)(y0 + ty) * W + x0 + tx) * CH
-                                  : patch + ((ty + 1) * 18 + tx + 1) * PADC;
-    uint16_t *dst = dpre + (img + (size_t)(y0 + ty) * W + x0 + tx) * CH;
-    for (int c8 = 0; c8 < CH; c8 += 8) {
-        uint32_t o[8];
+        for (int e = 0; e < 8; ++e)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            float v = 0.f;
+            for (int t = 0; t < 9; ++t) wr[e][t] = ws[(8 * q + e) * 9 + t];
+#pragma unroll 2
+        for (int pass = 0; pass < 8; ++pass) {
+            const int p = pass * 32 + (tid >> 3), ty = p >> 4, tx = p & 15;
+            const size_t o = (img + (size_t)(y0 + ty) * W + x0 + tx) * CH + 8 * q;
+            float gg[9];
 #pragma unroll
-            for (int t = 0; t < 9; ++t) v += ws[(c8 + e) * 9 + t] * gg[t];
-            o[e] = (int16_t)ac[c8 + e] > 0 ? f2bf(v) : 0u;
+            for (int t = 0; t < 9; ++t) gg[t] = gp[(ty + 2 - t / 3) * 18 + tx + 2 - t % 3];
+            // the ReLU mask comes from mask_act (the activations at z) when the
+            // layer input act is a tangent, else from act itself
+            const uint4 mv = mask_act ? *reinterpret_cast<const uint4 *>(mask_act + o)
+                                      : *reinterpret_cast<const uint4 *>(patch + ((ty + 1) * 18 + tx + 1) * PADC + 8 * q);
+            const uint32_t mu[4] = {mv.x, mv.y, mv.z, mv.w};
+            uint32_t r[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                float v = 0.f;
+#pragma unroll
+                for (int t = 0; t < 9; ++t) v += wr[e][t] * gg[t];
+                r[e] = (int16_t)((e & 1) ? mu[e >> 1] >> 16 : mu[e >> 1] & 0xFFFFu) > 0 ? f2bf(v) : 0u;
+            }
+            *reinterpret_cast<uint4 *>(dpre + o) =
+                make_uint4(r[0] | (r[1] << 16), r[2] | (r[3] << 16), r[4] | (r[5] << 16), r[6] | (r[7] << 16));
         }
-        *reinterpret_cast<uint4 *>(dst + c8) =
-            make_uint4(o[0] | (o[1] << 16), o[2] | (o[3] << 16), o[4] | (o[5] << 16), o[6] | (o[7] << 16));
     }
-    for (int pr = tid; pr < CH * 9; pr += 256) {
-        const int c = pr / 9, t = pr - c * 9, dy = t / 3, dx = t % 3;
-        float s = 0.f;
-        for (int py = 0; py < 16; ++py)
-            for (int px = 0; px < 16; ++px)
-                s += bf2f(patch[((py + dy) * 18 + px + dx) * PADC + c]) * gp[(py + 1) * 18 + px + 1];
-        prow[pr] = s;
+    // dW[c][3 dy + dx] += act[py][px] g[py - dy][px - dx] over the patch pixels (g zero outside the block)
+    const int c = tid & 63, w = tid >> 6;
+    float acc[9] = {};
+    for (int py = w; py < 18; py += 4) {
+        float win[3][3] = {};   // win[dy][dx] = g[py - dy][px - dx]: gz row py + 2 - dy, column px + 2 - dx
+#pragma unroll
+        for (int px = 0; px < 18; ++px) {
+            const float a = bf2f(patch[(py * 18 + px) * PADC + c]);
+#pragma unroll
+            for (int dy = 0; dy < 3; ++dy) {
+                win[dy][2] = win[dy][1];
+                win[dy][1] = win[dy][0];
+                win[dy][0] = gz[(py + 2 - dy) * 20 + px + 2];
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx) acc[3 * dy + dx] = fmaf(a, win[dy][dx], acc[3 * dy + dx]);
+            }
+        }
     }
-    float sg = gp[(ty + 1) * 18 + tx + 1];
+    float sg = gp[((tid >> 4) + 1) * 18 + (tid & 15) + 1];
     for (int o = 32; o >= 1; o >>= 1) sg += __shfl_xor(sg, o);
-    if ((tid & 63) == 0) red[tid >> 6] = sg;
+    __syncthreads();   // the patch is free
+#pragma unroll
+    for (int t = 0; t < 9; ++t) red[w * (CH * 9 + 1) + c * 9 + t] = acc[t];
+    if (c == 0) red[w * (CH * 9 + 1) + CH * 9] = sg;
     __syncthreads();
-    if (tid == 0) prow[CH * 9] = red[0] + red[1] + red[2] + red[3];
+    sum_waves(red, CH * 9 + 1, prow, tid);
 }
 
 // Weight and bias gradients of a 64 -> 64 layer:
 //   dW[o][c][t] += sum_p dpre[p][o] act[p + (t - centre)][c],  db[o] += sum_p dpre[p][o].
-// A workgroup walks 16x16 pixel blocks and accumulates all 9 x 64 x 64
-// outputs in MFMA accumulators (wave w: output channels 16w..16w+15).
+// A workgroup is two teams of four waves; a team walks 32 x 8 pixel blocks and
+// accumulates all 9 x 64 x 64 outputs (wave w: input channels 16 w .. +15 against
+// all output channels). A K step is one row of 32 pixels: the four fragments
+// of dpre and the three shifted fragments of one new activation row are read
+// from LDS transposed, and the activation rows of the three vertical taps stay
+// in registers from one step to the next, so 36 products take 14 reads. LDS
+// holds the pixels as in memory (128 B each), their 32-byte quarters swizzled
+// by the column so that a read's 16 pixels spread over all banks. At the end the
+// teams' sums meet in LDS, one row of partials per workgroup.
+// Bound by MFMA and the staging latency: 31 us per layer at 16 x 128^2
+// (77 with operands transposed by 2-byte LDS stores, three shifted copies).
 constexpr int DW_PART = 9 * 4 * 4 * 256 + 64;    // per-workgroup partials: accumulators + bias sums
+constexpr int DWB_H = 8, DWB_W = 32;             // block of a team
+constexpr int DWP_W = DWB_W + 2, DWP_PIX = (DWB_H + 2) * DWP_W, DWD_PIX = DWB_H * DWB_W;
+constexpr int DWP_ROUNDS = (DWP_PIX * 8 + 255) / 256;            // 16-byte chunks of the patch per thread
+constexpr int DW_TEAM_BYTES = DWP_ROUNDS * 256 * 16 + DWD_PIX * CH * 2;
 
-__global__ void __launch_bounds__(256) k_dw64(const uint16_t *__restrict__ dpre, const uint16_t *__restrict__ act,
+typedef short short4v __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) short4v lds_short4;
+
+// Byte offset of channel c of the staged pixel in column x of a row of `width`
+// pixels. The swizzle depends on the column alone, so rows are constant offsets.
+__device__ __forceinline__ int dw_off(int row, int width, int x, int c) {
+    return (row * width + x) * (CH * 2) + (((c >> 4) ^ (x >> 1)) & 3) * 32 + (c & 15) * 2;
+}
+// MFMA fragment of 16 channels (rows or columns) and 32 pixels of a row (K; lane
+// group g holds pixels 4 g .. +3 and 16 + 4 g .. +3, the same order for both
+// operands): p points at the lane's first four channels and pixel.
+__device__ __forceinline__ bf16x8 dw_frag(const unsigned char *p) {
+    const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4 *)p);
+    const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4 *)(p + 16 * CH * 2));
+    const short v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return __builtin_bit_cast(bf16x8, v);
+}
+
+__global__ void __launch_bounds__(512) k_dw64(const uint16_t *__restrict__ dpre, const uint16_t *__restrict__ act,
                                               float *__restrict__ part, int H, int W, int nbx, int nby, int nblocks) {
     extern __shared__ uint4 smem4[];
-    uint16_t *dT = reinterpret_cast<uint16_t *>(smem4);   // [64][DT_STRIDE]   dpre transposed
-    uint16_t *aT = dT + CH * DT_STRIDE;                   // [3][64][AT_STRIDE] act transposed, shifted by dx
-    float *red = reinterpret_cast<float *>(aT + 3 * CH * AT_STRIDE);   // [256]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, j = lane & 15;
-    floatx4 acc[9][4];
+    const int tid = threadIdx.x & 255, team = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);   // scalars: uniform per wave
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    unsigned char *sa = reinterpret_cast<unsigned char *>(smem4) + team * DW_TEAM_BYTES;   // act patch
+    unsigned char *sd = sa + DWP_ROUNDS * 256 * 16;                                         // dpre block
+    floatx4 acc[9][4], bacc = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int t = 0; t < 9; ++t)
 #pragma unroll
-        for (int n = 0; n < 4; ++n) acc[t][n] = floatx4{0.f, 0.f, 0.f, 0.f};
-    float bsum = 0.f;
-    const BlockWalk walk(blockIdx.x, gridDim.x, nblocks);
-    for (int blk = walk.begin; blk < walk.end; blk += walk.step) {
-        int b, y0, x0;
-        block_origin(blk, nbx, nby, 16, b, y0, x0);
-        const size_t img = (size_t)b * H * W;
+        for (int o = 0; o < 4; ++o) acc[t][o] = floatx4{0.f, 0.f, 0.f, 0.f};
+    const int lx = 4 * (lane >> 4) + ((lane & 15) >> 2), lc = 4 * (lane & 3);   // the lane's pixel and channels of a fragment
+    const unsigned char *pa[3], *pd[4];
+#pragma unroll
+    for (int dx = 0; dx < 3; ++dx) pa[dx] = sa + dw_off(0, DWP_W, lx + dx, wave * 16 + lc);
+#pragma unroll
+    for (int o = 0; o < 4; ++o) pd[o] = sd + dw_off(0, DWB_W, lx, o * 16 + lc);
+    const uint32_t one2 = 0x3F803F80u;
+    const bf16x8 ones = as_bf16x8(make_uint4(one2, one2, one2, one2));
+    const BlockWalk walk(blockIdx.x, gridDim.x, nblocks / 2);   // h is a multiple of 16: blocks come in pairs
+    for (int pair = walk.begin; pair < walk.end; pair += walk.step) {
+        const int blk = 2 * pair + team;
         __syncthreads();
-        for (int e = tid; e < 256 * 8; e += 256) {
-            const int pix = e >> 3, ch = e & 7;
-            const uint4 v = reinterpret_cast<const uint4 *>(
-                dpre + (img + (size_t)(y0 + (pix >> 4)) * W + x0 + (pix & 15)) * CH)[ch];
-            const uint32_t u[4] = {v.x, v.y, v.z, v.w};
+        {
+            const int b = blk / (nbx * nby), rem = blk - b * nbx * nby, by = rem / nbx;
+            const int y0 = by * DWB_H, x0 = (rem - by * nbx) * DWB_W;
+            const size_t img = (size_t)b * H * W * CH;
+            int st = tid;   // opaque: the chunks' addresses are formed anew instead of being held (spilled) across blocks
+            asm volatile("" : "+v"(st));
+            // straight into LDS: chunk e of a region lands at byte 16 e, so the lane
+            // fetches the channels that the swizzle puts there
+            auto stage = [&](auto N, const uint16_t *src, unsigned char *dst, int width, int chunks, int yo, int xo) {
+                const __amdgpu_buffer_rsrc_t rs = item_rsrc(src + img, H, W);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                dT[(ch * 8 + 2 * q) * DT_STRIDE + pix] = (uint16_t)(u[q] & 0xFFFFu);
-                dT[(ch * 8 + 2 * q + 1) * DT_STRIDE + pix] = (uint16_t)(u[q] >> 16);
-            }
-        }
-        for (int e = tid; e < PATCH_CHUNKS; e += 256) {
-            const int pix = e >> 3, ch = e & 7, py = pix / 18, px = pix - py * 18;
-            const int y = y0 - 1 + py, x = x0 - 1 + px;
-            uint4 v = make_uint4(0u, 0u, 0u, 0u);
-            if (y >= 0 && y < H && x >= 0 && x < W)
-                v = reinterpret_cast<const uint4 *>(act + (img + (size_t)y * W + x) * CH)[ch];
-            const uint32_t u[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int dx = 0; dx < 3; ++dx) {
-                const int cc = px - dx;
-                if (cc < 0 || cc >= 16) continue;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    aT[(dx * CH + ch * 8 + 2 * q) * AT_STRIDE + py * 16 + cc] = (uint16_t)(u[q] & 0xFFFFu);
-                    aT[(dx * CH + ch * 8 + 2 * q + 1) * AT_STRIDE + py * 16 + cc] = (uint16_t)(u[q] >> 16);
+                for (int k = 0; k < decltype(N)::value; ++k) {
+                    const int e = st + k * 256, p = e >> 3, row = p / width, col = p - row * width;
+                    const int y = yo + row, x = xo + col, c = ((((e & 7) >> 1) ^ (col >> 1)) & 3) * 16 + (e & 1) * 8;
+                    const bool in = e < chunks && (unsigned)y < (unsigned)H && (unsigned)x < (unsigned)W;
+                    lds_dma16(rs, dst + (k * 256 + wave * 64) * 16, in ? px_off(y * W + x, c) : OOB);
                 }
-            }
+            };
+            stage(std::integral_constant<int, DWP_ROUNDS>{}, act, sa, DWP_W, DWP_PIX * 8, y0 - 1, x0 - 1);
+            stage(std::integral_constant<int, 8>{}, dpre, sd, DWB_W, DWD_PIX * 8, y0, x0);
+            lds_dma_wait();
         }
         __syncthreads();
         {
-            const int o = tid & 63, q0 = (tid >> 6) * 64;
-            for (int p = q0; p < q0 + 64; ++p) bsum += bf2f(dT[o * DT_STRIDE + p]);
-        }
-        for (int ks = 0; ks < 8; ++ks) {
-            const int pr = 2 * ks;
-            const bf16x8 a =
-                as_bf16x8(*reinterpret_cast<const uint4 *>(dT + (wave * 16 + j) * DT_STRIDE + pr * 16 + 8 * g));
-            const int row = pr + (g >> 1), col = 8 * (g & 1);
+            bf16x8 rows[3][3];   // activation rows r, r + 1, r + 2 of the patch at slot row % 3, shifts dx
 #pragma unroll
-            for (int t = 0; t < 9; ++t) {
-                const int dy = t / 3, dx = t - dy * 3;
+            for (int r = 0; r < 2; ++r)
 #pragma unroll
-                for (int n = 0; n < 4; ++n) {
-                    const bf16x8 bv = as_bf16x8(*reinterpret_cast<const uint4 *>(
-                        aT + (dx * CH + n * 16 + j) * AT_STRIDE + (row + dy) * 16 + col));
-                    acc[t][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bv, acc[t][n], 0, 0, 0);
-                }
+                for (int dx = 0; dx < 3; ++dx) rows[r][dx] = dw_frag(pa[dx] + r * DWP_W * CH * 2);
+#pragma unroll
+            for (int r = 0; r < DWB_H; ++r) {
+                bf16x8 a[4];
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx) rows[(r + 2) % 3][dx] = dw_frag(pa[dx] + (r + 2) * DWP_W * CH * 2);
+#pragma unroll
+                for (int o = 0; o < 4; ++o) a[o] = dw_frag(pd[o] + r * DWB_W * CH * 2);
+#pragma unroll
+                for (int t = 0; t < 9; ++t)
+#pragma unroll
+                    for (int o = 0; o < 4; ++o)
+                        acc[t][o] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[o], rows[(r + t / 3) % 3][t % 3],
+                                                                            acc[t][o], 0, 0, 0);
+                // bias: wave w sums output channels 16 w .. +15
+                const bf16x8 aw = wave == 0 ? a[0] : wave == 1 ? a[1] : wave == 2 ? a[2] : a[3];
+                bacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aw, ones, bacc, 0, 0, 0);
             }
         }
     }
-    // this workgroup's partial sums, in accumulator order (coalesced; reduced by k_dw64_reduce)
-    float *pp = part + (size_t)blockIdx.x * DW_PART;
-#pragma unroll
-    for (int t = 0; t < 9; ++t)
-#pragma unroll
-        for (int n = 0; n < 4; ++n)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) pp[((t * 4 + n) * 4 + r) * 256 + tid] = acc[t][n][r];
-    red[tid] = bsum;
+    // team 1's sums through LDS, added to team 0's; one row of partials in
+    // accumulator order (coalesced; reduced by k_dw64_reduce)
+    float *xs = reinterpret_cast<float *>(smem4);
     __syncthreads();
-    if (tid < CH) pp[9 * 4 * 4 * 256 + tid] = red[tid] + red[tid + 64] + red[tid + 128] + red[tid + 192];
+    if (team == 1) {
+#pragma unroll
+        for (int t = 0; t < 9; ++t)
+#pragma unroll
+            for (int o = 0; o < 4; ++o)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) xs[((t * 4 + o) * 4 + r) * 256 + tid] = acc[t][o][r];
+        if ((lane & 15) == 0)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) xs[9 * 4 * 4 * 256 + wave * 16 + 4 * (lane >> 4) + r] = bacc[r];
+    }
+    __syncthreads();
+    if (team == 0) {
+        float *pp = part + (size_t)blockIdx.x * DW_PART;
+#pragma unroll
+        for (int t = 0; t < 9; ++t)
+#pragma unroll
+            for (int o = 0; o < 4; ++o)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int e = ((t * 4 + o) * 4 + r) * 256 + tid;
+                    pp[e] = acc[t][o][r] + xs[e];
+                }
+        if ((lane & 15) == 0)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int e = 9 * 4 * 4 * 256 + wave * 16 + 4 * (lane >> 4) + r;
+                pp[e] = bacc[r] + xs[e];
+            }
+    }
 }
 
-// dW[o][c][t] and db[o] from the per-workgroup partials of k_dw64, in a fixed order.
-__global__ void k_dw64_reduce(const float *__restrict__ part, int nwg, float *__restrict__ dW, float *__restrict__ db) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= 9 * 4 * 4 * 256 + CH) return;
-    float s8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};      // eight independent loads in flight
-    int w = 0;
-    for (; w + 8 <= nwg; w += 8)
+// Sum over rows r < nrows of part[r * stride + e] for the workgroup's E consecutive
+// elements: 1024 / E threads per element take every (1024 / E)-th row with
+// eight loads in flight, then the threads' sums meet in LDS (fixed order).
+// Valid in the first E threads.
+template <int E>
+__device__ __forceinline__ float reduce_rows(const float *__restrict__ part, int nrows, int stride, int e, int count,
+                                             float (*red)[E]) {
+    constexpr int G = 1024 / E;
+    const int grp = threadIdx.x / E, le = threadIdx.x % E;
+    float s8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if (e < count) {
+        int r = grp;
+        for (; r + 7 * G < nrows; r += 8 * G)
 #pragma unroll
-        for (int k = 0; k < 8; ++k) s8[k] += part[(size_t)(w + k) * DW_PART + e];
-    for (; w < nwg; ++w) s8[0] += part[(size_t)w * DW_PART + e];
-    const float s = ((s8[0] + s8[1]) + (s8[2] + s8[3])) + ((s8[4] + s8[5]) + (s8[6] + s8[7]));
+            for (int k = 0; k < 8; ++k) s8[k] += part[(size_t)(r + k * G) * stride + e];
+        for (; r < nrows; r += G) s8[0] += part[(size_t)r * stride + e];
+    }
+    red[grp][le] = ((s8[0] + s8[1]) + (s8[2] + s8[3])) + ((s8[4] + s8[5]) + (s8[6] + s8[7]));
+    for (int h = G / 2; h >= 1; h >>= 1) {
+        __syncthreads();
+        if (grp < h) red[grp][le] += red[grp + h][le];
+    }
+    return red[0][le];
+}
+
+// dW[o][c][t] and db[o] from the per-workgroup partials of k_dw64: 9 us for 256 rows
+// (21 with one thread per element, which left most of the device idle).
+__global__ void __launch_bounds__(1024) k_dw64_reduce(const float *__restrict__ part, int nwg, float *__restrict__ dW,
+                                                      float *__restrict__ db) {
+    constexpr int E = 64;
+    __shared__ float red[1024 / E][E];
+    const int e = blockIdx.x * E + threadIdx.x % E;
+    const float s = reduce_rows<E>(part, nwg, DW_PART, e, DW_PART, red);
+    if (threadIdx.x >= E) return;
     if (e < 9 * 4 * 4 * 256) {
-        const int tid = e & 255, r = (e >> 8) & 3, n = (e >> 10) & 3, t = e >> 12;
-        const int wave = tid >> 6, lane = tid & 63, o = wave * 16 + 4 * (lane >> 4) + r, c = n * 16 + (lane & 15);
+        const int tid = e & 255, r = (e >> 8) & 3, o4 = (e >> 10) & 3, t = e >> 12;
+        const int wave = tid >> 6, lane = tid & 63, o = o4 * 16 + 4 * (lane >> 4) + r, c = wave * 16 + (lane & 15);
         dW[(o * CH + c) * 9 + t] = s;
     } else {
         db[e - 9 * 4 * 4 * 256] = s;
@@ -664,45 +787,66 @@ __global__ void k_dw64_reduce(const float *__restrict__ part, int nwg, float *__
 
 // Weight and bias gradients of the first layer, this block's share: dW0[c][t] = sum_p z[p + (t - centre)]
 // dpre[p][c] and db0[c] = sum_p dpre[p][c] into row `block` of part (640 floats, parameter order).
+// Lane c of wave w takes channel c over rows 4 w .. 4 w + 3, each gradient read
+// once for all taps against a 3 x 3 window of z that slides along the row: 14 us
+// for 16 x 128^2 pixels (39 with one (c, t) pair per thread).
 __global__ void __launch_bounds__(256) k_dw_in(const float *__restrict__ z, const uint16_t *__restrict__ dpre,
                                                float *__restrict__ part, int H, int W) {
     __shared__ float zp[18][18];
-    __shared__ uint16_t dp[256][CH + 2];
+    __shared__ uint4 dp4[256 * CH / 8];
+    __shared__ float red[4 * (CH * 9 + CH)];
     const int b = blockIdx.z, y0 = blockIdx.y * 16, x0 = blockIdx.x * 16, tid = threadIdx.x;
     const size_t img = (size_t)b * H * W;
     for (int e = tid; e < 18 * 18; e += 256) {
         const int py = e / 18, px = e - py * 18, y = y0 - 1 + py, x = x0 - 1 + px;
         zp[py][px] = (y >= 0 && y < H && x >= 0 && x < W) ? z[img + (size_t)y * W + x] : 0.f;
     }
-    for (int e = tid; e < 256 * CH; e += 256) {
-        const int pix = e >> 6, c = e & 63;
-        dp[pix][c] = dpre[(img + (size_t)(y0 + (pix >> 4)) * W + x0 + (pix & 15)) * CH + c];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const int e = tid + k * 256, pix = e >> 3;
+        dp4[e] = reinterpret_cast<const uint4 *>(dpre + (img + (size_t)(y0 + (pix >> 4)) * W + x0 + (pix & 15)) * CH)[e & 7];
     }
     __syncthreads();
-    for (int pr = tid; pr < CH * 9 + CH; pr += 256) {
-        float s = 0.f;
-        if (pr < CH * 9) {
-            const int c = pr / 9, t = pr - c * 9, dy = t / 3, dx = t % 3;
-            for (int p = 0; p < 256; ++p) s += zp[(p >> 4) + dy][(p & 15) + dx] * bf2f(dp[p][c]);
-        } else {
-            const int c = pr - CH * 9;
-            for (int p = 0; p < 256; ++p) s += bf2f(dp[p][c]);
+    const uint16_t *dp = reinterpret_cast<const uint16_t *>(dp4);
+    const int c = tid & 63, w = tid >> 6;
+    float acc[9] = {}, bs = 0.f;
+    for (int y = 4 * w; y < 4 * w + 4; ++y) {
+        float win[3][3];   // win[dy][dx] = z[y + dy - 1][x + dx - 1]
+#pragma unroll
+        for (int dy = 0; dy < 3; ++dy) {
+            win[dy][1] = zp[y + dy][0];
+            win[dy][2] = zp[y + dy][1];
         }
-        part[((size_t)(blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * (CH * 9 + CH) + pr] = s;
+#pragma unroll
+        for (int x = 0; x < 16; ++x) {
+            const float d = bf2f(dp[(y * 16 + x) * CH + c]);
+            bs += d;
+#pragma unroll
+            for (int dy = 0; dy < 3; ++dy) {
+                win[dy][0] = win[dy][1];
+                win[dy][1] = win[dy][2];
+                win[dy][2] = zp[y + dy][x + 2];
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx) acc[3 * dy + dx] = fmaf(d, win[dy][dx], acc[3 * dy + dx]);
+            }
+        }
     }
+#pragma unroll
+    for (int t = 0; t < 9; ++t) red[w * (CH * 9 + CH) + c * 9 + t] = acc[t];
+    red[w * (CH * 9 + CH) + CH * 9 + c] = bs;
+    __syncthreads();
+    sum_waves(red, CH * 9 + CH,
+              part + ((size_t)(blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * (CH * 9 + CH), tid);
 }
 
 // out[e] = sum over rows r < nrows of part[r * stride + e], e < count (fixed order).
-__global__ void k_reduce_rows(const float *__restrict__ part, int nrows, int stride, int count, float *__restrict__ out) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= count) return;
-    float s8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    int r = 0;
-    for (; r + 8 <= nrows; r += 8)
-#pragma unroll
-        for (int k = 0; k < 8; ++k) s8[k] += part[(size_t)(r + k) * stride + e];
-    for (; r < nrows; ++r) s8[0] += part[(size_t)r * stride + e];
-    out[e] = ((s8[0] + s8[1]) + (s8[2] + s8[3])) + ((s8[4] + s8[5]) + (s8[6] + s8[7]));
+__global__ void __launch_bounds__(1024) k_reduce_rows(const float *__restrict__ part, int nrows, int stride, int count,
+                                                      float *__restrict__ out) {
+    constexpr int E = 16;
+    __shared__ float red[1024 / E][E];
+    const int e = blockIdx.x * E + threadIdx.x % E;
+    const float s = reduce_rows<E>(part, nrows, stride, e, count, red);
+    if (threadIdx.x < E && e < count) out[e] = s;
 }
 
 // Adam (beta1 0.9, beta2 0.999, eps 1e-8) with the bias corrections
@@ -891,8 +1035,8 @@ void *cnn_alloc(ri_cnn *n, size_t bytes) {
 
 size_t conv64_lds() { return (size_t)CP_ROWS * CP_COLS * PADC * 2 + (size_t)WPK * 16 + CH * 4; }
 size_t convout_lds() { return (size_t)18 * 18 * PADC * 2 + 9 * CH * 4; }
-size_t outbwd_lds() { return (size_t)18 * 18 * PADC * 2 + 18 * 18 * 4 + CH * 9 * 4 + 16; }
-size_t dw64_lds() { return ((size_t)CH * DT_STRIDE + 3 * CH * AT_STRIDE) * 2 + 256 * 4; }
+size_t outbwd_lds() { return (size_t)18 * 18 * PADC * 2 + (18 * 18 + 20 * 20 + CH * 9) * 4; }
+size_t dw64_lds() { return std::max<size_t>(2 * DW_TEAM_BYTES, sizeof(float) * DW_PART); }
 
 void check_shape(const ri_cnn *n, int B, int h, int w) {
     if (B < 1 || h < 16 || w < 16 || h % 16 || w % 16 || h > n->maxH || w > n->maxW || B > n->maxB)
@@ -912,7 +1056,7 @@ int persistent_grid(const ri_cnn *n, int nblocks) {
 }
 
 // Forward through all layers. Training: hidden activations into act[0..L-2],
-// then the output layer reads act[L-2]. Inference: ping-pong act[0], act[1];
+// then the output layer reads act[L-2] (not run when D is NULL). Inference: ping-pong act[0], act[1];
 // the last hidden layer is not stored but projected onto the output layer's
 // nine taps inside its kernel, and a stencil pass forms D.
 void forward(ri_cnn *n, const float *z, float *D, int B, int h, int w, const CnnGeo &geo, hipStream_t s) {
@@ -934,7 +1078,9 @@ void forward(ri_cnn *n, const float *z, float *D, int B, int h, int w, const Cnn
                                (const uint16_t *)nullptr, geo, h, w, nbx, nby, nb,
                                reinterpret_cast<const uint4 *>(n->wproj), n->S, plane);
     }
-    if (n->training)
+    if (n->training && D == nullptr) {
+        // only the activations are wanted
+    } else if (n->training)
         hipLaunchKernelGGL(HIP_KERNEL_NAME(k_conv_out<false>), grid, dim3(256), convout_lds(), s, A(L - 2), z, D,
                            n->params + n->off[2 * (L - 1)], n->params + n->off[2 * (L - 1) + 1], h, w);
     else
@@ -943,7 +1089,7 @@ void forward(ri_cnn *n, const float *z, float *D, int B, int h, int w, const Cnn
     RI_CHECK_HIP(hipGetLastError());
 }
 
-// Parameter gradients of sum(g * f) into grads (zeroed here), where f is the
+// Parameter gradients of sum(g * f) into grads (every entry written), where f is the
 // network (ins = the activations of forward(), zin = z) or its linearisation
 // at z applied to a tangent (ins = the tangents of jvp_store(), zin = the
 // tangent v): the same passes, the layer inputs taken from ins while the ReLU
@@ -952,21 +1098,21 @@ void backward_core(ri_cnn *n, const float *zin, const float *g, const std::vecto
                    int B, int h, int w, hipStream_t s) {
     const int L = n->L;
     dim3 grid(w / 16, h / 16, B);
-    fill_real<float>(grads, n->P, 0.f, s);
     const int nblk16 = (w / 16) * (h / 16) * B;
     hipLaunchKernelGGL(k_out_backward, grid, dim3(256), outbwd_lds(), s, g, ins[L - 2],
-                       n->params + n->off[2 * (L - 1)], n->dpre[0], n->blkpart, h, w, n->act[L - 2]);
-    hipLaunchKernelGGL(k_reduce_rows, dim3((CH * 9 + 1 + 255) / 256), dim3(256), 0, s, n->blkpart, nblk16, CH * 9 + 1,
+                       n->params + n->off[2 * (L - 1)], n->dpre[0], n->blkpart, h, w,
+                       ins[L - 2] == n->act[L - 2] ? (const uint16_t *)nullptr : n->act[L - 2]);
+    hipLaunchKernelGGL(k_reduce_rows, dim3((CH * 9 + 1 + 15) / 16), dim3(1024), 0, s, n->blkpart, nblk16, CH * 9 + 1,
                        CH * 9 + 1, grads + n->off[2 * (L - 1)]);
     int cur = 0;
-    const int nbx = w / 16, nby = h / 16, nb = nbx * nby * B;                  // 16 x 16 blocks (weight gradients)
-    const int cby = (h + CB_ROWS - 1) / CB_ROWS, cnb = nbx * cby * B;         // 32 x 16 blocks (convolutions)
+    const int dbx = (w + DWB_W - 1) / DWB_W, dby = h / DWB_H, dnb = dbx * dby * B;   // blocks of the weight gradients
+    const int nwg = persistent_grid(n, dnb / 2);
+    const int nbx = w / 16, cby = (h + CB_ROWS - 1) / CB_ROWS, cnb = nbx * cby * B;  // 32 x 16 blocks (convolutions)
     const CnnGeo full;
     for (int l = L - 2; l >= 1; --l) {
-        const int nwg = persistent_grid(n, nb);
-        hipLaunchKernelGGL(k_dw64, dim3(nwg), dim3(256), dw64_lds(), s, n->dpre[cur], ins[l - 1], n->dwpart, h, w,
-                           nbx, nby, nb);
-        hipLaunchKernelGGL(k_dw64_reduce, dim3((9 * 4 * 4 * 256 + CH + 255) / 256), dim3(256), 0, s, n->dwpart, nwg,
+        hipLaunchKernelGGL(k_dw64, dim3(nwg), dim3(512), dw64_lds(), s, n->dpre[cur], ins[l - 1], n->dwpart, h, w,
+                           dbx, dby, dnb);
+        hipLaunchKernelGGL(k_dw64_reduce, dim3(DW_PART / 64), dim3(1024), 0, s, n->dwpart, nwg,
                            grads + n->off[2 * l], grads + n->off[2 * l + 1]);
         hipLaunchKernelGGL(HIP_KERNEL_NAME(k_conv64<1>), dim3(persistent_grid(n, cnb)), dim3(CNT), conv64_lds(), s,
                            n->dpre[cur], n->dpre[cur ^ 1],
@@ -976,7 +1122,7 @@ void backward_core(ri_cnn *n, const float *zin, const float *g, const std::vecto
         cur ^= 1;
     }
     hipLaunchKernelGGL(k_dw_in, grid, dim3(256), 0, s, zin, n->dpre[cur], n->blkpart, h, w);
-    hipLaunchKernelGGL(k_reduce_rows, dim3((CH * 9 + CH + 255) / 256), dim3(256), 0, s, n->blkpart, nblk16,
+    hipLaunchKernelGGL(k_reduce_rows, dim3((CH * 9 + CH + 15) / 16), dim3(1024), 0, s, n->blkpart, nblk16,
                        CH * 9 + CH, CH * 9 + CH, grads + n->off[0]);
     RI_CHECK_HIP(hipGetLastError());
 }
@@ -1284,7 +1430,7 @@ ri_status ri_cnn_grad(ri_cnn *n, const float *z, const float *g, int32_t B, int3
         if (!n->training) throw Error(RI_EINVAL, "network created without training buffers");
         hipStream_t s = reinterpret_cast<hipStream_t>(stream);
         check_shape(n, B, h, w);
-        forward(n, z, n->D, B, h, w, CnnGeo(), s);
+        forward(n, z, nullptr, B, h, w, CnnGeo(), s);
         backward(n, z, g, B, h, w, s);
         RI_CHECK_HIP(hipMemcpyAsync(grads, n->grads, sizeof(float) * n->P, hipMemcpyDeviceToDevice, s));
     });
@@ -1333,7 +1479,7 @@ ri_status ri_cnn_jvp(ri_cnn *n, const float *z, const float *v, float *out, int3
         if (!n->training) throw Error(RI_EINVAL, "network created without training buffers");
         hipStream_t s = reinterpret_cast<hipStream_t>(stream);
         check_shape(n, B, h, w);
-        forward(n, z, n->D, B, h, w, CnnGeo(), s);
+        forward(n, z, nullptr, B, h, w, CnnGeo(), s);
         jvp(n, v, out, B, h, w, s);
     });
 }
@@ -1345,7 +1491,7 @@ ri_status ri_cnn_vjp(ri_cnn *n, const float *z, const float *u, float *out, int3
         if (!n->training) throw Error(RI_EINVAL, "network created without training buffers");
         hipStream_t s = reinterpret_cast<hipStream_t>(stream);
         check_shape(n, B, h, w);
-        forward(n, z, n->D, B, h, w, CnnGeo(), s);
+        forward(n, z, nullptr, B, h, w, CnnGeo(), s);
         vjp(n, u, out, B, h, w, s);
     });
 }
@@ -1359,7 +1505,7 @@ ri_status ri_cnn_fne_norm(ri_cnn *n, const float *z, int32_t B, int32_t h, int32
         hipStream_t s = reinterpret_cast<hipStream_t>(stream);
         check_shape(n, B, h, w);
         const int64_t np = (int64_t)B * h * w;
-        forward(n, z, n->D, B, h, w, CnnGeo(), s);
+        forward(n, z, nullptr, B, h, w, CnnGeo(), s);
         float *v = n->zin, *t = n->D, *a = n->g;
         hipLaunchKernelGGL(k_normal, dim3(gridn(np)), dim3(256), 0, s, v, np, seed);
         dot_partials<float>(v, v, np, n->part, s);
@@ -1390,7 +1536,7 @@ ri_status ri_cnn_jvp_grad(ri_cnn *n, const float *z, const float *v, const float
         if (!n->training) throw Error(RI_EINVAL, "network created without training buffers");
         hipStream_t s = reinterpret_cast<hipStream_t>(stream);
         check_shape(n, B, h, w);
-        forward(n, z, n->D, B, h, w, CnnGeo(), s);
+        forward(n, z, nullptr, B, h, w, CnnGeo(), s);
         jvp_grad(n, v, u, n->D, B, h, w, s);
         RI_CHECK_HIP(hipMemcpyAsync(grads, n->grads2, sizeof(float) * n->P, hipMemcpyDeviceToDevice, s));
     });
