@@ -3,18 +3,18 @@
 //
 // Activations: bfloat16, NHWC with 64 channels (128 B per pixel).
 // 64 -> 64 layers: implicit GEMM on v_mfma_f32_16x16x32_bf16. A persistent
-// workgroup of four waves keeps the layer's packed weights in LDS and walks
-// 32 x 16 pixel blocks; for each block it stages the 34 x 18 input patch in
-// LDS (channel stride padded to 144 B) and every wave computes eight pixel
-// rows for all 64 output channels: output channels are the MFMA rows (A =
-// weights, pre-packed in lane order so each lane reads one 16-byte chunk),
-// pixels the MFMA columns (B = the patch), K = 9 taps x 64 input channels in
-// steps of 32; a patch row fragment serves the three row taps.
+// workgroup of eight waves keeps the layer's packed weights in registers (32
+// output channels per wave) and walks 32 x 16 pixel blocks; for each block the
+// 34 x 18 input patch goes straight to LDS, the next block's while the current one
+// is computed: output channels are the MFMA rows (A = weights, pre-packed in
+// lane order so each lane reads one 16-byte chunk), pixels the MFMA columns (B =
+// the patch), K = 9 taps x 64 input channels in steps of 32; a patch row
+// fragment serves the three row taps.
 // Lane l holds A[l%16][8(l/16)..+7], B[8(l/16)..+7][l%16] and receives
 // D[4(l/16)..+3][l%16], so the epilogue stores four consecutive channels of
-// one pixel. The next block's patch is loaded into registers while the
-// current one is computed. Blocks are dealt to XCDs in contiguous ranges so
-// neighbouring blocks (which share halo rows) meet in the same L2.
+// one pixel. Blocks are dealt to XCDs in contiguous ranges so neighbouring blocks
+// (which share halo rows) meet in the same L2; every other forward layer walks
+// its blocks backwards.
 // The same kernel computes the backward data pass with the weights flipped in
 // space and transposed in channels, and a ReLU-mask epilogue.
 // Weight gradients: MFMA with K = pixels; both operands are staged in LDS as they
@@ -61,9 +61,13 @@ __device__ __forceinline__ int4 valid_rect(const CnnGeo &g, int b, int h, int w)
 // Blocks of the persistent walk of workgroup `wg`: workgroups are dealt to the
 // 8 XCDs round-robin, so XCD x = wg % 8 takes the contiguous range
 // [x nb / 8, (x+1) nb / 8) and its nwg / 8 workgroups stride through it.
+// at(i): the block of index i, or, with rev, of nb - 1 - i (a layer that starts where
+// the previous one stopped finds that end of its input in the memory-side cache).
 struct BlockWalk {
-    int begin, end, step;
-    __device__ BlockWalk(int wg, int nwg, int nb) {
+    int begin, end, step, last = 0, sign = 1;
+    __device__ int at(int i) const { return last + sign * i; }
+    __device__ BlockWalk(int wg, int nwg, int nb, bool rev = false) {
+        if (rev) { last = nb - 1; sign = -1; }
         const int per = nwg / N_XCD;
         if (per == 0 || nwg % N_XCD) { begin = wg; end = nb; step = nwg; return; }
         const int x = wg % N_XCD;
@@ -124,11 +128,24 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t item_rsrc(const uint16_t *base
 // Byte offset of channel c of pixel p (p < 2^25) in an item.
 __device__ __forceinline__ unsigned px_off(int p, int c) { return (unsigned)p * (CH * 2u) + (unsigned)c * 2u; }
 
+// The same resource as four words for lds_dma16.
+__device__ __forceinline__ u32x4 item_rsrc4(const uint16_t *base, int H, int W) {
+    const uint64_t a = reinterpret_cast<uint64_t>(base);
+    return u32x4{(unsigned)__builtin_amdgcn_readfirstlane((int)a), (unsigned)__builtin_amdgcn_readfirstlane((int)(a >> 32)),
+                 (unsigned)H * (unsigned)W * (CH * 2u), 0x00020000u};
+}
 // 16 bytes per lane from the buffer to LDS at base + 16 lane (base the same for the
-// whole wave); past-the-end offsets store zeros. lds_dma_wait before the barrier
-// that hands the data over.
-__device__ __forceinline__ void lds_dma16(__amdgpu_buffer_rsrc_t rs, unsigned char *base, unsigned off) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)base, 16, off, 0, 0, 0);
+// whole wave); past-the-end offsets store zeros. In assembly because the
+// compiler makes every later LDS read wait for the builtin's transfer, also a
+// read of another buffer; here lds_dma_wait before the barrier that hands the
+// data over is the wait. (Counted waits of the compiler's own loads only
+// become stricter.)
+__device__ __forceinline__ void lds_dma16(u32x4 rs, unsigned char *base, unsigned off) {
+    const unsigned at = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)base;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                 :
+                 : "s"(__builtin_amdgcn_readfirstlane(at)), "v"(off), "s"(rs)
+                 : "memory", "m0");
 }
 __device__ __forceinline__ void lds_dma_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
@@ -170,23 +187,189 @@ __device__ __forceinline__ void sched_interleave() {
 // 64 -> 64 convolution, persistent. MODE 0: out = relu(conv + bias), zero
 // outside the batch item's valid rectangle. MODE 1 (backward data): out =
 // conv * [mask_act > 0] (mask_act: the post-ReLU activation the gradient
-// flows into). MODE 2: as MODE 0, but the activations are projected onto the
-// nine taps of the 64 -> 1 output layer instead of being stored.
+// flows into).
 // Eight waves (two per SIMD); blocks of 32 x 16 pixels (nbx x nby per item,
-// the last block row may reach past H); wave w computes block rows
-// 4w..4w+3 for all 64 output channels: 4 x 4 accumulator tiles (initialised
-// with the bias). The K loop runs as 18 steps (dx, kb, dy): the six patch
-// rows of a (dx, kb) pair are loaded once and serve the three row taps, and
-// each step's fragments are loaded while the previous step's MFMAs run. The
-// results go through LDS (the patch area, swizzled) so that every lane
-// stores 16 contiguous bytes and a wave writes whole pixel rows.
+// the last block row may reach past H). Wave w holds the weights of 32 output
+// channels (half w % 2) in registers for the whole launch and computes block
+// rows 8 (w / 2) .. +7, four at a time: 2 x 4 accumulator tiles (initialised with
+// the bias). The K loop runs over (dx, kb, dy): the six patch rows of a
+// (dx, kb) pair are loaded once and serve three row taps and two channel
+// tiles, so a product costs a quarter of an LDS read (weights in LDS took 0.375,
+// which kept LDS busy three quarters of the time). LDS holds two patches: the next
+// block's goes straight there while this one is computed, one barrier per block.
+// A patch pixel takes 128 bytes, its 16-byte chunks swizzled by the column so
+// that 16 neighbouring pixels spread over all banks.
+// Bound by the clock that the device holds under MFMA and HBM load (1.84 GHz at
+// 2048^2, MFMA busy half of the cycles, 1.1 GB per layer): 315 us per layer at
+// 2048^2 in both forms, 311 with alternating directions (about 265 us when all
+// activations are zero). Per network of ten layers, weights in LDS -> here:
+// 2.50 -> 2.44 ms at 2048^2, 688 -> 630 us at 1024^2, 223 -> 205 us at 512^2;
+// per training layer at 16 x 128^2 34 -> 27.5 us (MODE 1), 27 -> 25.5 (MODE 0).
 // ---------------------------------------------------------------------------
+constexpr int CV_PATCH = CP_ROWS * CP_COLS * CH * 2;      // bytes of a patch
+constexpr int CV_ROUNDS = (CP_CHUNKS + CNT - 1) / CNT;    // 16-byte chunks per thread
+size_t conv64_lds() { return 2 * (size_t)CV_PATCH; }
+
+// Byte offset of 16-byte chunk q of the patch pixel in column x.
+__device__ __forceinline__ int cv_off(int row, int x, int q) {
+    return (row * CP_COLS + x) * (CH * 2) + ((q ^ (x >> 1)) & 7) * 16;
+}
+
+__device__ __forceinline__ void conv_patch_dma(unsigned char *dst, const uint16_t *__restrict__ in, int blk, int nbx,
+                                               int nby, int H, int W, int tid, int wave) {
+    int b, y0, x0;
+    block_origin(blk, nbx, nby, CB_ROWS, b, y0, x0);
+    const u32x4 rs = item_rsrc4(in + (size_t)b * H * W * CH, H, W);
+    asm volatile("" : "+v"(tid));   // addresses are formed anew for each block, not held in registers
+#pragma unroll
+    for (int k = 0; k < CV_ROUNDS; ++k) {
+        const int e = tid + k * CNT, pix = e >> 3, row = pix / CP_COLS, col = pix - row * CP_COLS;
+        const int y = y0 - 1 + row, x = x0 - 1 + col, q = ((e & 7) ^ (col >> 1)) & 7;
+        const bool ok = (unsigned)y < (unsigned)H && (unsigned)x < (unsigned)W;
+        if ((k + 1) * CNT <= CP_CHUNKS || e < CP_CHUNKS)
+            lds_dma16(rs, dst + (k * CNT + wave * 64) * 16, ok ? px_off(y * W + x, q * 8) : OOB);
+    }
+}
+
 template <int MODE>
 __global__ void __launch_bounds__(CNT) k_conv64(const uint16_t *__restrict__ in, uint16_t *__restrict__ out,
                                                 const uint4 *__restrict__ wpk, const float *__restrict__ bias,
                                                 const uint16_t *__restrict__ mask_act, CnnGeo geo, int H, int W,
-                                                int nbx, int nby, int nblocks, const uint4 *__restrict__ wproj,
-                                                float *__restrict__ S, int64_t plane) {
+                                                int nbx, int nby, int nblocks, int rev) {
+    extern __shared__ uint4 smem4[];
+    unsigned char *lds = reinterpret_cast<unsigned char *>(smem4);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 4, j = lane & 15, hf = wave & 1, r0 = (wave >> 1) * 8;
+    const BlockWalk walk(blockIdx.x, gridDim.x, nblocks, rev != 0);
+    if (walk.begin >= walk.end) return;
+    conv_patch_dma(lds, in, walk.at(walk.begin), nbx, nby, H, W, tid, wave);
+    bf16x8 wa[18][2];   // [(2 dx + kb) * 3 + dy][channel tile 2 hf + m]
+#pragma unroll
+    for (int st = 0; st < 18; ++st)
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+            wa[st][m] = as_bf16x8(wpk[((((st % 3) * 3 + st / 6) * 2 + (st / 3) % 2) * 4 + 2 * hf + m) * 64 + lane]);
+    floatx4 bb[2];
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+        bb[m] = MODE != 1 ? *reinterpret_cast<const floatx4 *>(bias + (2 * hf + m) * 16 + 4 * g)
+                          : floatx4{0.f, 0.f, 0.f, 0.f};
+    int pb[3];          // the lane's patch offsets for the three column taps (kb = 0; kb = 1 flips bit 6)
+#pragma unroll
+    for (int dx = 0; dx < 3; ++dx) pb[dx] = cv_off(r0, j + dx, g);
+    int cur = 0;
+    lds_dma_wait();
+    for (int blk = walk.begin; blk < walk.end; blk += walk.step) {
+        __syncthreads();   // this block's patch is in LDS; nobody reads the other one any more
+        int b, y0, x0;
+        block_origin(walk.at(blk), nbx, nby, CB_ROWS, b, y0, x0);
+        const size_t img = (size_t)b * H * W * CH;
+        bool all_in = true, x_in = true;
+        int4 vr = make_int4(0, H, 0, W);
+        if (MODE != 1 && geo.N != 0) {
+            vr = valid_rect(geo, b, H, W);
+            x_in = x0 + j >= vr.z && x0 + j < vr.w;
+            all_in = y0 >= vr.x && y0 + CB_ROWS <= vr.y && x0 >= vr.z && x0 + 16 <= vr.w;
+        }
+        const __amdgpu_buffer_rsrc_t os = item_rsrc(out + img, H, W);
+        uint2 mv[4][2];
+        auto load_mask = [&](int y) {   // the post-ReLU activations of four rows from y
+            const __amdgpu_buffer_rsrc_t ms = item_rsrc(mask_act + img, H, W);
+#pragma unroll
+            for (int ni = 0; ni < 4; ++ni)
+#pragma unroll
+                for (int m = 0; m < 2; ++m) {
+                    const unsigned off = y + ni < H ? px_off((y + ni) * W + x0 + j, (2 * hf + m) * 16 + 4 * g) : OOB;
+                    mv[ni][m] = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(ms, off, 0, 0));
+                }
+        };
+        if (MODE == 1) load_mask(y0 + r0);   // ahead of the next patch, whose loads complete later
+        if (blk + walk.step < walk.end)
+            conv_patch_dma(lds + (cur ^ 1) * CV_PATCH, in, walk.at(blk + walk.step), nbx, nby, H, W, tid, wave);
+        const unsigned char *patch = lds + cur * CV_PATCH;
+#pragma unroll 1
+        for (int rp = 0; rp < 8; rp += 4) {
+            floatx4 acc[2][4];
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+#pragma unroll
+                for (int ni = 0; ni < 4; ++ni) acc[m][ni] = bb[m];
+            }
+            const unsigned char *pp = patch + rp * CP_COLS * CH * 2;
+            bf16x8 bc[6], bn[6];
+#pragma unroll
+            for (int r = 0; r < 6; ++r) bc[r] = as_bf16x8(*reinterpret_cast<const uint4 *>(pp + pb[0] + r * CP_COLS * CH * 2));
+#pragma unroll
+            for (int pr = 0; pr < 6; ++pr) {             // pr = 2 dx + kb
+                if (pr < 5) {
+#pragma unroll
+                    for (int r = 0; r < 6; ++r)
+                        bn[r] = as_bf16x8(*reinterpret_cast<const uint4 *>(
+                            pp + (pb[(pr + 1) / 2] ^ ((pr + 1) % 2 * 64)) + r * CP_COLS * CH * 2));
+                }
+#pragma unroll
+                for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+                    for (int m = 0; m < 2; ++m)
+#pragma unroll
+                        for (int ni = 0; ni < 4; ++ni)
+                            acc[m][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[pr * 3 + dy][m], bc[ni + dy],
+                                                                                 acc[m][ni], 0, 0, 0);
+                if (pr < 5) sched_interleave<6, 24>();
+#pragma unroll
+                for (int r = 0; r < 6; ++r) bc[r] = bn[r];
+            }
+            // 16-byte stores: lane rows g and g ^ 1 (lanes l and l ^ 16) exchange
+            // halves with v_permlane16_swap so that a lane holds eight
+            // consecutive channels: even rows keep channel tile 2 hf, odd rows
+            // take tile 2 hf + 1; the lane owns 16-byte chunk
+            // 2 (2 hf + (g & 1)) + (g >> 1).
+#pragma unroll
+            for (int ni = 0; ni < 4; ++ni) {
+                const int y = y0 + r0 + rp + ni;
+                const bool inside = all_in || (x_in && y >= vr.x && y < vr.y);
+                uint2 pk[2];
+#pragma unroll
+                for (int m = 0; m < 2; ++m) {
+                    float v[4];
+                    if (MODE != 1) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) v[r] = inside ? fmaxf(acc[m][ni][r], 0.f) : 0.f;
+                    } else {
+                        // the gradient flows where the post-ReLU activation is > 0
+                        const int16_t m4[4] = {(int16_t)(mv[ni][m].x & 0xFFFFu), (int16_t)(mv[ni][m].x >> 16),
+                                               (int16_t)(mv[ni][m].y & 0xFFFFu), (int16_t)(mv[ni][m].y >> 16)};
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) v[r] = m4[r] > 0 ? acc[m][ni][r] : 0.f;
+                    }
+                    const bf16x2 lo = {(__bf16)v[0], (__bf16)v[1]}, hi = {(__bf16)v[2], (__bf16)v[3]};
+                    pk[m] = make_uint2(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi));
+                }
+                const auto sx = __builtin_amdgcn_permlane16_swap(pk[0].x, pk[1].x, false, false);
+                const auto sy = __builtin_amdgcn_permlane16_swap(pk[0].y, pk[1].y, false, false);
+                const u32x4 v = {sx[0], sy[0], sx[1], sy[1]};
+                const int q = 2 * (2 * hf + (g & 1)) + (g >> 1);
+                __builtin_amdgcn_raw_buffer_store_b128(v, os, y < H ? px_off(y * W + x0 + j, q * 8) : OOB, 0, 0);
+            }
+            if (MODE == 1 && rp == 0) load_mask(y0 + r0 + 4);
+        }
+        // the next patch is in LDS once at most this block's eight stores (and
+        // mask loads) are outstanding: loads and stores complete in order
+        asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+        cur ^= 1;
+    }
+}
+
+// The last hidden layer: relu(conv + bias) as k_conv64<0>, projected onto the
+// nine taps of the 64 -> 1 output layer instead of being stored. Eight waves;
+// wave w computes block rows 4w..4w+3 for all 64 output channels from weights in
+// LDS: 4 x 4 accumulator tiles. Each step's fragments are loaded while the
+// previous step's MFMAs run. (The projection needs a pixel's 64 channels in
+// one wave, so this layer keeps the weights in LDS.)
+__global__ void __launch_bounds__(CNT) k_conv64_proj(const uint16_t *__restrict__ in, const uint4 *__restrict__ wpk,
+                                                     const float *__restrict__ bias, CnnGeo geo, int H, int W, int nbx,
+                                                     int nby, int nblocks, const uint4 *__restrict__ wproj,
+                                                     float *__restrict__ S, int64_t plane, int rev) {
     extern __shared__ uint4 smem4[];
     uint16_t *patch = reinterpret_cast<uint16_t *>(smem4);                 // [34*18][PADC]
     uint4 *wl = smem4 + (CP_ROWS * CP_COLS * PADC * 2) / 16;                // [WPK]
@@ -194,10 +377,10 @@ __global__ void __launch_bounds__(CNT) k_conv64(const uint16_t *__restrict__ in,
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int g = lane >> 4, j = lane & 15;
     for (int e = tid; e < WPK; e += CNT) wl[e] = wpk[e];
-    if (tid < CH) bs[tid] = MODE != 1 ? bias[tid] : 0.f;
-    const BlockWalk walk(blockIdx.x, gridDim.x, nblocks);
+    if (tid < CH) bs[tid] = bias[tid];
+    const BlockWalk walk(blockIdx.x, gridDim.x, nblocks, rev != 0);
     uint4 pre[CPRE8];
-    if (walk.begin < walk.end) conv_patch_fetch(pre, in, walk.begin, nbx, nby, H, W, tid);
+    if (walk.begin < walk.end) conv_patch_fetch(pre, in, walk.at(walk.begin), nbx, nby, H, W, tid);
     for (int blk = walk.begin; blk < walk.end; blk += walk.step) {
         __syncthreads();   // the previous block's patch and staging reads are done
 #pragma unroll
@@ -206,7 +389,7 @@ __global__ void __launch_bounds__(CNT) k_conv64(const uint16_t *__restrict__ in,
             if (e < CP_CHUNKS) *reinterpret_cast<uint4 *>(patch + (e >> 3) * PADC + (e & 7) * 8) = pre[k];
         }
         __syncthreads();
-        if (blk + walk.step < walk.end) conv_patch_fetch(pre, in, blk + walk.step, nbx, nby, H, W, tid);
+        if (blk + walk.step < walk.end) conv_patch_fetch(pre, in, walk.at(blk + walk.step), nbx, nby, H, W, tid);
         floatx4 acc[4][CRW];
 #pragma unroll
         for (int mi = 0; mi < 4; ++mi) {
@@ -253,17 +436,14 @@ __global__ void __launch_bounds__(CNT) k_conv64(const uint16_t *__restrict__ in,
             }
         }
         int b, y0, x0;
-        block_origin(blk, nbx, nby, CB_ROWS, b, y0, x0);
-        const size_t img = (size_t)b * H * W * CH;
+        block_origin(walk.at(blk), nbx, nby, CB_ROWS, b, y0, x0);
         bool all_in = true, x_in = true;
         int4 vr = make_int4(0, H, 0, W);
-        if (MODE != 1 && geo.N != 0) {
+        if (geo.N != 0) {
             vr = valid_rect(geo, b, H, W);
             x_in = x0 + j >= vr.z && x0 + j < vr.w;
             all_in = y0 >= vr.x && y0 + CB_ROWS <= vr.y && x0 >= vr.z && x0 + 16 <= vr.w;
         }
-        __amdgpu_buffer_rsrc_t ms;
-        if (MODE == 1) ms = item_rsrc(mask_act + img, H, W);
         // bf16 results: pk[ni][mi] = channels 16 mi + 4 g .. +3 of pixel (row ni, column j)
         uint2 pk[CRW][4];
 #pragma unroll
@@ -273,75 +453,42 @@ __global__ void __launch_bounds__(CNT) k_conv64(const uint16_t *__restrict__ in,
 #pragma unroll
             for (int mi = 0; mi < 4; ++mi) {
                 float v[4];
-                if (MODE != 1) {
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) v[r] = inside ? fmaxf(acc[mi][ni][r], 0.f) : 0.f;
-                } else {
-                    // the gradient flows where the post-ReLU activation is > 0
-                    const unsigned off = y < H ? px_off(y * W + x0 + j, mi * 16 + 4 * g) : OOB;
-                    const uint2 mv = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(ms, off, 0, 0));
-                    const int16_t m4[4] = {(int16_t)(mv.x & 0xFFFFu), (int16_t)(mv.x >> 16),
-                                           (int16_t)(mv.y & 0xFFFFu), (int16_t)(mv.y >> 16)};
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) v[r] = m4[r] > 0 ? acc[mi][ni][r] : 0.f;
-                }
+                for (int r = 0; r < 4; ++r) v[r] = inside ? fmaxf(acc[mi][ni][r], 0.f) : 0.f;
                 const bf16x2 lo = {(__bf16)v[0], (__bf16)v[1]}, hi = {(__bf16)v[2], (__bf16)v[3]};
                 pk[ni][mi] = make_uint2(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi));
             }
         }
-        if (MODE == 2) {
-            // last hidden layer: project the block's activations onto the nine
-            // taps of the 64 -> 1 output layer, s_t[p] = sum_c W[c][t] act[p][c]
-            // (MFMA rows t < 9 of a zero-padded 16-row A), instead of storing
-            // them. The activations go through LDS (the patch area, swizzled by
-            // pixel) to reach the MFMA operand layout.
-            __syncthreads();   // every wave is done with the patch
-            uint16_t *stg = patch + wave * (CRW * 16 * 64);                // [CRW rows][16 px][64 ch]
+        // last hidden layer: project the block's activations onto the nine
+        // taps of the 64 -> 1 output layer, s_t[p] = sum_c W[c][t] act[p][c]
+        // (MFMA rows t < 9 of a zero-padded 16-row A), instead of storing
+        // them. The activations go through LDS (the patch area, swizzled by
+        // pixel) to reach the MFMA operand layout.
+        __syncthreads();   // every wave is done with the patch
+        uint16_t *stg = patch + wave * (CRW * 16 * 64);                // [CRW rows][16 px][64 ch]
 #pragma unroll
-            for (int ni = 0; ni < CRW; ++ni)
+        for (int ni = 0; ni < CRW; ++ni)
 #pragma unroll
-                for (int mi = 0; mi < 4; ++mi) {
-                    const int q = (2 * mi + (g >> 1)) ^ (j & 7);
-                    *reinterpret_cast<uint2 *>(stg + (ni * 16 + j) * 64 + q * 8 + (g & 1) * 4) = pk[ni][mi];
-                }
-            __builtin_amdgcn_wave_barrier();   // the wave reads back what its other lanes staged
-            const bf16x8 ap0 = as_bf16x8(wproj[lane]), ap1 = as_bf16x8(wproj[64 + lane]);
-#pragma unroll
-            for (int ni = 0; ni < CRW; ++ni) {
-                const int y = y0 + wave * CRW + ni;
-                const uint16_t *sp = stg + (ni * 16 + j) * 64;
-                const bf16x8 b0 = as_bf16x8(*reinterpret_cast<const uint4 *>(sp + ((g ^ (j & 7)) * 8)));
-                const bf16x8 b1 = as_bf16x8(*reinterpret_cast<const uint4 *>(sp + (((4 + g) ^ (j & 7)) * 8)));
-                floatx4 pr = floatx4{0.f, 0.f, 0.f, 0.f};
-                pr = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap0, b0, pr, 0, 0, 0);
-                pr = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap1, b1, pr, 0, 0, 0);
-                if (y < H) {
-                    float *sq = S + (size_t)b * H * W + (size_t)y * W + x0 + j;
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        if (4 * g + r < 9) sq[(size_t)(4 * g + r) * plane] = pr[r];
-                }
+            for (int mi = 0; mi < 4; ++mi) {
+                const int q = (2 * mi + (g >> 1)) ^ (j & 7);
+                *reinterpret_cast<uint2 *>(stg + (ni * 16 + j) * 64 + q * 8 + (g & 1) * 4) = pk[ni][mi];
             }
-            continue;
-        }
-        // Direct 16-byte stores: lane rows g and g ^ 1 (lanes l and l ^ 16)
-        // exchange halves with v_permlane16_swap so that a lane holds eight
-        // consecutive channels. For the tile pair (mi, mi + 1): even rows keep
-        // tile mi (their 4 channels + the odd row's 4), odd rows take tile
-        // mi + 1; a lane then owns 16-byte chunk 2 (mi + (g & 1)) + (g >> 1).
-        const __amdgpu_buffer_rsrc_t os = item_rsrc(out + img, H, W);
+        __builtin_amdgcn_wave_barrier();   // the wave reads back what its other lanes staged
+        const bf16x8 ap0 = as_bf16x8(wproj[lane]), ap1 = as_bf16x8(wproj[64 + lane]);
 #pragma unroll
         for (int ni = 0; ni < CRW; ++ni) {
             const int y = y0 + wave * CRW + ni;
+            const uint16_t *sp = stg + (ni * 16 + j) * 64;
+            const bf16x8 b0 = as_bf16x8(*reinterpret_cast<const uint4 *>(sp + ((g ^ (j & 7)) * 8)));
+            const bf16x8 b1 = as_bf16x8(*reinterpret_cast<const uint4 *>(sp + (((4 + g) ^ (j & 7)) * 8)));
+            floatx4 pr = floatx4{0.f, 0.f, 0.f, 0.f};
+            pr = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap0, b0, pr, 0, 0, 0);
+            pr = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap1, b1, pr, 0, 0, 0);
+            if (y < H) {
+                float *sq = S + (size_t)b * H * W + (size_t)y * W + x0 + j;
 #pragma unroll
-            for (int mp = 0; mp < 4; mp += 2) {
-                uint2 a = pk[ni][mp], c = pk[ni][mp + 1];
-                const auto sx = __builtin_amdgcn_permlane16_swap(a.x, c.x, false, false);
-                const auto sy = __builtin_amdgcn_permlane16_swap(a.y, c.y, false, false);
-                const u32x4 v = {sx[0], sy[0], sx[1], sy[1]};
-                const int q = 2 * (mp + (g & 1)) + (g >> 1);
-                const unsigned off = y < H ? px_off(y * W + x0 + j, q * 8) : OOB;
-                __builtin_amdgcn_raw_buffer_store_b128(v, os, off, 0, 0);
+                for (int r = 0; r < 4; ++r)
+                    if (4 * g + r < 9) sq[(size_t)(4 * g + r) * plane] = pr[r];
             }
         }
     }
@@ -667,7 +814,7 @@ __global__ void __launch_bounds__(512) k_dw64(const uint16_t *__restrict__ dpre,
             // straight into LDS: chunk e of a region lands at byte 16 e, so the lane
             // fetches the channels that the swizzle puts there
             auto stage = [&](auto N, const uint16_t *src, unsigned char *dst, int width, int chunks, int yo, int xo) {
-                const __amdgpu_buffer_rsrc_t rs = item_rsrc(src + img, H, W);
+                const u32x4 rs = item_rsrc4(src + img, H, W);
 #pragma unroll
                 for (int k = 0; k < decltype(N)::value; ++k) {
                     const int e = st + k * 256, p = e >> 3, row = p / width, col = p - row * width;
@@ -1033,7 +1180,7 @@ void *cnn_alloc(ri_cnn *n, size_t bytes) {
     return p;
 }
 
-size_t conv64_lds() { return (size_t)CP_ROWS * CP_COLS * PADC * 2 + (size_t)WPK * 16 + CH * 4; }
+size_t conv64_proj_lds() { return (size_t)CP_ROWS * CP_COLS * PADC * 2 + (size_t)WPK * 16 + CH * 4; }
 size_t convout_lds() { return (size_t)18 * 18 * PADC * 2 + 9 * CH * 4; }
 size_t outbwd_lds() { return (size_t)18 * 18 * PADC * 2 + (18 * 18 + 20 * 20 + CH * 9) * 4; }
 size_t dw64_lds() { return std::max<size_t>(2 * DW_TEAM_BYTES, sizeof(float) * DW_PART); }
@@ -1071,12 +1218,11 @@ void forward(ri_cnn *n, const float *z, float *D, int B, int h, int w, const Cnn
         if (n->training || l < L - 2)
             hipLaunchKernelGGL(HIP_KERNEL_NAME(k_conv64<0>), dim3(persistent_grid(n, nb)), dim3(CNT), conv64_lds(), s,
                                A(l - 1), A(l), wl, n->params + n->off[2 * l + 1], (const uint16_t *)nullptr, geo, h,
-                               w, nbx, nby, nb, (const uint4 *)nullptr, (float *)nullptr, plane);
+                               w, nbx, nby, nb, l & 1);
         else
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_conv64<2>), dim3(persistent_grid(n, nb)), dim3(CNT), conv64_lds(), s,
-                               A(l - 1), (uint16_t *)nullptr, wl, n->params + n->off[2 * l + 1],
-                               (const uint16_t *)nullptr, geo, h, w, nbx, nby, nb,
-                               reinterpret_cast<const uint4 *>(n->wproj), n->S, plane);
+            hipLaunchKernelGGL(k_conv64_proj, dim3(persistent_grid(n, nb)), dim3(CNT), conv64_proj_lds(), s, A(l - 1),
+                               wl, n->params + n->off[2 * l + 1], geo, h, w, nbx, nby, nb,
+                               reinterpret_cast<const uint4 *>(n->wproj), n->S, plane, l & 1);
     }
     if (n->training && D == nullptr) {
         // only the activations are wanted
@@ -1117,8 +1263,7 @@ void backward_core(ri_cnn *n, const float *zin, const float *g, const std::vecto
         hipLaunchKernelGGL(HIP_KERNEL_NAME(k_conv64<1>), dim3(persistent_grid(n, cnb)), dim3(CNT), conv64_lds(), s,
                            n->dpre[cur], n->dpre[cur ^ 1],
                            reinterpret_cast<const uint4 *>(n->wbwd + (size_t)(l - 1) * WPK * 8),
-                           (const float *)nullptr, n->act[l - 1], full, h, w, nbx, cby, cnb, (const uint4 *)nullptr,
-                           (float *)nullptr, (int64_t)0);
+                           (const float *)nullptr, n->act[l - 1], full, h, w, nbx, cby, cnb, 0);
         cur ^= 1;
     }
     hipLaunchKernelGGL(k_dw_in, grid, dim3(256), 0, s, zin, n->dpre[cur], n->blkpart, h, w);
@@ -1148,8 +1293,7 @@ void jvp(ri_cnn *n, const float *v, float *out, int B, int h, int w, hipStream_t
         hipLaunchKernelGGL(HIP_KERNEL_NAME(k_conv64<1>), dim3(persistent_grid(n, cnb)), dim3(CNT), conv64_lds(), s,
                            n->dpre[cur], n->dpre[cur ^ 1],
                            reinterpret_cast<const uint4 *>(n->wfwd + (size_t)(l - 1) * WPK * 8),
-                           (const float *)nullptr, n->act[l], full, h, w, nbx, cby, cnb, (const uint4 *)nullptr,
-                           (float *)nullptr, (int64_t)0);
+                           (const float *)nullptr, n->act[l], full, h, w, nbx, cby, cnb, 0);
         cur ^= 1;
     }
     hipLaunchKernelGGL(HIP_KERNEL_NAME(k_conv_out<false>), grid, dim3(256), convout_lds(), s, n->dpre[cur],
@@ -1178,8 +1322,7 @@ void jvp_store(ri_cnn *n, const float *v, float *out, int B, int h, int w, hipSt
         hipLaunchKernelGGL(HIP_KERNEL_NAME(k_conv64<1>), dim3(persistent_grid(n, cnb)), dim3(CNT), conv64_lds(), s,
                            n->tan[l - 1], n->tan[l],
                            reinterpret_cast<const uint4 *>(n->wfwd + (size_t)(l - 1) * WPK * 8),
-                           (const float *)nullptr, n->act[l], full, h, w, nbx, cby, cnb, (const uint4 *)nullptr,
-                           (float *)nullptr, (int64_t)0);
+                           (const float *)nullptr, n->act[l], full, h, w, nbx, cby, cnb, 0);
     hipLaunchKernelGGL(HIP_KERNEL_NAME(k_conv_out<false>), grid, dim3(256), convout_lds(), s, n->tan[L - 2],
                        (const float *)nullptr, out, n->params + n->off[2 * (L - 1)], (const float *)nullptr, h, w);
     RI_CHECK_HIP(hipGetLastError());
@@ -1210,8 +1353,7 @@ void vjp(ri_cnn *n, const float *u, float *out, int B, int h, int w, hipStream_t
         hipLaunchKernelGGL(HIP_KERNEL_NAME(k_conv64<1>), dim3(persistent_grid(n, cnb)), dim3(CNT), conv64_lds(), s,
                            n->dpre[cur], n->dpre[cur ^ 1],
                            reinterpret_cast<const uint4 *>(n->wbwd + (size_t)(l - 1) * WPK * 8),
-                           (const float *)nullptr, n->act[l - 1], full, h, w, nbx, cby, cnb, (const uint4 *)nullptr,
-                           (float *)nullptr, (int64_t)0);
+                           (const float *)nullptr, n->act[l - 1], full, h, w, nbx, cby, cnb, 0);
         cur ^= 1;
     }
     hipLaunchKernelGGL(HIP_KERNEL_NAME(k_conv_out<true>), grid, dim3(256), convout_lds(), s, n->dpre[cur],
@@ -1255,7 +1397,7 @@ ri_cnn *create(const ri_cnn_desc &d, uint64_t seed) {
     RI_CHECK_HIP(hipGetDevice(&dev));
     hipDeviceProp_t prop;
     RI_CHECK_HIP(hipGetDeviceProperties(&prop, dev));
-    const size_t need = std::max(conv64_lds(), dw64_lds());
+    const size_t need = std::max(std::max(conv64_lds(), conv64_proj_lds()), dw64_lds());
     if (need > (size_t)prop.sharedMemPerBlock)
         throw Error(RI_EUNSUPPORTED, "CNN kernels need " + std::to_string(need) +
                                          " B of LDS per workgroup; the device allows " +
