@@ -14,16 +14,24 @@
 // by Durand-Kerner in long double, then mapped to z) and checked for
 // orthonormality before use. High-pass g[t] = (-1)^t h[L-1-t].
 //
-// Transform (per basis b = blockIdx.z, all 8 wavelet bases in one launch):
-// one level on an n x n block (row stride N): rows then columns, each
+// Transform (all 8 wavelet bases in one launch per level): one level on an n x n
+// block (row stride N) in both directions, each
 // a[k] = sum_t h[t] x[(2k+t) mod n], d[k] = sum_t g[t] x[(2k+t) mod n],
-// low half first; the top-left block goes on to the next level. The column
-// pass writes only the low-low block for the next level and finalises every
+// low half first; the top-left block goes on to the next level. The analysis
+// writes only the low-low block for the next level and finalises every
 // other coefficient in place: the dual update (clip), the new weight, or the
 // plain coefficient. Synthesis runs the adjoint from the coarsest level, reading
 // the coarse block from the previous level's result and the details from the
-// coefficients; its last row pass sums the 8 bases and the Dirac part and
+// coefficients; its last level sums the 8 bases and the Dirac part and
 // applies max(0, z - .) with the Dirac dual update fused.
+//
+// Bound: memory. A sub-iteration cannot do without reading and writing the nine
+// dual planes and reading the nine weights (470 MB in FP32 at 2048^2 with z and
+// x: 97 us at the rate of a copy). One pass per level and both directions in LDS
+// leave the low-low blocks as the only other traffic; with a pass per direction
+// and a plane in between for every basis a sub-iteration moved 1.45 GB in 16
+// launches and took 370 us, this form moves 0.75 GB in 8 and takes 193 us (finest
+// level 59 us analysis and 56 us synthesis, the three others 78 us).
 #include <cmath>
 #include <complex>
 #include <utility>
@@ -58,40 +66,40 @@ __device__ __forceinline__ void static_for_(F &&f, std::integer_sequence<int, I.
 template <int N, typename F>
 __device__ __forceinline__ void static_for(F &&f) { static_for_(f, std::make_integer_sequence<int, N>{}); }
 
-// 16 bytes of T as one LDS vector load.
+// 16 bytes of T as one LDS vector load; four elements of memory whose alignment is
+// that of one element (coefficients and images may be caller buffers).
 template <typename T>
 using vec16 = T __attribute__((ext_vector_type(16 / sizeof(T))));
+template <typename T>
+using vec4 = T __attribute__((ext_vector_type(4)));
+template <typename T>
+struct __attribute__((packed, aligned(sizeof(T)))) mem4 {
+    vec4<T> v;
+};
+template <typename T>
+__device__ __forceinline__ vec4<T> load4(const T *p) { return reinterpret_cast<const mem4<T> *>(p)->v; }
+template <typename T>
+__device__ __forceinline__ void store4(T *p, vec4<T> v) { reinterpret_cast<mem4<T> *>(p)->v = v; }
 
 enum { FIN_DUAL = 0, FIN_WEIGHT = 1, FIN_COEF = 2 };
-enum { SYN_PROX = 0, SYN_PLAIN = 1 };
+enum { SYN_PROX = 0, SYN_PLAIN = 1, SYN_LEVEL = 2 };
 
-// Finalised coefficient val (unscaled) of basis slot j (1..8, 0 = Dirac) at flat index e.
+// Finalised coefficient of basis slot j (0 = Dirac) from its transform val
+// (unscaled), its dual variable v and weight w.
 template <typename T, int FIN>
-__device__ __forceinline__ void finalise(T *dst9, const T *w9, size_t i9, T val, T scale, T par) {
+__device__ __forceinline__ T final_value(T v, T w, T val, T scale, T par) {
     const T cval = val * scale;
     if (FIN == FIN_DUAL) {
-        const T lim = par * w9[i9];
-        dst9[i9] = fmin(fmax(dst9[i9] + cval, -lim), lim);
-    } else if (FIN == FIN_WEIGHT) {
-        dst9[i9] = par / (par + fabs(cval));
-    } else {
-        dst9[i9] = cval;
+        const T lim = par * w;
+        return fmin(fmax(v + cval, -lim), lim);
     }
+    return FIN == FIN_WEIGHT ? par / (par + fabs(cval)) : cval;
 }
-
-// Column passes are register-blocked: a thread computes KB consecutive outputs
-// of one column from one window of inputs held in registers (2 KB + L - 2
-// inputs for analysis, KB + L/2 - 1 of each half for synthesis); KB is 8 on
-// the finest level and smaller on the coarse ones, whose few columns would
-// otherwise leave most of the device idle (col_block below). Row passes
-// stage the row in LDS by coalesced loads; the analysis computes one output
-// per lane per step, the synthesis 8 consecutive outputs per lane from
-// 16-byte LDS windows (k_syn_rows, k_syn_final). The
-// filter length L is a template parameter (one instantiation per basis, chosen
-// from blockIdx.z).
-// Column block of level side n: 8 outputs per thread at the finest levels, 4
-// at n = 1024, 2 below (more workgroups for the small coarse levels).
-inline int col_block(int n) { return n >= 2048 ? 8 : (n >= 1024 ? 4 : 2); }
+template <typename T, int FIN>
+__device__ __forceinline__ void finalise(T *dst9, const T *w9, size_t i9, T val, T scale, T par) {
+    if (FIN == FIN_DUAL) dst9[i9] = final_value<T, FIN>(dst9[i9], w9[i9], val, scale, par);
+    else dst9[i9] = final_value<T, FIN>((T)0, (T)0, val, scale, par);
+}
 
 // f(std::integral_constant<int, L>) for the filter length L = 2 (b + 1) of basis b.
 template <typename F>
@@ -108,143 +116,142 @@ __device__ __forceinline__ void with_length(int b, F &&f) {
     }
 }
 
-// Row analysis of the n x n block of every basis: in (basis stride in_bs) -> tmp.
-// Workgroup: one row of one basis, staged in LDS by coalesced loads; lane
-// outputs k = tid, tid + 256, ... of both halves.
-template <typename T>
-__global__ void __launch_bounds__(256) k_ana_rows(const T *__restrict__ in, int64_t in_bs, T *__restrict__ tmp,
-                                                  int N, int n) {
-    extern __shared__ unsigned char smem_raw[];
-    T *row_s = reinterpret_cast<T *>(smem_raw);
-    const int b = blockIdx.z, row = blockIdx.y, half = n >> 1, m = n - 1;
-    const T *src = in + b * in_bs + (size_t)row * N;
-    for (int e = threadIdx.x; e < n; e += blockDim.x) row_s[e] = src[e];
-    __syncthreads();
-    T *dst = tmp + (size_t)b * N * N + (size_t)row * N;
-    with_length(b, [&](auto Lc) {
-        constexpr int L = decltype(Lc)::value;
-        for (int k = threadIdx.x; k < half; k += blockDim.x) {
-            T a = 0, d = 0;
-#pragma unroll
-            for (int t = 0; t < L; ++t) {
-                const T v = row_s[(2 * k + t) & m];
-                a += fh<T>(b, t) * v;
-                d += fg<T>(b, t) * v;
-            }
-            dst[k] = a;
-            dst[half + k] = d;
-        }
-    });
-}
+// One level in one pass: a workgroup transforms a tile in both directions and
+// only coefficients and the low-low block touch memory. A tile has 64 low columns
+// (128 columns of the level's block; a quadrant's rows are runs of 256 bytes in
+// FP32) and 8 S low rows (16 S rows). The longest filter needs 14 rows and
+// columns beyond the tile: with S = 4 1.2 times the work in each direction, about a third of
+// the time the memory takes. The analysis runs columns first, so that the
+// input goes straight from memory to registers, the synthesis rows first, so that
+// the coefficients do.
+constexpr int TC = 64;             // low columns of a tile
+constexpr int KB = 8;              // low rows of a column strip: one thread's register window
+constexpr int APITCH = 2 * TC + 16;
 
-// Register-blocked row analysis (n a multiple of 8). The row is staged in LDS
-// with a periodic tail, s[e] = row[e mod n] for e < n + AH; a lane computes the
-// four output pairs k = 4 j .. 4 j + 3 from the window s[8 j .. 8 j + 24)
-// (outputs need s[2 k + t], t < L <= 16) read as 16-byte vectors, and stores
-// each half as one 4-element vector. ALLB: the eight bases share the input
-// row (the finest level) and one workgroup computes all of them; otherwise
-// one workgroup per row and basis (blockIdx.z).
-constexpr int AH = 16;
-constexpr int AWIN = 24;
-
-template <typename T>
-using vec4o = T __attribute__((ext_vector_type(4)));
-
-template <typename T, int L>
-__device__ __forceinline__ void ana_row_block(int b, const T *s, T (&a)[4], T (&d)[4]) {
-    constexpr int E = 16 / sizeof(T);
-    T w[AWIN];
+// E consecutive elements from 16-byte-aligned LDS.
+template <typename T, int E>
+__device__ __forceinline__ void lds_window(const T *p, T (&w)[E]) {
+    constexpr int V = 16 / sizeof(T);
 #pragma unroll
-    for (int i = 0; i < AWIN / E; ++i) {
-        const vec16<T> v = reinterpret_cast<const vec16<T> *>(s)[i];
+    for (int i = 0; i < E / V; ++i) {
+        const vec16<T> v = reinterpret_cast<const vec16<T> *>(p)[i];
 #pragma unroll
-        for (int e = 0; e < E; ++e) w[i * E + e] = v[e];
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        T aa = 0, dd = 0;
-#pragma unroll
-        for (int t = 0; t < L; ++t) {
-            aa = fma(fh<T>(b, t), w[2 * u + t], aa);
-            dd = fma(fg<T>(b, t), w[2 * u + t], dd);
-        }
-        a[u] = aa;
-        d[u] = dd;
+        for (int e = 0; e < V; ++e) w[i * V + e] = v[e];
     }
 }
 
-template <typename T>
-__device__ __forceinline__ void store4(T *p, const T (&v)[4]) {
-    vec4o<T> o;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) o[e] = v[e];
-    *reinterpret_cast<vec4o<T> *>(p) = o;
-}
-
-template <typename T, int ALLB>
-__global__ void __launch_bounds__(256) k_ana_rows_rb(const T *__restrict__ in, int64_t in_bs, T *__restrict__ tmp,
-                                                     int N, int n) {
-    extern __shared__ unsigned char smem_raw[];
-    T *s = reinterpret_cast<T *>(smem_raw);
-    const int row = blockIdx.y, half = n >> 1, m = n - 1, tid = threadIdx.x;
-    const int b0 = ALLB ? 0 : (int)blockIdx.z;
-    const T *src = in + b0 * in_bs + (size_t)row * N;
-    for (int e = tid; e < n + AH; e += blockDim.x) s[e] = src[e & m];
-    __syncthreads();
+// Analysis of one level block (n x n, row stride N; basis stride in_bs, 0 for the
+// image): low-low block into out (unless last) and every other coefficient
+// finalised into dst9 (slot b + 1).
+//   Column pass: thread = one column and one strip of KB low rows, whose
+// 2 KB + L - 2 inputs stay in registers (for all bases with ALLB: the finest
+// level's bases share their input); both halves' KB outputs go to LDS. 128 S
+// threads have the tile's columns, a last wave the 16 columns beyond it.
+//   Row pass: thread = four low columns of one row of each half, from 24-element
+// windows in LDS (outputs need columns 2 k + t, t < L <= 16); its 16 results are
+// finalised as 4-element vectors, whose dual variables and weights were
+// asked for before the column pass. SMALL: blocks of n < 8, element by element.
+template <typename T, int FIN, int S, bool ALLB, bool SMALL>
+__global__ void __launch_bounds__(128 * S + 64)
+k_ana(const T *__restrict__ in, int64_t in_bs, T *__restrict__ out, T *dst9, const T *__restrict__ w9, int N, int n,
+      int last, T scale, T par) {
+    __shared__ __attribute__((aligned(16))) T mid[2 * KB * S * APITCH];
+    const int tid = threadIdx.x, half = n >> 1, m = n - 1;
+    const bool main = tid < 128 * S;
+    const int strip = main ? tid >> 7 : (tid - 128 * S) >> 4;
+    const int lc = main ? tid & 127 : 128 + ((tid - 128 * S) & 15);
+    const int k0 = (blockIdx.y * S + strip) * KB, gcol = (blockIdx.x * 2 * TC + lc) & m;
+    const bool cact = strip < S && k0 < half;
+    const int kr = tid >> 4, j = tid & 15;
+    const int k = blockIdx.y * KB * S + kr, kc = blockIdx.x * TC + 4 * j;
+    const bool ract = main && k < half && kc < half;
     const size_t NN = (size_t)N * N;
+    T r[2 * KB + LMAX - 2];
+    auto load = [&](const T *src, auto NRc) {
+#pragma unroll
+        for (int q = 0; q < decltype(NRc)::value; ++q) r[q] = src[(size_t)((2 * k0 + q) & m) * N + gcol];
+    };
     auto basis = [&](int b, auto Lc) {
         constexpr int L = decltype(Lc)::value;
-        T *dst = tmp + (size_t)b * NN + (size_t)row * N;
-        for (int j = tid; 4 * j < half; j += blockDim.x) {
-            T a[4], d[4];
-            ana_row_block<T, L>(b, s + 8 * j, a, d);
-            store4<T>(dst + 4 * j, a);
-            store4<T>(dst + half + 4 * j, d);
+        const size_t e0 = (size_t)k * N + kc, dh = (size_t)half * N;
+        T *d9 = dst9 + (size_t)(b + 1) * NN;
+        const T *l9 = w9 + (size_t)(b + 1) * NN;
+        vec4<T> v[4], w[4];
+        if (!ALLB && cact) load(in + b * in_bs, std::integral_constant<int, 2 * KB + L - 2>{});
+        if (FIN == FIN_DUAL && !SMALL && ract) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (q == 0 && !last) continue;
+                const size_t p = e0 + (q & 2 ? dh : 0) + (q & 1 ? half : 0);
+                v[q] = load4<T>(d9 + p);
+                w[q] = load4<T>(l9 + p);
+            }
+        }
+        if (cact) {
+            T *lo = mid + strip * KB * APITCH + lc, *hi = lo + KB * S * APITCH;
+#pragma unroll
+            for (int kk = 0; kk < KB; ++kk) {
+                T a = 0, d = 0;
+#pragma unroll
+                for (int t = 0; t < L; ++t) {
+                    a = fma(fh<T>(b, t), r[2 * kk + t], a);
+                    d = fma(fg<T>(b, t), r[2 * kk + t], d);
+                }
+                lo[kk * APITCH] = a;
+                hi[kk * APITCH] = d;
+            }
+        }
+        __syncthreads();
+        if (ract) {
+#pragma unroll
+            for (int vh = 0; vh < 2; ++vh) {
+                T x[24];
+                lds_window<T, 24>(mid + (vh * KB * S + kr) * APITCH + 8 * j, x);
+                vec4<T> c[2];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    T a = 0, d = 0;
+#pragma unroll
+                    for (int t = 0; t < L; ++t) {
+                        a = fma(fh<T>(b, t), x[2 * u + t], a);
+                        d = fma(fg<T>(b, t), x[2 * u + t], d);
+                    }
+                    c[0][u] = a;
+                    c[1][u] = d;
+                }
+#pragma unroll
+                for (int hh = 0; hh < 2; ++hh) {
+                    const size_t p = e0 + (vh ? dh : 0) + (hh ? half : 0);
+                    const bool low = vh == 0 && hh == 0 && !last;
+                    if (SMALL) {
+                        for (int u = 0; u < 4; ++u)
+                            if (kc + u < half) {
+                                if (low) out[b * NN + e0 + u] = c[hh][u];
+                                else finalise<T, FIN>(d9, l9, p + u, c[hh][u], scale, par);
+                            }
+                    } else if (low) {
+                        store4<T>(out + b * NN + e0, c[hh]);
+                    } else {
+                        vec4<T> o;
+#pragma unroll
+                        for (int u = 0; u < 4; ++u)
+                            o[u] = final_value<T, FIN>(v[2 * vh + hh][u], w[2 * vh + hh][u], c[hh][u], scale, par);
+                        store4<T>(d9 + p, o);
+                    }
+                }
+            }
         }
     };
     if (ALLB) {
+        if (cact) load(in, std::integral_constant<int, 2 * KB + LMAX - 2>{});
         static_for<NW>([&](auto bc) {
             constexpr int b = decltype(bc)::value;
+            if (b > 0) __syncthreads();       // the previous basis' windows are read
             basis(b, std::integral_constant<int, 2 * (b + 1)>{});
         });
     } else {
-        with_length(b0, [&](auto Lc) { basis(b0, Lc); });
+        with_length(blockIdx.z, [&](auto Lc) { basis(blockIdx.z, Lc); });
     }
-}
-
-// Column analysis: tmp -> low-low block into work (unless last) and every
-// other coefficient finalised into dst9 (slot b + 1). Thread: column col,
-// outputs k0 .. k0 + KB - 1 of both halves.
-template <typename T, int FIN, int KB>
-__global__ void __launch_bounds__(256) k_ana_cols(const T *__restrict__ tmp, T *__restrict__ work, T *dst9,
-                                                  const T *__restrict__ w9, int N, int n, int last, T scale, T par) {
-    const int b = blockIdx.z;
-    const int col = blockIdx.x * 64 + (threadIdx.x & 63);
-    const int k0 = (blockIdx.y * 4 + (threadIdx.x >> 6)) * KB, half = n >> 1, m = n - 1;
-    if (col >= n || k0 >= half) return;
-    const size_t NN = (size_t)N * N;
-    const T *src = tmp + b * NN + col;
-    const size_t base9 = (size_t)(b + 1) * NN;
-    with_length(b, [&](auto Lc) {
-        constexpr int L = decltype(Lc)::value, NR = 2 * KB + L - 2;
-        T r[NR];
-#pragma unroll
-        for (int j = 0; j < NR; ++j) r[j] = src[(size_t)((2 * k0 + j) & m) * N];
-#pragma unroll
-        for (int kk = 0; kk < KB; ++kk) {
-            const int k = k0 + kk;
-            if (k >= half) break;
-            T a = 0, d = 0;
-#pragma unroll
-            for (int t = 0; t < L; ++t) {
-                a += fh<T>(b, t) * r[2 * kk + t];
-                d += fg<T>(b, t) * r[2 * kk + t];
-            }
-            if (!last && col < half) work[b * NN + (size_t)k * N + col] = a;
-            else finalise<T, FIN>(dst9, w9, base9 + (size_t)k * N + col, a, scale, par);
-            finalise<T, FIN>(dst9, w9, base9 + (size_t)(half + k) * N + col, d, scale, par);
-        }
-    });
 }
 
 // Dirac slot of the analysis (weights or plain coefficients).
@@ -254,234 +261,152 @@ __global__ void k_ana_dirac(const T *__restrict__ x, T *dst9, int64_t n, T scale
         finalise<T, FIN>(dst9, nullptr, (size_t)i, x[i], scale, par);
 }
 
-// Synthesis of 2 KB consecutive outputs i0 .. i0 + 2 KB - 1 (i0 even) along one
-// axis from the low half A and the high half D (element k at A[k * stride]):
-// x[i] = sum_{t = i mod 2} h[t] A[k] + g[t] D[k], k = (i - t)/2 mod half.
-template <typename T, int L, int KB>
-__device__ __forceinline__ void syn_block(int b, const T *A, const T *D, size_t stride, int i0, int half, T *x) {
-    constexpr int S2 = L / 2, NA = KB + S2 - 1;
-    const int kb0 = (i0 >> 1) - S2 + 1, hm = half - 1;
-    T ar[NA], dr[NA];
-#pragma unroll
-    for (int j = 0; j < NA; ++j) {
-        const size_t k = (size_t)((kb0 + j) & hm);
-        ar[j] = A[k * stride];
-        dr[j] = D[k * stride];
+// Synthesis of one level block (n x n): the coarse block (rows and columns < n/2)
+// from low (or from the coefficients at the coarsest level), the rest from
+// the coefficients v9 (slot b + 1).
+//   Row pass: thread = 8 outputs of one coefficient row, from the 12 elements of
+// each half that they need, x[2u + par] = sum_{s2 < L/2} h[par + 2 s2] A[u - s2] +
+// g[par + 2 s2] D[u - s2]; the 8 S rows of each half and the L/2 - 1 before them go
+// to LDS. Column pass: thread = one column and 16 rows from windows of
+// KB + L/2 - 1 elements of each half.
+// SYN_LEVEL: to out (basis b = blockIdx.z). ALLB (the finest level): the sum over
+// the bases stays in registers, and with the Dirac slot SYN_PLAIN gives
+// x = scale * s, SYN_PROX x = max(0, z - scale * s) and the Dirac dual update
+// v0 = clip(v0 + scale * x, -t w0, t w0). SMALL: n < 8, element by element.
+template <typename T, int MODE>
+__device__ __forceinline__ void syn_point(T *v9, const T *w9, const T *z, T *x, size_t p, T sum, T scale, T thr) {
+    const T tot = v9[p] + sum;
+    if (MODE == SYN_PLAIN) {
+        x[p] = scale * tot;
+    } else {
+        const T xo = fmax((T)0, z[p] - scale * tot);
+        x[p] = xo;
+        const T lim = thr * w9[p];
+        v9[p] = fmin(fmax(v9[p] + scale * xo, -lim), lim);
     }
+}
+
+template <typename T, int MODE, int S, bool SMALL>
+__global__ void __launch_bounds__(128 * S)
+k_syn(T *v9, const T *__restrict__ low, T *__restrict__ out, const T *__restrict__ w9, const T *__restrict__ z, int N,
+      int n, int coarsest, T scale, T thr) {
+    constexpr bool ALLB = MODE != SYN_LEVEL;
+    constexpr int PITCH = 2 * TC;
+    __shared__ __attribute__((aligned(16))) T mid[2 * (KB * S + LMAX / 2 - 1) * PITCH];
+    const int tid = threadIdx.x, half = n >> 1, hm = half - 1;
+    const int j = tid & 15, kbase = blockIdx.y * KB * S, u0 = blockIdx.x * TC + 4 * j;
+    const int strip = tid >> 7, col = tid & 127;
+    const int i0 = 2 * (kbase + strip * KB), gcol = blockIdx.x * 2 * TC + col;
+    const size_t NN = (size_t)N * N;
+    T acc[2 * KB] = {};
+    auto basis = [&](int b, auto Lc) {
+        constexpr int L = decltype(Lc)::value, S2 = L / 2, NR = KB * S + S2 - 1;
+        constexpr int NV = 1 + (S2 - 1 + 3) / 4, W0 = 4 * (NV - 1);     // vectors of a window, its elements before u0
+        const T *cf = v9 + (size_t)(b + 1) * NN;
+        const T *lo = coarsest ? cf : low + b * NN;
+        if (u0 < half) {
+            for (int rr = tid >> 4; rr < 2 * NR; rr += KB * S) {
+                const int vh = rr >= NR ? 1 : 0;
+                const int k = (kbase - (S2 - 1) + rr - vh * NR) & hm;
+                const T *ra = vh ? cf + (size_t)(half + k) * N : lo + (size_t)k * N;
+                const T *rd = cf + (size_t)(vh * half + k) * N + half;
+                T wa[4 * NV], wd[4 * NV];
 #pragma unroll
-    for (int u = 0; u < KB; ++u) {
+                for (int q = 0; q < NV; ++q) {
+                    const int c0 = u0 - W0 + 4 * q;
+                    vec4<T> va, vd;
+                    if (SMALL) {
+                        for (int e = 0; e < 4; ++e) {
+                            va[e] = ra[(c0 + e) & hm];
+                            vd[e] = rd[(c0 + e) & hm];
+                        }
+                    } else {
+                        va = load4<T>(ra + (c0 & hm));
+                        vd = load4<T>(rd + (c0 & hm));
+                    }
 #pragma unroll
-        for (int par = 0; par < 2; ++par) {
-            T v = 0;
+                    for (int e = 0; e < 4; ++e) {
+                        wa[4 * q + e] = va[e];
+                        wd[4 * q + e] = vd[e];
+                    }
+                }
+                T x[8];
 #pragma unroll
-            for (int s2 = 0; s2 < S2; ++s2) {
-                const int t = par + 2 * s2;
-                v += fh<T>(b, t) * ar[u - s2 + S2 - 1] + fg<T>(b, t) * dr[u - s2 + S2 - 1];
+                for (int u = 0; u < 4; ++u) {
+#pragma unroll
+                    for (int par = 0; par < 2; ++par) {
+                        T v = 0;
+#pragma unroll
+                        for (int s2 = 0; s2 < S2; ++s2) {
+                            v = fma(fh<T>(b, par + 2 * s2), wa[u + W0 - s2], v);
+                            v = fma(fg<T>(b, par + 2 * s2), wd[u + W0 - s2], v);
+                        }
+                        x[2 * u + par] = v;
+                    }
+                }
+                T *dst = mid + rr * PITCH + 8 * j;
+                constexpr int V = 16 / sizeof(T);
+#pragma unroll
+                for (int q = 0; q < 8 / V; ++q) {
+                    vec16<T> o;
+#pragma unroll
+                    for (int e = 0; e < V; ++e) o[e] = x[q * V + e];
+                    reinterpret_cast<vec16<T> *>(dst)[q] = o;
+                }
             }
-            x[2 * u + par] = v;
         }
-    }
-}
-
-// Column synthesis of level block n: the coarse block (rows and columns < n/2)
-// from work (or from the coefficients at the coarsest level), the rest from
-// the coefficients v9 (slot b + 1) -> tmp. Thread: column col, rows i0 .. i0 + 2 KB - 1.
-template <typename T, int KB>
-__global__ void __launch_bounds__(256) k_syn_cols(const T *__restrict__ v9, const T *__restrict__ work,
-                                                  T *__restrict__ tmp, int N, int n, int coarsest) {
-    const int b = blockIdx.z;
-    const int col = blockIdx.x * 64 + (threadIdx.x & 63);
-    const int i0 = (blockIdx.y * 4 + (threadIdx.x >> 6)) * 2 * KB, half = n >> 1;
-    if (col >= n || i0 >= n) return;
-    const size_t NN = (size_t)N * N;
-    const T *cf = v9 + (size_t)(b + 1) * NN + col;
-    const T *lo = (!coarsest && col < half) ? work + b * NN + col : cf;
-    T x[2 * KB];
-    with_length(b, [&](auto Lc) {
-        syn_block<T, decltype(Lc)::value, KB>(b, lo, cf + (size_t)half * N, N, i0, half, x);
-    });
-    T *dst = tmp + b * NN + col;
-#pragma unroll
-    for (int u = 0; u < 2 * KB; ++u)
-        if (i0 + u < n) dst[(size_t)(i0 + u) * N] = x[u];
-}
-
-// Row synthesis of one staged row (low half A = s[0, half), high half D =
-// s[half, n)) at output j: sum_{t = j mod 2} h[t] A[k] + g[t] D[k], k = (j - t)/2 mod half.
-// Used for the coarse levels with n < 8 only.
-template <typename T, int L>
-__device__ __forceinline__ T syn_row_at(int b, const T *row_s, int j, int half) {
-    const int hm = half - 1, j2 = j >> 1, par = j & 1;
-    T x = 0;
-#pragma unroll
-    for (int s2 = 0; s2 < L / 2; ++s2) {
-        const int k = (j2 - s2) & hm;
-        x += fh<T>(b, par + 2 * s2) * row_s[k] + fg<T>(b, par + 2 * s2) * row_s[half + k];
-    }
-    return x;
-}
-
-// Row synthesis of level block n < 8: tmp -> work. Workgroup: one row of one
-// basis staged in LDS, one output per lane.
-template <typename T>
-__global__ void __launch_bounds__(64) k_syn_rows_small(const T *__restrict__ tmp, T *__restrict__ work, int N,
-                                                       int n) {
-    __shared__ T row_s[8];
-    const int b = blockIdx.z, row = blockIdx.y, half = n >> 1;
-    const size_t NN = (size_t)N * N;
-    const T *src = tmp + b * NN + (size_t)row * N;
-    if (threadIdx.x < n) row_s[threadIdx.x] = src[threadIdx.x];
-    __syncthreads();
-    T *dst = work + b * NN + (size_t)row * N;
-    with_length(b, [&](auto Lc) {
-        if (threadIdx.x < n) dst[threadIdx.x] = syn_row_at<T, decltype(Lc)::value>(b, row_s, threadIdx.x, half);
-    });
-}
-
-// Register-blocked row synthesis (n >= 8). A row of one basis is staged in LDS
-// with a periodic halo of RH elements in front of each half:
-//   s[k] = A[(k - RH) mod half]  and  s[RH + half + k] = D[(k - RH) mod half],
-// k < RH + half. A lane computes the 8 consecutive outputs x[2u + par],
-// u = u0 .. u0 + 3 (u0 = 4 i for its block i), from the 12-element windows
-// s[u0 .. u0 + 12) of both halves, read as 16-byte vectors: A[u - s2] is
-// window element u - u0 + RH - s2 for s2 < L/2 <= 8.
-constexpr int RH = 8;
-constexpr int RWIN = 12;
-
-template <typename T>
-using vec8o = T __attribute__((ext_vector_type(8)));   // the 8 outputs of a lane block
-
-// Element e < n + 2 RH of the staged row: its source index in the row (low half, then high half).
-__device__ __forceinline__ int staged_src(int e, int half) {
-    const int hs = e >= RH + half ? 1 : 0;
-    const int k = e - hs * (RH + half);
-    return hs * half + ((k - RH) & (half - 1));
-}
-
-template <typename T>
-__device__ __forceinline__ void lds_window(const T *p, T (&w)[RWIN]) {
-    constexpr int E = 16 / sizeof(T);
-#pragma unroll
-    for (int i = 0; i < RWIN / E; ++i) {
-        const vec16<T> v = reinterpret_cast<const vec16<T> *>(p)[i];
-#pragma unroll
-        for (int e = 0; e < E; ++e) w[i * E + e] = v[e];
-    }
-}
-
-// acc[2u + par] += sum_{s2 < L/2} h[par + 2 s2] A[u0 + u - s2] + g[par + 2 s2] D[u0 + u - s2].
-template <typename T, int L>
-__device__ __forceinline__ void syn_row_block(int b, const T *s, int half, int u0, T (&acc)[8]) {
-    T wa[RWIN], wd[RWIN];
-    lds_window<T>(s + u0, wa);
-    lds_window<T>(s + RH + half + u0, wd);
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-#pragma unroll
-        for (int par = 0; par < 2; ++par) {
-            T v = acc[2 * u + par];
-#pragma unroll
-            for (int s2 = 0; s2 < L / 2; ++s2) {
-                v = fma(fh<T>(b, par + 2 * s2), wa[u + RH - s2], v);
-                v = fma(fg<T>(b, par + 2 * s2), wd[u + RH - s2], v);
-            }
-            acc[2 * u + par] = v;
-        }
-    }
-}
-
-// 8 outputs to library-owned memory (the level buffers, 8-element aligned blocks).
-template <typename T>
-__device__ __forceinline__ void store8(T *p, const T (&v)[8]) {
-    vec8o<T> o;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) o[e] = v[e];
-    *reinterpret_cast<vec8o<T> *>(p) = o;
-}
-
-// Row synthesis of level block n (8 <= n < N): tmp -> work. Workgroup: one
-// row of one basis, n / 8 lanes (at least 64).
-template <typename T>
-__global__ void __launch_bounds__(256) k_syn_rows(const T *__restrict__ tmp, T *__restrict__ work, int N, int n) {
-    extern __shared__ unsigned char smem_raw[];
-    T *s = reinterpret_cast<T *>(smem_raw);
-    const int b = blockIdx.z, row = blockIdx.y, half = n >> 1, tid = threadIdx.x;
-    const size_t NN = (size_t)N * N;
-    const T *src = tmp + b * NN + (size_t)row * N;
-    for (int e = tid; e < n + 2 * RH; e += blockDim.x) s[e] = src[staged_src(e, half)];
-    __syncthreads();
-    if (8 * tid >= n) return;
-    T acc[8] = {};
-    with_length(b, [&](auto Lc) { syn_row_block<T, decltype(Lc)::value>(b, s, half, 4 * tid, acc); });
-    store8<T>(work + b * NN + (size_t)row * N + 8 * tid, acc);
-}
-
-// Last row synthesis (n = N), summed over the 8 bases plus the Dirac slot:
-// SYN_PLAIN: x = scale * s; SYN_PROX: x = max(0, z - scale * s) and the
-// Dirac dual update v0 = clip(v0 + scale * x, -t w0, t w0). Workgroup: one
-// row, 256 lanes, each with NB blocks of 8 outputs (8 (tid + 256 ib)); the 8
-// bases' staged rows pass through LDS one after another, the next one loaded
-// into registers while the current one is used.
-template <typename T, int MODE, int NB>
-__global__ void __launch_bounds__(256) k_syn_final(const T *__restrict__ tmp, T *v9, const T *__restrict__ w9,
-                                                   const T *__restrict__ z, T *__restrict__ x, int N, T scale,
-                                                   T thr) {
-    extern __shared__ unsigned char smem_raw[];
-    T *s = reinterpret_cast<T *>(smem_raw);
-    constexpr int PQ = 8 * NB + 1;           // staged elements per lane: ceil((256 * 8 NB + 2 RH) / 256)
-    const int row = blockIdx.y, half = N >> 1, tid = threadIdx.x, ns = N + 2 * RH;
-    const size_t NN = (size_t)N * N;
-    T acc[NB][8], pre[PQ];
-    int src[PQ];                             // the staging sources, the same for every basis
-#pragma unroll
-    for (int ib = 0; ib < NB; ++ib)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[ib][e] = 0;
-    const T *r0 = tmp + (size_t)row * N;
-#pragma unroll
-    for (int q = 0; q < PQ; ++q) {
-        const int e = tid + 256 * q;
-        src[q] = e < ns ? staged_src(e, half) : 0;
-        pre[q] = e < ns ? r0[src[q]] : (T)0;
-    }
-    static_for<NW>([&](auto bc) {
-        constexpr int b = decltype(bc)::value;
         __syncthreads();
+        T ar[KB + S2 - 1], dr[KB + S2 - 1];
+        const T *lp = mid + strip * KB * PITCH + col, *hp = lp + NR * PITCH;
 #pragma unroll
-        for (int q = 0; q < PQ; ++q)
-            if (tid + 256 * q < ns) s[tid + 256 * q] = pre[q];
-        __syncthreads();
-        if (b + 1 < NW) {
-            const T *nxt = tmp + (b + 1) * NN + (size_t)row * N;
-#pragma unroll
-            for (int q = 0; q < PQ; ++q) {
-                const int e = tid + 256 * q;
-                if (e < ns) pre[q] = nxt[src[q]];
-            }
+        for (int q = 0; q < KB + S2 - 1; ++q) {
+            ar[q] = lp[q * PITCH];
+            dr[q] = hp[q * PITCH];
         }
 #pragma unroll
-        for (int ib = 0; ib < NB; ++ib)
-            if (8 * (tid + 256 * ib) < N) syn_row_block<T, 2 * (b + 1)>(b, s, half, 4 * (tid + 256 * ib), acc[ib]);
-    });
+        for (int u = 0; u < KB; ++u) {
 #pragma unroll
-    for (int ib = 0; ib < NB; ++ib) {
-        const int j0 = 8 * (tid + 256 * ib);
-        if (j0 >= N) break;
-        // element accesses: v9, z and x may be caller buffers of any element alignment
-        const size_t p = (size_t)row * N + j0;
+            for (int par = 0; par < 2; ++par) {
+                T v = acc[2 * u + par];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const T tot = v9[p + e] + acc[ib][e];
-            if (MODE == SYN_PLAIN) {
-                x[p + e] = scale * tot;
-            } else {
-                const T xo = fmax((T)0, z[p + e] - scale * tot);
-                x[p + e] = xo;
-                const T lim = thr * w9[p + e];
-                v9[p + e] = fmin(fmax(v9[p + e] + scale * xo, -lim), lim);
+                for (int s2 = 0; s2 < S2; ++s2) {
+                    v = fma(fh<T>(b, par + 2 * s2), ar[u - s2 + S2 - 1], v);
+                    v = fma(fg<T>(b, par + 2 * s2), dr[u - s2 + S2 - 1], v);
+                }
+                acc[2 * u + par] = v;
             }
         }
+    };
+    if (ALLB) {
+        static_for<NW>([&](auto bc) {
+            constexpr int b = decltype(bc)::value;
+            if (b > 0) __syncthreads();       // the previous basis' columns are read
+            basis(b, std::integral_constant<int, 2 * (b + 1)>{});
+        });
+    } else {
+        with_length(blockIdx.z, [&](auto Lc) { basis(blockIdx.z, Lc); });
     }
+    if (gcol >= n) return;
+#pragma unroll
+    for (int u = 0; u < 2 * KB; ++u) {
+        if (i0 + u >= n) break;
+        const size_t p = (size_t)(i0 + u) * N + gcol;
+        if constexpr (ALLB) syn_point<T, MODE>(v9, w9, z, out, p, acc[u], scale, thr);
+        else out[blockIdx.z * NN + p] = acc[u];
+    }
+}
+
+// The finest level's sum over the bases where their planes were written one by
+// one, with the Dirac slot.
+template <typename T, int MODE>
+__global__ void __launch_bounds__(256) k_syn_sum(const T *__restrict__ planes, T *v9, const T *__restrict__ w9,
+                                                 const T *__restrict__ z, T *__restrict__ x, int64_t n, T scale, T thr) {
+    const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (p >= n) return;
+    T sum = 0;
+#pragma unroll
+    for (int b = 0; b < NW; ++b) sum += planes[b * n + p];
+    syn_point<T, MODE>(v9, w9, z, x, (size_t)p, sum, scale, thr);
 }
 
 inline int cdiv(int a, int b) { return (a + b - 1) / b; }
@@ -583,41 +508,52 @@ void upload_filters(ri_ctx *c) {
     (void)c;
 }
 
+// launch(S, ALLB, SMALL) for the level block n. The finest level's bases in one
+// workgroup (ALLB) read the image once and keep the sum of the synthesis in
+// registers; it pays as soon as there is a workgroup per CU, if need be with half
+// the tile's rows (S = 2). Five sub-iterations at N = 2048: 924 us in
+// FP32 and 1774 us in FP64 against 1248 and 2354 us with a workgroup per basis and
+// a sum over the planes; at N = 1024 with S = 2 409 and 533 us against 406 and 686;
+// below, the workgroups are too few. Elsewhere the tallest tile that gives every CU
+// a workgroup: asking for two or four a CU measured the same within 2%.
+template <typename F>
+void dispatch_tile(ri_ctx *c, int n, bool finest, F &&launch) {
+    const int64_t t4 = (int64_t)cdiv(n, 2 * TC) * cdiv(n, 2 * KB * 4);   // tiles of S = 4
+    using std::integral_constant;
+    using no = std::false_type;
+    using yes = std::true_type;
+    const int cus = c->dev.cu_count;
+    if (n < 8) launch(integral_constant<int, 1>{}, no{}, yes{});
+    else if (finest && t4 >= cus) launch(integral_constant<int, 4>{}, yes{}, no{});
+    else if (finest && t4 * 2 >= cus) launch(integral_constant<int, 2>{}, yes{}, no{});
+    else if (t4 * NW >= cus) launch(integral_constant<int, 4>{}, no{}, no{});
+    else if (t4 * NW * 2 >= cus) launch(integral_constant<int, 2>{}, no{}, no{});
+    else launch(integral_constant<int, 1>{}, no{}, no{});
+}
+
 // Psi^dagger x into dst9 (FIN selects the dual update, the weights or the plain coefficients).
 template <typename T, int FIN>
 void analysis(ri_ctx *c, const T *x, T *dst9, T par, bool dirac, hipStream_t s) {
     SaraState &st = c->sara;
     const int N = c->N;
     const T scale = (T)(1.0 / 3.0);
-    T *work = (T *)st.work, *tmp = (T *)st.tmp;
+    T *const buf[2] = {(T *)st.work, (T *)st.tmp};   // the low-low blocks of even and odd levels
     const T *w9 = (const T *)st.w;
     if (dirac)
         hipLaunchKernelGGL(HIP_KERNEL_NAME(k_ana_dirac<T, FIN>), dim3(1024), dim3(256), 0, s, x, dst9,
                            (int64_t)N * N, scale, par);
     for (int l = 0; l < LEVELS; ++l) {
-        const int n = N >> l;
-        const T *in = l == 0 ? x : work;
+        const int n = N >> l, last = l == LEVELS - 1 ? 1 : 0;
+        const T *in = l == 0 ? x : buf[(l + 1) & 1];
         const int64_t in_bs = l == 0 ? 0 : (int64_t)N * N;
-        if (n % 8 != 0)
-            hipLaunchKernelGGL(k_ana_rows<T>, dim3(1, n, NW), dim3(256), sizeof(T) * n, s, in, in_bs, tmp, N, n);
-        else if (l == 0)
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_ana_rows_rb<T, 1>), dim3(1, n, 1), dim3(256),
-                               sizeof(T) * (n + AH), s, in, in_bs, tmp, N, n);
-        else
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_ana_rows_rb<T, 0>), dim3(1, n, NW),
-                               dim3(std::min(256, std::max(64, n / 8))), sizeof(T) * (n + AH), s, in, in_bs, tmp,
-                               N, n);
-        const int kb = col_block(n), last = l == LEVELS - 1 ? 1 : 0;
-        const dim3 g(cdiv(n, 64), cdiv(n / 2, 4 * kb), NW);
-        if (kb == 8)
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_ana_cols<T, FIN, 8>), g, dim3(256), 0, s, tmp, work, dst9, w9, N, n,
-                               last, scale, par);
-        else if (kb == 4)
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_ana_cols<T, FIN, 4>), g, dim3(256), 0, s, tmp, work, dst9, w9, N, n,
-                               last, scale, par);
-        else
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_ana_cols<T, FIN, 2>), g, dim3(256), 0, s, tmp, work, dst9, w9, N, n,
-                               last, scale, par);
+        auto launch = [&](auto Sc, auto ALLBc, auto SMALLc) {
+            constexpr int S = decltype(Sc)::value;
+            constexpr bool ALLB = decltype(ALLBc)::value;
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_ana<T, FIN, S, ALLB, decltype(SMALLc)::value>),
+                               dim3(cdiv(n, 2 * TC), cdiv(n, 2 * KB * S), ALLB ? 1 : NW), dim3(128 * S + 64), 0, s, in,
+                               in_bs, buf[l & 1], dst9, w9, N, n, last, scale, par);
+        };
+        dispatch_tile(c, n, l == 0, launch);
     }
 }
 
@@ -627,30 +563,22 @@ void synthesis(ri_ctx *c, T *v9, const T *z, T *x, T thr, hipStream_t s) {
     SaraState &st = c->sara;
     const int N = c->N;
     const T scale = (T)(1.0 / 3.0);
-    T *work = (T *)st.work, *tmp = (T *)st.tmp;
+    T *const buf[2] = {(T *)st.work, (T *)st.tmp};   // the blocks of even and odd levels
+    const T *w9 = (const T *)st.w;
     for (int l = LEVELS - 1; l >= 0; --l) {
-        const int n = N >> l;
-        const int kb = col_block(n), coarsest = l == LEVELS - 1 ? 1 : 0;
-        const dim3 g(cdiv(n, 64), cdiv(n, 4 * 2 * kb), NW);
-        if (kb == 8)
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_syn_cols<T, 8>), g, dim3(256), 0, s, v9, work, tmp, N, n, coarsest);
-        else if (kb == 4)
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_syn_cols<T, 4>), g, dim3(256), 0, s, v9, work, tmp, N, n, coarsest);
-        else
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_syn_cols<T, 2>), g, dim3(256), 0, s, v9, work, tmp, N, n, coarsest);
-        if (l > 0 && n >= 8)
-            hipLaunchKernelGGL(k_syn_rows<T>, dim3(1, n, NW), dim3(std::max(64, n / 8)), sizeof(T) * (n + 2 * RH), s,
-                               tmp, work, N, n);
-        else if (l > 0)
-            hipLaunchKernelGGL(k_syn_rows_small<T>, dim3(1, n, NW), dim3(64), 0, s, tmp, work, N, n);
+        const int n = N >> l, coarsest = l == LEVELS - 1 ? 1 : 0;
+        auto launch = [&](auto Sc, auto ALLBc, auto SMALLc) {
+            constexpr int S = decltype(Sc)::value;
+            constexpr bool ALLB = decltype(ALLBc)::value;
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_syn<T, ALLB ? MODE : (int)SYN_LEVEL, S, decltype(SMALLc)::value>),
+                               dim3(cdiv(n, 2 * TC), cdiv(n, 2 * KB * S), ALLB ? 1 : NW), dim3(128 * S), 0, s, v9,
+                               buf[(l + 1) & 1], ALLB ? x : buf[l & 1], w9, z, N, n, coarsest, scale, thr);
+            if (l == 0 && !ALLB)
+                hipLaunchKernelGGL(HIP_KERNEL_NAME(k_syn_sum<T, MODE>), dim3(cdiv(N * N, 256)), dim3(256), 0, s, buf[0],
+                                   v9, w9, z, x, (int64_t)N * N, scale, thr);
+        };
+        dispatch_tile(c, n, l == 0, launch);
     }
-    const size_t lds = sizeof(T) * (N + 2 * RH);
-    if (N <= 2048)
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_syn_final<T, MODE, 1>), dim3(1, N), dim3(256), lds, s, tmp, v9,
-                           (const T *)st.w, z, x, N, scale, thr);
-    else
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_syn_final<T, MODE, 2>), dim3(1, N), dim3(256), lds, s, tmp, v9,
-                           (const T *)st.w, z, x, N, scale, thr);
 }
 
 }  // namespace
