@@ -12,9 +12,9 @@
 // columns, so every global access is a contiguous row segment:
 //   pass A: N1-point transforms along rows n2 + N2*n1, times W_{N'}^{n2 k1};
 //   pass B: N2-point transforms along rows N2*k1 + n2, written to row k1 + N1*k2.
-// For N' = 4096 and 8192 each column's points stay in registers (a few lanes
-// per column, see k_colpass_a_reg); for the other sizes a stripe of CW
-// columns is transformed in LDS by Stockham passes.
+// For N' = 4096 and 8192 these are two launches with each column's points in registers
+// (a few lanes per column, see k_colpass_a_reg); below, one launch with whole columns
+// in LDS (k_colfft).
 #include <type_traits>
 #include <utility>
 
@@ -50,9 +50,22 @@ constexpr int brev(int k, int bits) {
 }
 constexpr int ilog2(int R) { return R <= 1 ? 0 : 1 + ilog2(R / 2); }
 
+// a b with the roundings spelled out, so that the same transform gives the same
+// bits from whichever kernel the compiler builds it into (left to itself it contracts
+// the imaginary part either way): the product that is rounded by itself is a.x b.y
+// (mulxy) or a.y b.x (mulyx).
+template <typename T>
+__device__ __forceinline__ cx<T> mulxy(cx<T> a, cx<T> b) {
+    return mk<T>(fma(a.x, b.x, -(a.y * b.y)), fma(a.y, b.x, a.x * b.y));
+}
+template <typename T>
+__device__ __forceinline__ cx<T> mulyx(cx<T> a, cx<T> b) {
+    return mk<T>(fma(a.x, b.x, -(a.y * b.y)), fma(a.x, b.y, a.y * b.x));
+}
+
 // In-register R-point DFT, natural order in and out:
-// V[k] = sum_r v[r] exp(-+ 2 pi i r k / R).
-template <typename T, int R>
+// V[k] = sum_r v[r] exp(-+ 2 pi i r k / R). X: with the roundings spelled out.
+template <typename T, int R, bool X = false>
 __device__ __forceinline__ void dft_reg(cx<T> *v, bool inv) {
 #pragma unroll
     for (int span = R / 2; span >= 1; span >>= 1) {
@@ -66,7 +79,7 @@ __device__ __forceinline__ void dft_reg(cx<T> *v, bool inv) {
             const int e = mloc * (16 / (2 * span));
             if (e != 0) {
                 cx<T> w = mk<T>((T)kRoot16[e][0], inv ? -(T)kRoot16[e][1] : (T)kRoot16[e][1]);
-                d = d * w;
+                d = !X ? d * w : kRoot16[e][0] < 0 ? mulyx(d, w) : mulxy(d, w);
             }
             v[m + span] = d;
         }
@@ -81,33 +94,29 @@ __device__ __forceinline__ void dft_reg(cx<T> *v, bool inv) {
 template <bool PAD>
 __device__ __forceinline__ int pidx(int i) { return PAD ? i + (i >> 5) : i; }
 
-// One Stockham radix-R pass over s[L][CW] (transform along the first index),
-// in place: every thread loads its groups, barrier, computes, stores, barrier.
-// Requires (L/R)*CW <= (16/R) * blockDim.x.
+// One Stockham radix-R pass over the row s[L], in place: every thread loads its
+// groups, barrier, computes, stores, barrier. Requires L/R <= (16/R) * blockDim.x.
 template <typename T, int R, bool PAD>
-__device__ __forceinline__ void stockham_pass(cx<T> *s, int L, int logCW, int Ns, const cx<T> *__restrict__ tw,
-                                              int tw_mul, bool inv) {
+__device__ __forceinline__ void stockham_pass(cx<T> *s, int L, int Ns, const cx<T> *__restrict__ tw,
+                                              bool inv) {
     constexpr int G = 16 / R;
-    const int CW = 1 << logCW;
-    const int ng = (L / R) << logCW;
+    const int ng = L / R;
     cx<T> v[G][R];
 #pragma unroll
     for (int i = 0; i < G; ++i) {
-        const int g = threadIdx.x + i * blockDim.x;
-        if (g < ng) {
-            const int col = g & (CW - 1), j = g >> logCW;
+        const int j = threadIdx.x + i * blockDim.x;
+        if (j < ng) {
 #pragma unroll
-            for (int r = 0; r < R; ++r) v[i][r] = s[pidx<PAD>(((j + r * (L / R)) << logCW) + col)];
+            for (int r = 0; r < R; ++r) v[i][r] = s[pidx<PAD>(j + r * ng)];
         }
     }
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < G; ++i) {
-        const int g = threadIdx.x + i * blockDim.x;
-        if (g < ng) {
-            const int col = g & (CW - 1), j = g >> logCW;
+        const int j = threadIdx.x + i * blockDim.x;
+        if (j < ng) {
             const int jm = j & (Ns - 1);
-            const int step = jm * tw_mul * (L / (Ns * R));
+            const int step = jm * (L / (Ns * R));
             if (jm != 0) {
 #pragma unroll
                 for (int r = 1; r < R; ++r) {
@@ -119,23 +128,10 @@ __device__ __forceinline__ void stockham_pass(cx<T> *s, int L, int logCW, int Ns
             dft_reg<T, R>(v[i], inv);
             const int idxD = (j - jm) * R + jm;
 #pragma unroll
-            for (int r = 0; r < R; ++r) s[pidx<PAD>(((idxD + r * Ns) << logCW) + col)] = v[i][r];
+            for (int r = 0; r < R; ++r) s[pidx<PAD>(idxD + r * Ns)] = v[i][r];
         }
     }
     __syncthreads();
-}
-
-// Full L-point transform of every column of s[L][CW]; caller syncs before.
-template <typename T, bool PAD>
-__device__ void fft_lds(cx<T> *s, int logL, int logCW, const cx<T> *__restrict__ tw, int tw_mul, bool inv) {
-    const int L = 1 << logL;
-    int Ns = 1, rem = logL;
-    while (rem > 0) {
-        if (rem >= 4) { stockham_pass<T, 16, PAD>(s, L, logCW, Ns, tw, tw_mul, inv); Ns <<= 4; rem -= 4; }
-        else if (rem == 3) { stockham_pass<T, 8, PAD>(s, L, logCW, Ns, tw, tw_mul, inv); Ns <<= 3; rem -= 3; }
-        else if (rem == 2) { stockham_pass<T, 4, PAD>(s, L, logCW, Ns, tw, tw_mul, inv); Ns <<= 2; rem -= 2; }
-        else { stockham_pass<T, 2, PAD>(s, L, logCW, Ns, tw, tw_mul, inv); Ns <<= 1; rem -= 1; }
-    }
 }
 
 __device__ __forceinline__ bool in_band(int r, int N, int Np) { return r < N / 2 || r >= Np - N / 2; }
@@ -146,7 +142,7 @@ __device__ __forceinline__ bool in_band(int r, int N, int Np) { return r < N / 2
 // group j from ld(index) and leaves 16 j + r in LDS; the last pass (radix R,
 // Ns = L/R, twiddle step j) hands outputs j + r Ns to st(index, value). Both
 // index patterns run contiguously over j, so the global accesses coalesce; the
-// passes between are the LDS Stockham passes. Same arithmetic as fft_lds.
+// passes between are the LDS Stockham passes.
 template <typename T, bool PAD, typename Load>
 __device__ __forceinline__ void row_first_pass(cx<T> *s, int L, bool inv, Load &&ld) {
     const int ng = L / 16;
@@ -191,7 +187,7 @@ __device__ __forceinline__ void row_fft(cx<T> *s, int logL, const cx<T> *__restr
     row_first_pass<T, PAD>(s, L, inv, ld);
     int Ns = 16, rem = logL - 4;
     while (rem > 4) {
-        stockham_pass<T, 16, PAD>(s, L, 0, Ns, tw, 1, inv);
+        stockham_pass<T, 16, PAD>(s, L, Ns, tw, inv);
         Ns <<= 4;
         rem -= 4;
     }
@@ -279,52 +275,137 @@ __global__ void __launch_bounds__(512) k_irowfft_crop(const cx<T> *__restrict__ 
     row_fft<T, PAD>(s, logNp, tw, true, [&](int k) { return row[k]; }, st);
 }
 
-// Four-step pass A (in place): rows n2 + N2*n1 of stripe [x0, x0+CW).
-template <typename T>
-__global__ void k_colpass_a(cx<T> *__restrict__ grid, const cx<T> *__restrict__ tw, int N, int logNp, int logN1,
-                            int logN2, int logCW, int band_in, int inv) {
-    extern __shared__ unsigned char smem_raw[];
-    cx<T> *s = reinterpret_cast<cx<T> *>(smem_raw);
-    const int Np = 1 << logNp, N1 = 1 << logN1, N2 = 1 << logN2, CW = 1 << logCW;
-    const int x0 = blockIdx.x * CW, n2 = blockIdx.y;
-    const int nel = N1 * CW;
-    for (int e = threadIdx.x; e < nel; e += blockDim.x) {
-        const int n1 = e >> logCW, c = e & (CW - 1);
-        const int r = n2 + N2 * n1;
-        cx<T> v = mk<T>((T)0, (T)0);
-        if (!band_in || in_band(r, N, Np)) v = grid[(size_t)r * Np + x0 + c];
-        s[e] = v;
-    }
-    __syncthreads();
-    fft_lds<T, false>(s, logN1, logCW, tw, Np >> logN1, inv != 0);
-    for (int e = threadIdx.x; e < nel; e += blockDim.x) {
-        const int k1 = e >> logCW, c = e & (CW - 1);
-        cx<T> w = tw[n2 * k1];
-        if (inv) w.y = -w.y;
-        grid[(size_t)(n2 + N2 * k1) * Np + x0 + c] = s[e] * w;
-    }
+// ---------------------------------------------------------------------------
+// Column transforms up to N' = 2048: a workgroup has CW whole columns in LDS, one
+// read and one write of the grid. The arithmetic is that of the four-step form
+// N' = N1 N2: N1-point transforms over the rows n2 + N2 n1, times W_{N'}^{n2 k1},
+// N2-point transforms over n2, frequency k1 + N1 k2; each of the two by a radix-16
+// pass (radix N1 or N2 below 16) and a radix-2 or -4 one. Neighbouring stripes run
+// on one XCD (workgroups are dealt to the 8 XCDs in turn), whose L2 holds the lines
+// they share. Bound by memory latency: 18 us at N' = 2048 in FP32 for 50 MB (10 us
+// at the rate of a copy), 11 at 1024 and 5 at 256, with 4 columns of FP32 (2 of FP64) a
+// workgroup; 8 columns measured 18, 11.5 and 5, and a launch for each of the two
+// transforms with the grid in between 49, 29 and 18.
+// ---------------------------------------------------------------------------
+template <typename F, int... I>
+__device__ __forceinline__ void static_for_(F &&f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
 }
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F &&f) { static_for_(f, std::make_integer_sequence<int, N>{}); }
 
-// Four-step pass B: rows N2*k1 + n2 -> rows k1 + N1*k2, or, in place
-// (out == in), -> rows N2*k1 + k2 (a workgroup's own rows).
-template <typename T>
-__global__ void k_colpass_b(const cx<T> *in, cx<T> *out, const cx<T> *__restrict__ tw,
-                            int N, int logNp, int logN1, int logN2, int logCW, int band_out, int inv) {
+template <typename T, int LOGNP>
+struct FullCol {
+    static constexpr int NP = 1 << LOGNP, LOG1 = full_log_n1(LOGNP), N1 = 1 << LOG1, N2 = NP >> LOG1;
+    static constexpr int LCW = sizeof(T) == 4 ? 2 : 1, CW = 1 << LCW;
+    static constexpr int NT = NP * CW / 16 < 64 ? 64 : NP * CW / 16;
+    static constexpr int RA = N1 < 16 ? N1 : 16, RA2 = N1 / RA, RB = N2 < 16 ? N2 : 16, RB2 = N2 / RB;
+    static constexpr size_t LDS = sizeof(cx<T>) * (size_t)(NP + NP / 16) * CW;
+
+    // LDS element of point i of column col (padded against bank conflicts of the 16-strided stores)
+    static __device__ __forceinline__ int at(int i, int col) { return ((i + (i >> 4)) << LCW) + col; }
+
+    // f(q, col, registers) for the thread's groups of a radix-R pass.
+    template <int R, typename F>
+    static __device__ __forceinline__ void groups(cx<T> *v, F &&f) {
+#pragma unroll
+        for (int i = 0; i < 16 / R; ++i) {
+            const int g = threadIdx.x + i * NT;
+            if (16 / R * NT > NP / R * CW && g >= NP / R * CW) continue;
+            f(g >> LCW, g & (CW - 1), v + i * R);
+        }
+    }
+    template <int R>
+    static __device__ __forceinline__ void twiddle(cx<T> *v, const cx<T> *__restrict__ tw, int step, bool inv) {
+        if (step == 0) return;
+#pragma unroll
+        for (int r = 1; r < R; ++r) {
+            cx<T> w = tw[step * r];
+            if (inv) w.y = -w.y;
+            v[r] = mulxy(v[r], w);
+        }
+    }
+};
+
+template <typename T, int LOGNP>
+__global__ void __launch_bounds__((FullCol<T, LOGNP>::NT))
+k_colfft(const cx<T> *in, cx<T> *out, const cx<T> *__restrict__ tw, int N, int band_in, int band_out, int inv_) {
+    using C = FullCol<T, LOGNP>;
     extern __shared__ unsigned char smem_raw[];
     cx<T> *s = reinterpret_cast<cx<T> *>(smem_raw);
-    const int Np = 1 << logNp, N1 = 1 << logN1, N2 = 1 << logN2, CW = 1 << logCW;
-    const int x0 = blockIdx.x * CW, k1 = blockIdx.y;
-    const int nel = N2 * CW;
-    for (int e = threadIdx.x; e < nel; e += blockDim.x) {
-        const int n2 = e >> logCW, c = e & (CW - 1);
-        s[e] = in[(size_t)(N2 * k1 + n2) * Np + x0 + c];
-    }
+    constexpr int NP = C::NP, N1 = C::N1, N2 = C::N2, RA = C::RA, RA2 = C::RA2, RB = C::RB, RB2 = C::RB2;
+    const bool inv = inv_ != 0, permuted = out == in;
+    const int nb = gridDim.x, b = (nb & 7) ? (int)blockIdx.x : (int)(blockIdx.x & 7) * (nb >> 3) + (blockIdx.x >> 3);
+    const int x0 = b * C::CW;
+    cx<T> v[16];
+    C::template groups<RA>(v, [&](int q, int col, cx<T> *u) {
+        const int j = q & (N1 / RA - 1), n2 = q / (N1 / RA);
+#pragma unroll
+        for (int r = 0; r < RA; ++r) {
+            const int row = n2 + N2 * (j + r * (N1 / RA));
+            u[r] = (!band_in || in_band(row, N, NP)) ? in[(size_t)row * NP + x0 + col] : mk<T>((T)0, (T)0);
+        }
+    });
+    auto four_step = [&](cx<T> *u, int R, int n2, int k0, int dk) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            cx<T> w = tw[n2 * (k0 + dk * r)];
+            if (inv) w.y = -w.y;
+            u[r] = mulyx(u[r], w);
+        }
+    };
+    C::template groups<RA>(v, [&](int q, int col, cx<T> *u) {
+        const int j = q & (N1 / RA - 1), n2 = q / (N1 / RA);
+        dft_reg<T, RA, true>(u, inv);
+        if (RA2 == 1) four_step(u, RA, n2, 0, 1);
+#pragma unroll
+        for (int r = 0; r < RA; ++r) s[C::at(n2 * N1 + RA * j + r, col)] = u[r];
+    });
     __syncthreads();
-    fft_lds<T, false>(s, logN2, logCW, tw, Np >> logN2, inv != 0);
-    for (int e = threadIdx.x; e < nel; e += blockDim.x) {
-        const int k2 = e >> logCW, c = e & (CW - 1);
-        const int r = out == in ? N2 * k1 + k2 : k1 + N1 * k2;
-        if (!band_out || in_band(r, N, Np)) out[(size_t)r * Np + x0 + c] = s[e];
+    if constexpr (RA2 > 1) {
+        C::template groups<RA2>(v, [&](int q, int col, cx<T> *u) {
+            const int j = q & 15, n2 = q >> 4;
+#pragma unroll
+            for (int r = 0; r < RA2; ++r) u[r] = s[C::at(n2 * N1 + j + 16 * r, col)];
+            C::template twiddle<RA2>(u, tw, j * N2, inv);
+            dft_reg<T, RA2, true>(u, inv);
+            four_step(u, RA2, n2, j, 16);
+#pragma unroll
+            for (int r = 0; r < RA2; ++r) s[C::at(n2 * N1 + j + 16 * r, col)] = u[r];
+        });
+        __syncthreads();
+    }
+    auto store = [&](int k1, int k2, int col, cx<T> val) {
+        const int k = k1 + N1 * k2, row = permuted ? N2 * k1 + k2 : k;
+        if (!band_out || in_band(row, N, NP)) out[(size_t)row * NP + x0 + col] = val;
+    };
+    C::template groups<RB>(v, [&](int q, int col, cx<T> *u) {
+        const int k1 = q & (N1 - 1), j = q >> C::LOG1;
+#pragma unroll
+        for (int r = 0; r < RB; ++r) u[r] = s[C::at((j + r * (N2 / RB)) * N1 + k1, col)];
+        dft_reg<T, RB, true>(u, inv);
+        if (RB2 == 1) {
+#pragma unroll
+            for (int r = 0; r < RB; ++r) store(k1, r, col, u[r]);
+        }
+    });
+    if constexpr (RB2 > 1) {
+        __syncthreads();
+        C::template groups<RB>(v, [&](int q, int col, cx<T> *u) {
+            const int k1 = q & (N1 - 1), j = q >> C::LOG1;
+#pragma unroll
+            for (int r = 0; r < RB; ++r) s[C::at((RB * j + r) * N1 + k1, col)] = u[r];
+        });
+        __syncthreads();
+        C::template groups<RB2>(v, [&](int q, int col, cx<T> *u) {
+            const int k1 = q & (N1 - 1), j = q >> C::LOG1;
+#pragma unroll
+            for (int r = 0; r < RB2; ++r) u[r] = s[C::at((j + 16 * r) * N1 + k1, col)];
+            C::template twiddle<RB2>(u, tw, j * N1, inv);
+            dft_reg<T, RB2, true>(u, inv);
+#pragma unroll
+            for (int r = 0; r < RB2; ++r) store(k1, j + 16 * r, col, u[r]);
+        });
     }
 }
 
@@ -337,13 +418,6 @@ __global__ void k_colpass_b(const cx<T> *in, cx<T> *out, const cx<T> *__restrict
 // decimation in frequency, natural order in, bit-reversed out; twiddles come
 // from the FP64-computed table.
 // ---------------------------------------------------------------------------
-template <typename F, int... I>
-__device__ __forceinline__ void static_for_(F &&f, std::integer_sequence<int, I...>) {
-    (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F &&f) { static_for_(f, std::make_integer_sequence<int, N>{}); }
-
 template <typename T, int P>
 __device__ __forceinline__ void fftp_reg(cx<T> *v, const cx<T> *__restrict__ tw, int tw_mul, bool inv) {
     static_for<ilog2(P)>([&](auto St) {
@@ -514,10 +588,10 @@ __global__ void __launch_bounds__(512) k_half_rows(const T *__restrict__ x, cx<T
     });
     int Ns = 16, rem = logNp - 4;
     while (rem > 0) {
-        if (rem >= 4) { stockham_pass<T, 16, PAD>(s, Np, 0, Ns, tw, 1, false); Ns <<= 4; rem -= 4; }
-        else if (rem == 3) { stockham_pass<T, 8, PAD>(s, Np, 0, Ns, tw, 1, false); Ns <<= 3; rem -= 3; }
-        else if (rem == 2) { stockham_pass<T, 4, PAD>(s, Np, 0, Ns, tw, 1, false); Ns <<= 2; rem -= 2; }
-        else { stockham_pass<T, 2, PAD>(s, Np, 0, Ns, tw, 1, false); Ns <<= 1; rem -= 1; }
+        if (rem >= 4) { stockham_pass<T, 16, PAD>(s, Np, Ns, tw, false); Ns <<= 4; rem -= 4; }
+        else if (rem == 3) { stockham_pass<T, 8, PAD>(s, Np, Ns, tw, false); Ns <<= 3; rem -= 3; }
+        else if (rem == 2) { stockham_pass<T, 4, PAD>(s, Np, Ns, tw, false); Ns <<= 2; rem -= 2; }
+        else { stockham_pass<T, 2, PAD>(s, Np, Ns, tw, false); Ns <<= 1; rem -= 1; }
     }
     cx<T> *ra = scr + (size_t)((iy - N / 2) & (N - 1)) * scratch_pitch(N);
     cx<T> *rb = ra + scratch_pitch(N);   // n and n + 1 are neighbours: n is even
@@ -792,7 +866,7 @@ void half_cols(ri_ctx *c, Prec<T> &p, const cx<T> *in, cx<T> *out, bool inv, hip
 template <typename T, int L>
 constexpr int lanes_per_column() { return (L * (int)sizeof(cx<T>)) / 512 < 1 ? 1 : (L * (int)sizeof(cx<T>)) / 512; }
 
-int threads_for(int L, int CW) { return L * CW / 16 < 64 ? 64 : L * CW / 16; }
+int threads_for(int L) { return L / 16 < 64 ? 64 : L / 16; }
 
 // Column transforms of grid_io (scratch) into grid_out; grid_out == grid_io
 // leaves the second pass in place (permuted rows). band: the N packed band rows
@@ -820,22 +894,21 @@ void colfft(ri_ctx *c, cx<T> *grid_io, cx<T> *grid_out, const cx<T> *tw, bool in
                            (const cx<T> *)grid_io, grid_out, tw, c->N, logNp, band_out ? 1 : 0, inv ? 1 : 0);
         return;
     }
-    int logCW = sizeof(T) == 4 ? 6 : 5;
-    if ((1 << logCW) > Np) logCW = logNp;
-    const int CW = 1 << logCW;
-    {
-        const int L = 1 << logN1;
-        dim3 grid(Np / CW, 1 << logN2);
-        size_t lds = sizeof(cx<T>) * (size_t)L * CW;
-        hipLaunchKernelGGL(k_colpass_a<T>, grid, dim3(threads_for(L, CW)), lds, s, grid_io, tw, c->N, logNp, logN1,
-                           logN2, logCW, band_in ? 1 : 0, inv ? 1 : 0);
-    }
-    {
-        const int L = 1 << logN2;
-        dim3 grid(Np / CW, 1 << logN1);
-        size_t lds = sizeof(cx<T>) * (size_t)L * CW;
-        hipLaunchKernelGGL(k_colpass_b<T>, grid, dim3(threads_for(L, CW)), lds, s, grid_io, grid_out, tw, c->N,
-                           logNp, logN1, logN2, logCW, band_out ? 1 : 0, inv ? 1 : 0);
+    auto launch = [&](auto LOGNP) {
+        using C = FullCol<T, decltype(LOGNP)::value>;
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_colfft<T, decltype(LOGNP)::value>), dim3(Np / C::CW), dim3(C::NT), C::LDS,
+                           s, (const cx<T> *)grid_io, grid_out, tw, c->N, band_in ? 1 : 0, band_out ? 1 : 0,
+                           inv ? 1 : 0);
+    };
+    switch (logNp) {
+        case 5: return launch(std::integral_constant<int, 5>{});
+        case 6: return launch(std::integral_constant<int, 6>{});
+        case 7: return launch(std::integral_constant<int, 7>{});
+        case 8: return launch(std::integral_constant<int, 8>{});
+        case 9: return launch(std::integral_constant<int, 9>{});
+        case 10: return launch(std::integral_constant<int, 10>{});
+        case 11: return launch(std::integral_constant<int, 11>{});
+        default: throw Error(RI_EUNSUPPORTED, "image side outside 16 .. 4096");
     }
 }
 
@@ -853,10 +926,10 @@ template <typename T>
 void launch_zpad_rows(ri_ctx *c, Prec<T> &p, const T *x, cx<T> *dst, const cx<T> *chirp, int rowmask,
                       const Clear<T> &z, hipStream_t s) {
     if (row_pad<T>(c))
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_zpad_rowfft<T, true>), dim3(c->N), dim3(threads_for(c->Np, 1)),
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_zpad_rowfft<T, true>), dim3(c->N), dim3(threads_for(c->Np)),
                            row_lds<T>(c), s, x, dst, p.icorr, p.tw, c->N, c->logNp, chirp, rowmask, z);
     else
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_zpad_rowfft<T, false>), dim3(c->N), dim3(threads_for(c->Np, 1)),
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_zpad_rowfft<T, false>), dim3(c->N), dim3(threads_for(c->Np)),
                            row_lds<T>(c), s, x, dst, p.icorr, p.tw, c->N, c->logNp, chirp, rowmask, z);
 }
 
@@ -891,10 +964,10 @@ void adj_fft_crop(ri_ctx *c, Prec<T> &p, T *x, hipStream_t s) {
         const cx<T> *ch = c->P > 1 ? p.chirp + (size_t)st * c->N * c->N : nullptr;
         colfft<T>(c, p.gridA + (size_t)st * Np * Np, p.gridB, p.tw, true, false, true, s);
         if (row_pad<T>(c))
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_irowfft_crop<T, true>), dim3(c->N), dim3(threads_for(Np, 1)),
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_irowfft_crop<T, true>), dim3(c->N), dim3(threads_for(Np)),
                                row_lds<T>(c), s, p.gridB, x, p.icorr, p.tw, c->N, c->logNp, ch, st > 0 ? 1 : 0);
         else
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_irowfft_crop<T, false>), dim3(c->N), dim3(threads_for(Np, 1)),
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_irowfft_crop<T, false>), dim3(c->N), dim3(threads_for(Np)),
                                row_lds<T>(c), s, p.gridB, x, p.icorr, p.tw, c->N, c->logNp, ch, st > 0 ? 1 : 0);
     }
 }
@@ -927,10 +1000,10 @@ void fwd_half_fft(ri_ctx *c, Prec<T> &p, const T *x, const Clear<T> &z, hipStrea
     ProfScope prof(c, PROF_FFT, s);
     cx<T> *scr = half_scratch<T>(c, p);
     if (row_pad<T>(c))
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_half_rows<T, true>), dim3(N / 2), dim3(threads_for(Np, 1)), row_lds<T>(c),
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_half_rows<T, true>), dim3(N / 2), dim3(threads_for(Np)), row_lds<T>(c),
                            s, x, scr, p.icorr, p.tw, N, c->logNp, z);
     else
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_half_rows<T, false>), dim3(N / 2), dim3(threads_for(Np, 1)),
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_half_rows<T, false>), dim3(N / 2), dim3(threads_for(Np)),
                            row_lds<T>(c), s, x, scr, p.icorr, p.tw, N, c->logNp, z);
     half_cols<T>(c, p, scr, p.gridB, false, s);
 }
@@ -942,10 +1015,10 @@ void adj_half_fft(ri_ctx *c, Prec<T> &p, T *x, hipStream_t s) {
     cx<T> *scr = half_scratch<T>(c, p);
     half_cols<T>(c, p, p.gridA, scr, true, s);
     if (row_pad<T>(c))
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_half_irows<T, true>), dim3(N / 2), dim3(threads_for(Np, 1)),
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_half_irows<T, true>), dim3(N / 2), dim3(threads_for(Np)),
                            row_lds<T>(c), s, scr, x, p.icorr, p.tw, N, c->logNp);
     else
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_half_irows<T, false>), dim3(N / 2), dim3(threads_for(Np, 1)),
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_half_irows<T, false>), dim3(N / 2), dim3(threads_for(Np)),
                            row_lds<T>(c), s, scr, x, p.icorr, p.tw, N, c->logNp);
 }
 

@@ -265,7 +265,7 @@ template <typename T> void operator_adj_fft(ri_ctx *c, Prec<T> &p, T *x, hipStre
 // Grid row ky = k1 + N1 k2 of the whole plane without w-stacking is stored at
 // N2 k1 + k2 (N' = N1 N2), where the column transform's second pass leaves it
 // when it works in place.
-inline int full_log_n1(int logNp) { return (logNp + 1) / 2; }
+inline __host__ __device__ constexpr int full_log_n1(int logNp) { return (logNp + 1) / 2; }
 
 // gridding.hip
 enum { OP_DEGRID = 1, OP_GRID = 2, OP_FUSED = 3 };
