@@ -50,22 +50,33 @@ constexpr int brev(int k, int bits) {
 }
 constexpr int ilog2(int R) { return R <= 1 ? 0 : 1 + ilog2(R / 2); }
 
-// a b with the roundings spelled out, so that the same transform gives the same
-// bits from whichever kernel the compiler builds it into (left to itself it contracts
-// the imaginary part either way): the product that is rounded by itself is a.x b.y
-// (mulxy) or a.y b.x (mulyx).
-template <typename T>
-__device__ __forceinline__ cx<T> mulxy(cx<T> a, cx<T> b) {
-    return mk<T>(fma(a.x, b.x, -(a.y * b.y)), fma(a.y, b.x, a.x * b.y));
+// Products of the forward transforms with their roundings spelled out, so that the
+// same transform gives the same bits from whichever kernel the compiler builds it
+// into (left to itself it contracts a sum of two products either way, and shares
+// products where both parts of w are alike). XR: the real part's product that is
+// rounded by itself is a.x b.x, else a.y b.y; XI: the imaginary part's is a.x b.y,
+// else a.y b.x.
+template <bool XR, bool XI, typename T>
+__device__ __forceinline__ cx<T> mulr(cx<T> a, cx<T> b) {
+    return mk<T>(XR ? fma(a.y, -b.y, a.x * b.x) : fma(a.x, b.x, -(a.y * b.y)),
+                 XI ? fma(a.y, b.x, a.x * b.y) : fma(a.x, b.y, a.y * b.x));
 }
-template <typename T>
-__device__ __forceinline__ cx<T> mulyx(cx<T> a, cx<T> b) {
-    return mk<T>(fma(a.x, b.x, -(a.y * b.y)), fma(a.x, b.y, a.y * b.x));
+// Who transforms: anyone, the columns, or the first, the middle or the last pass of a row.
+enum { MUL_ANY = 0, MUL_COLS, MUL_FIRST, MUL_MID, MUL_LAST };
+// d w for the 16th root of unity with exponent e, at input m of the butterflies.
+template <typename T, int X>
+__device__ __forceinline__ cx<T> mul_root(cx<T> d, cx<T> w, int e, int m) {
+    if (X == MUL_ANY) return d * w;
+    if (X == MUL_COLS) return e > 4 ? mulr<false, false>(d, w) : mulr<false, true>(d, w);
+    if (e == 5 || e == 7) return mulr<true, false>(d, w);
+    if (X == MUL_FIRST) return (e & 1) ? mulr<false, true>(d, w) : mulr<false, false>(d, w);
+    if ((X == MUL_LAST && e == 6) || m == 9 || m == 11) return mulr<false, false>(d, w);
+    return mulr<true, true>(d, w);
 }
 
 // In-register R-point DFT, natural order in and out:
-// V[k] = sum_r v[r] exp(-+ 2 pi i r k / R). X: with the roundings spelled out.
-template <typename T, int R, bool X = false>
+// V[k] = sum_r v[r] exp(-+ 2 pi i r k / R).
+template <typename T, int R, int X = MUL_ANY>
 __device__ __forceinline__ void dft_reg(cx<T> *v, bool inv) {
 #pragma unroll
     for (int span = R / 2; span >= 1; span >>= 1) {
@@ -79,7 +90,7 @@ __device__ __forceinline__ void dft_reg(cx<T> *v, bool inv) {
             const int e = mloc * (16 / (2 * span));
             if (e != 0) {
                 cx<T> w = mk<T>((T)kRoot16[e][0], inv ? -(T)kRoot16[e][1] : (T)kRoot16[e][1]);
-                d = !X ? d * w : kRoot16[e][0] < 0 ? mulyx(d, w) : mulxy(d, w);
+                d = mul_root<T, X>(d, w, e, m);
             }
             v[m + span] = d;
         }
@@ -91,113 +102,102 @@ __device__ __forceinline__ void dft_reg(cx<T> *v, bool inv) {
     for (int k = 0; k < R; ++k) v[k] = t[k];
 }
 
-template <bool PAD>
-__device__ __forceinline__ int pidx(int i) { return PAD ? i + (i >> 5) : i; }
-
-// One Stockham radix-R pass over the row s[L], in place: every thread loads its
-// groups, barrier, computes, stores, barrier. Requires L/R <= (16/R) * blockDim.x.
-template <typename T, int R, bool PAD>
-__device__ __forceinline__ void stockham_pass(cx<T> *s, int L, int Ns, const cx<T> *__restrict__ tw,
-                                              bool inv) {
-    constexpr int G = 16 / R;
-    const int ng = L / R;
-    cx<T> v[G][R];
-#pragma unroll
-    for (int i = 0; i < G; ++i) {
-        const int j = threadIdx.x + i * blockDim.x;
-        if (j < ng) {
-#pragma unroll
-            for (int r = 0; r < R; ++r) v[i][r] = s[pidx<PAD>(j + r * ng)];
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < G; ++i) {
-        const int j = threadIdx.x + i * blockDim.x;
-        if (j < ng) {
-            const int jm = j & (Ns - 1);
-            const int step = jm * (L / (Ns * R));
-            if (jm != 0) {
-#pragma unroll
-                for (int r = 1; r < R; ++r) {
-                    cx<T> w = tw[step * r];
-                    if (inv) w.y = -w.y;
-                    v[i][r] = v[i][r] * w;
-                }
-            }
-            dft_reg<T, R>(v[i], inv);
-            const int idxD = (j - jm) * R + jm;
-#pragma unroll
-            for (int r = 0; r < R; ++r) s[pidx<PAD>(idxD + r * Ns)] = v[i][r];
-        }
-    }
-    __syncthreads();
-}
-
 __device__ __forceinline__ bool in_band(int r, int N, int Np) { return r < N / 2 || r >= Np - N / 2; }
 
-// Row transforms (one row of L = N' points per workgroup) read their input
-// straight into the first pass and write their output straight from the last:
-// the first pass (radix 16, Ns = 1, no twiddles) takes inputs j + r L/16 of
-// group j from ld(index) and leaves 16 j + r in LDS; the last pass (radix R,
-// Ns = L/R, twiddle step j) hands outputs j + r Ns to st(index, value). Both
-// index patterns run contiguously over j, so the global accesses coalesce; the
-// passes between are the LDS Stockham passes.
-template <typename T, bool PAD, typename Load>
-__device__ __forceinline__ void row_first_pass(cx<T> *s, int L, bool inv, Load &&ld) {
-    const int ng = L / 16;
-    for (int j = threadIdx.x; j < ng; j += blockDim.x) {
-        cx<T> v[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) v[r] = ld(j + r * ng);
-        dft_reg<T, 16>(v, inv);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) s[pidx<PAD>(16 * j + r)] = v[r];
-    }
-    __syncthreads();
+template <typename F, int... I>
+__device__ __forceinline__ void static_for_(F &&f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
 }
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F &&f) { static_for_(f, std::make_integer_sequence<int, N>{}); }
 
-template <typename T, int R, bool PAD, typename Store>
-__device__ __forceinline__ void row_last_pass(const cx<T> *s, int L, const cx<T> *__restrict__ tw, bool inv,
-                                              Store &&st) {
-    const int Ns = L / R;
-    for (int j = threadIdx.x; j < Ns; j += blockDim.x) {
-        cx<T> v[R];
+// Row transforms: one row of N' = 2^LOGNP points per workgroup, N'/16 threads (at
+// least a wave). The first pass (radix 16, no twiddles) takes input j + r N'/16 of
+// group j from ld(j, r), the last one (radix R, twiddle step j) hands output
+// j + r N'/R to st(j, r, value); r is a compile-time constant in both, and both index
+// patterns run contiguously over j, so the global accesses coalesce and none of
+// them depends on a branch. The passes between are radix-16 Stockham passes in LDS. A pass's
+// twiddles are asked for before the barrier in front of it.
+// Bound by memory latency and, for large rows, bandwidth. With the loads inside the
+// crop's branches and one runtime-sized kernel for all N' the rows took, in us in FP32, forwards
+// (with the clearing of the output grid) and backwards at N' = 256: 7.8 and 9.2,
+// now 4.0 and 3.8; at 2048: 16.5 and 12.0, now 12.9 and 8.1; at 8192: 239 and 119,
+// now 168 and 89; FP64 at 512: 12.1 and 9.6, now 6.1 and 5.5.
+// SPELL: with the products' roundings spelled out (mulr).
+template <typename T, int LOGNP, bool SPELL = false>
+struct RowFft {
+    static constexpr int NP = 1 << LOGNP, NT = NP / 16 < 64 ? 64 : NP / 16;
+    static constexpr int MID = (LOGNP - 5) / 4, R = 1 << (LOGNP - 4 - 4 * MID);
+    static constexpr size_t LDS = sizeof(cx<T>) * (size_t)(NP + NP / 32);
+
+    // LDS element of point i, padded by one element per 32 against bank conflicts
+    static __device__ __forceinline__ int at(int i) { return i + (i >> 5); }
+
+    // Twiddles of group j's radix-RR pass with Ns finished points: W^(step r), r = 1 .. RR - 1.
+    template <int RR>
+    static __device__ __forceinline__ void fetch(cx<T> *w, const cx<T> *__restrict__ tw, int step) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) v[r] = s[pidx<PAD>(j + r * Ns)];
-        if (j != 0) {
+        for (int r = 1; r < RR; ++r) w[r] = tw[step * r];
+    }
+    template <int RR, bool LAST>
+    static __device__ __forceinline__ void twiddle(cx<T> *v, const cx<T> *w0, bool any, bool inv) {
+        if (!any) return;
 #pragma unroll
-            for (int r = 1; r < R; ++r) {
-                cx<T> w = tw[j * r];
-                if (inv) w.y = -w.y;
-                v[r] = v[r] * w;
-            }
+        for (int r = 1; r < RR; ++r) {
+            cx<T> w = w0[r];
+            if (inv) w.y = -w.y;
+            v[r] = SPELL ? mulr<false, !LAST>(v[r], w) : v[r] * w;
         }
-        dft_reg<T, R>(v, inv);
-#pragma unroll
-        for (int r = 0; r < R; ++r) st(j + r * Ns, v[r]);
     }
-}
 
-// Whole row, logL >= 5: the first pass, radix-16 LDS passes, the last pass.
-template <typename T, bool PAD, typename Load, typename Store>
-__device__ __forceinline__ void row_fft(cx<T> *s, int logL, const cx<T> *__restrict__ tw, bool inv, Load &&ld,
-                                        Store &&st) {
-    const int L = 1 << logL;
-    row_first_pass<T, PAD>(s, L, inv, ld);
-    int Ns = 16, rem = logL - 4;
-    while (rem > 4) {
-        stockham_pass<T, 16, PAD>(s, L, Ns, tw, inv);
-        Ns <<= 4;
-        rem -= 4;
+    template <typename Load, typename Store>
+    static __device__ __forceinline__ void run(cx<T> *s, const cx<T> *__restrict__ tw, bool inv, Load &&ld, Store &&st) {
+        constexpr int NG = NP / 16, G = 16 / R, NL = NP / R;
+        const int tid = threadIdx.x;
+        const bool live = NT == NG || tid < NG;
+        cx<T> v[16], w[16];
+        if (live) {
+            static_for<16>([&](auto r) { v[r] = ld(tid, r); });
+            dft_reg<T, 16, SPELL ? MUL_FIRST : MUL_ANY>(v, inv);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[at(16 * tid + r)] = v[r];
+        }
+        static_for<MID>([&](auto m) {
+            constexpr int Ns = 16 << (4 * decltype(m)::value);
+            const int jm = tid & (Ns - 1);
+            if (live) fetch<16>(w, tw, jm * (NP / (Ns * 16)));
+            __syncthreads();
+            if (live) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) v[r] = s[at(tid + r * NG)];
+            }
+            __syncthreads();
+            if (live) {
+                twiddle<16, false>(v, w, jm != 0, inv);
+                dft_reg<T, 16, SPELL ? MUL_MID : MUL_ANY>(v, inv);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) s[at((tid - jm) * 16 + jm + r * Ns)] = v[r];
+            }
+        });
+#pragma unroll
+        for (int i = 0; i < G; ++i)
+            if (G * NT == NL || tid + i * NT < NL) fetch<R>(w + i * R, tw, tid + i * NT);
+        __syncthreads();
+        static_for<G>([&](auto i) {
+            const int j = tid + decltype(i)::value * NT;
+            if (G * NT != NL && j >= NL) return;
+            cx<T> *u = v + decltype(i)::value * R;
+#pragma unroll
+            for (int r = 0; r < R; ++r) u[r] = s[at(j + r * NL)];
+            twiddle<R, true>(u, w + decltype(i)::value * R, j != 0, inv);
+            dft_reg<T, R, SPELL ? MUL_LAST : MUL_ANY>(u, inv);
+            static_for<R>([&](auto r) { st(j, r, u[decltype(r)::value]); });
+        });
     }
-    switch (rem) {
-        case 4: row_last_pass<T, 16, PAD>(s, L, tw, inv, st); break;
-        case 3: row_last_pass<T, 8, PAD>(s, L, tw, inv, st); break;
-        case 2: row_last_pass<T, 4, PAD>(s, L, tw, inv, st); break;
-        default: row_last_pass<T, 2, PAD>(s, L, tw, inv, st); break;
-    }
-}
+};
+
+// The kernels of image side N'/2: pixel column ix = (gx + N/2) mod N' of grid column gx
+// = j + r N'/16 lies in the image for r < 4 and r >= 12.
 
 // Zero the output grid, the work counter and the partial sums, spread over the launch.
 template <typename T>
@@ -218,29 +218,32 @@ __global__ void k_clear(Clear<T> z) {
 // Z then the row DFT of image row iy (blockIdx.x), written to row (iy - N/2) & rowmask
 // (N' - 1: the grid row; N - 1: the N rows packed).
 // With a w-stack's phase screen (chirp != NULL) the padded image is x c_s.
-template <typename T, bool PAD>
-__global__ void __launch_bounds__(512) k_zpad_rowfft(const T *__restrict__ x, cx<T> *__restrict__ grid, const T *__restrict__ icorr,
-                              const cx<T> *__restrict__ tw, int N, int logNp, const cx<T> *__restrict__ chirp,
-                              int rowmask, Clear<T> z) {
+template <typename T, int LOGNP, bool CHIRP>
+__global__ void __launch_bounds__((RowFft<T, LOGNP>::NT))
+k_zpad_rowfft(const T *__restrict__ x, cx<T> *__restrict__ grid, const T *__restrict__ icorr,
+              const cx<T> *__restrict__ tw, const cx<T> *__restrict__ chirp, int rowmask, Clear<T> z) {
+    using F = RowFft<T, LOGNP, true>;
     extern __shared__ unsigned char smem_raw[];
-    cx<T> *s = reinterpret_cast<cx<T> *>(smem_raw);
-    const int Np = 1 << logNp;
+    constexpr int Np = F::NP, N = Np / 2;
     const int iy = blockIdx.x;
     const T cy = icorr[iy];
     const T *xr = x + (size_t)iy * N;
-    const cx<T> *chr = chirp ? chirp + (size_t)iy * N : nullptr;
-    auto ld = [&](int gx) -> cx<T> {
-        const int ix = (gx + N / 2) & (Np - 1);
-        if (ix >= N) return mk<T>((T)0, (T)0);
-        const T a = xr[ix] * icorr[ix] * cy;
-        if (chr) {
-            const cx<T> ch = chr[ix];
-            return mk<T>(a * ch.x, a * ch.y);
-        }
-        return mk<T>(a, (T)0);
-    };
+    const cx<T> *chr = CHIRP ? chirp + (size_t)iy * N : nullptr;
     cx<T> *row = grid + (size_t)((iy - N / 2) & rowmask) * Np;
-    row_fft<T, PAD>(s, logNp, tw, false, ld, [&](int k, cx<T> v) { row[k] = v; });
+    F::run(reinterpret_cast<cx<T> *>(smem_raw), tw, false,
+           [&](int j, auto r) -> cx<T> {
+               if constexpr (r >= 4 && r < 12) return mk<T>((T)0, (T)0);
+               const int ix = (j + r * (Np / 16) + N / 2) & (Np - 1);
+               const T a = xr[ix] * icorr[ix] * cy;
+               if (!CHIRP) {
+                   T zero = 0;              // opaque: products that the compiler knows to be
+                   asm("" : "+v"(zero));    // real would be contracted into the next butterflies
+                   return mk<T>(a, zero);
+               }
+               const cx<T> ch = chr[ix];
+               return mk<T>(a * ch.x, a * ch.y);
+           },
+           [&](int j, auto r, cx<T> v) { row[j + r * (Np / F::R)] = v; });
     clear_share<T>(z);
 }
 
@@ -248,31 +251,31 @@ __global__ void __launch_bounds__(512) k_zpad_rowfft(const T *__restrict__ x, cx
 // out[iy][ix] = Re{row[(ix - N/2) mod N']} / (kappa_hat_x kappa_hat_y). With a
 // w-stack's phase screen the value is Re{conj(c_s) row[...]} (Z_s^dagger), added
 // to out when accumulate != 0 (the sum over stacks).
-template <typename T, bool PAD>
-__global__ void __launch_bounds__(512) k_irowfft_crop(const cx<T> *__restrict__ grid, T *__restrict__ out, const T *__restrict__ icorr,
-                               const cx<T> *__restrict__ tw, int N, int logNp, const cx<T> *__restrict__ chirp,
-                               int accumulate) {
+template <typename T, int LOGNP, bool CHIRP>
+__global__ void __launch_bounds__((RowFft<T, LOGNP>::NT))
+k_irowfft_crop(const cx<T> *__restrict__ grid, T *__restrict__ out, const T *__restrict__ icorr,
+               const cx<T> *__restrict__ tw, const cx<T> *__restrict__ chirp, int accumulate) {
+    using F = RowFft<T, LOGNP>;
     extern __shared__ unsigned char smem_raw[];
-    cx<T> *s = reinterpret_cast<cx<T> *>(smem_raw);
-    const int Np = 1 << logNp;
+    constexpr int Np = F::NP, N = Np / 2;
     const int iy = blockIdx.x;
     const cx<T> *row = grid + (size_t)((iy - N / 2) & (Np - 1)) * Np;
     const T cy = icorr[iy];
     T *orow = out + (size_t)iy * N;
-    const cx<T> *chr = chirp ? chirp + (size_t)iy * N : nullptr;
-    auto st = [&](int gx, cx<T> v) {
-        const int ix = (gx + N / 2) & (Np - 1);   // the crop: image column ix < N
-        if (ix >= N) return;
-        T re = v.x;
-        if (chr) {
-            const cx<T> ch = chr[ix];
-            re = v.x * ch.x + v.y * ch.y;
-        }
-        const T val = re * icorr[ix] * cy;
-        if (accumulate) orow[ix] += val;
-        else orow[ix] = val;
-    };
-    row_fft<T, PAD>(s, logNp, tw, true, [&](int k) { return row[k]; }, st);
+    const cx<T> *chr = CHIRP ? chirp + (size_t)iy * N : nullptr;
+    F::run(reinterpret_cast<cx<T> *>(smem_raw), tw, true, [&](int j, auto r) { return row[j + r * (Np / 16)]; },
+           [&](int j, auto r, cx<T> v) {
+               const int ix = (j + r * (Np / F::R) + N / 2) & (Np - 1);   // the crop: image column ix < N
+               if (ix >= N) return;
+               T re = v.x;
+               if (CHIRP) {
+                   const cx<T> ch = chr[ix];
+                   re = v.x * ch.x + v.y * ch.y;
+               }
+               const T val = re * icorr[ix] * cy;
+               if (accumulate) orow[ix] += val;
+               else orow[ix] = val;
+           });
 }
 
 // ---------------------------------------------------------------------------
@@ -287,13 +290,6 @@ __global__ void __launch_bounds__(512) k_irowfft_crop(const cx<T> *__restrict__ 
 // workgroup; 8 columns measured 18, 11.5 and 5, and a launch for each of the two
 // transforms with the grid in between 49, 29 and 18.
 // ---------------------------------------------------------------------------
-template <typename F, int... I>
-__device__ __forceinline__ void static_for_(F &&f, std::integer_sequence<int, I...>) {
-    (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F &&f) { static_for_(f, std::make_integer_sequence<int, N>{}); }
-
 template <typename T, int LOGNP>
 struct FullCol {
     static constexpr int NP = 1 << LOGNP, LOG1 = full_log_n1(LOGNP), N1 = 1 << LOG1, N2 = NP >> LOG1;
@@ -322,7 +318,7 @@ struct FullCol {
         for (int r = 1; r < R; ++r) {
             cx<T> w = tw[step * r];
             if (inv) w.y = -w.y;
-            v[r] = mulxy(v[r], w);
+            v[r] = mulr<false, true>(v[r], w);
         }
     }
 };
@@ -351,12 +347,12 @@ k_colfft(const cx<T> *in, cx<T> *out, const cx<T> *__restrict__ tw, int N, int b
         for (int r = 0; r < R; ++r) {
             cx<T> w = tw[n2 * (k0 + dk * r)];
             if (inv) w.y = -w.y;
-            u[r] = mulyx(u[r], w);
+            u[r] = mulr<false, false>(u[r], w);
         }
     };
     C::template groups<RA>(v, [&](int q, int col, cx<T> *u) {
         const int j = q & (N1 / RA - 1), n2 = q / (N1 / RA);
-        dft_reg<T, RA, true>(u, inv);
+        dft_reg<T, RA, MUL_COLS>(u, inv);
         if (RA2 == 1) four_step(u, RA, n2, 0, 1);
 #pragma unroll
         for (int r = 0; r < RA; ++r) s[C::at(n2 * N1 + RA * j + r, col)] = u[r];
@@ -368,7 +364,7 @@ k_colfft(const cx<T> *in, cx<T> *out, const cx<T> *__restrict__ tw, int N, int b
 #pragma unroll
             for (int r = 0; r < RA2; ++r) u[r] = s[C::at(n2 * N1 + j + 16 * r, col)];
             C::template twiddle<RA2>(u, tw, j * N2, inv);
-            dft_reg<T, RA2, true>(u, inv);
+            dft_reg<T, RA2, MUL_COLS>(u, inv);
             four_step(u, RA2, n2, j, 16);
 #pragma unroll
             for (int r = 0; r < RA2; ++r) s[C::at(n2 * N1 + j + 16 * r, col)] = u[r];
@@ -383,7 +379,7 @@ k_colfft(const cx<T> *in, cx<T> *out, const cx<T> *__restrict__ tw, int N, int b
         const int k1 = q & (N1 - 1), j = q >> C::LOG1;
 #pragma unroll
         for (int r = 0; r < RB; ++r) u[r] = s[C::at((j + r * (N2 / RB)) * N1 + k1, col)];
-        dft_reg<T, RB, true>(u, inv);
+        dft_reg<T, RB, MUL_COLS>(u, inv);
         if (RB2 == 1) {
 #pragma unroll
             for (int r = 0; r < RB; ++r) store(k1, r, col, u[r]);
@@ -402,7 +398,7 @@ k_colfft(const cx<T> *in, cx<T> *out, const cx<T> *__restrict__ tw, int N, int b
 #pragma unroll
             for (int r = 0; r < RB2; ++r) u[r] = s[C::at((j + 16 * r) * N1 + k1, col)];
             C::template twiddle<RB2>(u, tw, j * N1, inv);
-            dft_reg<T, RB2, true>(u, inv);
+            dft_reg<T, RB2, MUL_COLS>(u, inv);
 #pragma unroll
             for (int r = 0; r < RB2; ++r) store(k1, j + 16 * r, col, u[r]);
         });
@@ -565,38 +561,39 @@ __global__ void __launch_bounds__(64) k_colpass_b_reg(const cx<T> *in, cx<T> *ou
 // One workgroup holds CW adjacent whole columns in LDS: one read of the
 // scratch per parity and one write of the grid forward, one read of the grid
 // and one write of the scratch back. Bound by memory latency and bandwidth; the
-// adjoint's columns and rows take 59 + 26 us at N' = 4096 in FP32 (whole plane,
-// two column passes: about 150), 189 + 119 at 8192 (about 680), and the FP64
-// forward ones 13 + 19 at 2048 (about 130).
+// adjoint's columns and rows take 59 + 21 us at N' = 4096 in FP32 (whole plane,
+// two column passes: about 150), 189 + 89 at 8192 (about 680).
 // ---------------------------------------------------------------------------
 inline __device__ __host__ int scratch_pitch(int N) { return N >= 64 ? N + 16 : N; }
 
 // Image rows 2 b and 2 b + 1 -> rows of the scratch (row index n mod N).
-template <typename T, bool PAD>
-__global__ void __launch_bounds__(512) k_half_rows(const T *__restrict__ x, cx<T> *__restrict__ scr, const T *__restrict__ icorr,
-                            const cx<T> *__restrict__ tw, int N, int logNp, Clear<T> z) {
+template <typename T, int LOGNP>
+__global__ void __launch_bounds__((RowFft<T, LOGNP>::NT))
+k_half_rows(const T *__restrict__ x, cx<T> *__restrict__ scr, const T *__restrict__ icorr,
+            const cx<T> *__restrict__ tw, Clear<T> z) {
+    using F = RowFft<T, LOGNP>;
     extern __shared__ unsigned char smem_raw[];
     cx<T> *s = reinterpret_cast<cx<T> *>(smem_raw);
-    const int Np = 1 << logNp, iy = 2 * blockIdx.x;
+    constexpr int Np = F::NP, N = Np / 2;
+    const int iy = 2 * blockIdx.x;
     const T ca = icorr[iy], cb = icorr[iy + 1];
     const T *xa = x + (size_t)iy * N, *xb = xa + N;
-    row_first_pass<T, PAD>(s, Np, false, [&](int gx) -> cx<T> {
-        const int ix = (gx + N / 2) & (Np - 1);
-        if (ix >= N) return mk<T>((T)0, (T)0);
-        const T c = icorr[ix];
-        return mk<T>(xa[ix] * c * ca, xb[ix] * c * cb);
-    });
-    int Ns = 16, rem = logNp - 4;
-    while (rem > 0) {
-        if (rem >= 4) { stockham_pass<T, 16, PAD>(s, Np, Ns, tw, false); Ns <<= 4; rem -= 4; }
-        else if (rem == 3) { stockham_pass<T, 8, PAD>(s, Np, Ns, tw, false); Ns <<= 3; rem -= 3; }
-        else if (rem == 2) { stockham_pass<T, 4, PAD>(s, Np, Ns, tw, false); Ns <<= 2; rem -= 2; }
-        else { stockham_pass<T, 2, PAD>(s, Np, Ns, tw, false); Ns <<= 1; rem -= 1; }
-    }
+    F::run(s, tw, false,
+           [&](int j, auto r) -> cx<T> {
+               if constexpr (r >= 4 && r < 12) return mk<T>((T)0, (T)0);
+               const int ix = (j + r * (Np / 16) + N / 2) & (Np - 1);
+               const T c = icorr[ix];
+               return mk<T>(xa[ix] * c * ca, xb[ix] * c * cb);
+           },
+           [&](int j, auto r, cx<T> v) { s[F::at(j + r * (Np / F::R))] = v; });   // where the group read its inputs
+    __syncthreads();
     cx<T> *ra = scr + (size_t)((iy - N / 2) & (N - 1)) * scratch_pitch(N);
     cx<T> *rb = ra + scratch_pitch(N);   // n and n + 1 are neighbours: n is even
-    for (int k = threadIdx.x; k < N; k += blockDim.x) {
-        const cx<T> p = s[pidx<PAD>(k)], q = s[pidx<PAD>(k == 0 ? N : Np - k)];
+#pragma unroll
+    for (int i = 0; i < (N + F::NT - 1) / F::NT; ++i) {
+        const int k = threadIdx.x + i * F::NT;
+        if (N % F::NT != 0 && k >= N) break;
+        const cx<T> p = s[F::at(k)], q = s[F::at(k == 0 ? N : Np - k)];
         if (k == 0) {
             ra[0] = mk<T>(p.x, q.x);
             rb[0] = mk<T>(p.y, q.y);
@@ -610,34 +607,40 @@ __global__ void __launch_bounds__(512) k_half_rows(const T *__restrict__ x, cx<T
 
 // Rows of the scratch -> image rows 2 b and 2 b + 1: the real inverse row
 // transforms of both half spectra as one complex one, cropped and corrected.
-template <typename T, bool PAD>
-__global__ void __launch_bounds__(512) k_half_irows(const cx<T> *__restrict__ scr, T *__restrict__ out, const T *__restrict__ icorr,
-                             const cx<T> *__restrict__ tw, int N, int logNp) {
+template <typename T, int LOGNP>
+__global__ void __launch_bounds__((RowFft<T, LOGNP>::NT))
+k_half_irows(const cx<T> *__restrict__ scr, T *__restrict__ out, const T *__restrict__ icorr,
+             const cx<T> *__restrict__ tw) {
+    using F = RowFft<T, LOGNP>;
     extern __shared__ unsigned char smem_raw[];
-    cx<T> *s = reinterpret_cast<cx<T> *>(smem_raw);
-    const int Np = 1 << logNp, iy = 2 * blockIdx.x;
+    constexpr int Np = F::NP, N = Np / 2;
+    const int iy = 2 * blockIdx.x;
     const cx<T> *ra = scr + (size_t)((iy - N / 2) & (N - 1)) * scratch_pitch(N);
     const cx<T> *rb = ra + scratch_pitch(N);
     const T ca = icorr[iy], cb = icorr[iy + 1];
     T *oa = out + (size_t)iy * N, *ob = oa + N;
-    auto ld = [&](int k) -> cx<T> {
-        if (k == 0) return mk<T>(ra[0].x, rb[0].x);
-        if (k == N) return mk<T>(ra[0].y, rb[0].y);
-        const bool up = k > N;
-        cx<T> a = ra[up ? Np - k : k], b = rb[up ? Np - k : k];
-        if (up) {
-            a.y = -a.y;
-            b.y = -b.y;
-        }
-        return mk<T>((T)0.5 * (a.x - b.y), (T)0.5 * (a.y + b.x));
-    };
-    row_fft<T, PAD>(s, logNp, tw, true, ld, [&](int gx, cx<T> v) {
-        const int ix = (gx + N / 2) & (Np - 1);
-        if (ix >= N) return;
-        const T c = icorr[ix];
-        oa[ix] = v.x * c * ca;
-        ob[ix] = v.y * c * cb;
-    });
+    F::run(reinterpret_cast<cx<T> *>(smem_raw), tw, true,
+           [&](int j, auto r) -> cx<T> {
+               // spectrum element k from element k or, conjugated, N' - k; the real k = 0
+               // and k = N share element 0
+               const int k = j + r * (Np / 16), e = r < 8 ? k : (Np - k) & (N - 1);
+               cx<T> a = ra[e], b = rb[e];
+               if (r >= 8) {
+                   a.y = -a.y;
+                   b.y = -b.y;
+               }
+               const cx<T> v = mk<T>((T)0.5 * (a.x - b.y), (T)0.5 * (a.y + b.x));
+               if (r == 0) return j == 0 ? mk<T>(a.x, b.x) : v;
+               if (r == 8) return j == 0 ? mk<T>(-a.y, -b.y) : v;
+               return v;
+           },
+           [&](int j, auto r, cx<T> v) {
+               const int ix = (j + r * (Np / F::R) + N / 2) & (Np - 1);
+               const T c = icorr[ix & (N - 1)];
+               if (ix >= N) return;
+               oa[ix] = v.x * c * ca;
+               ob[ix] = v.y * c * cb;
+           });
 }
 
 // base[i] through a 32-bit byte offset (one address register instead of two).
@@ -866,7 +869,6 @@ void half_cols(ri_ctx *c, Prec<T> &p, const cx<T> *in, cx<T> *out, bool inv, hip
 template <typename T, int L>
 constexpr int lanes_per_column() { return (L * (int)sizeof(cx<T>)) / 512 < 1 ? 1 : (L * (int)sizeof(cx<T>)) / 512; }
 
-int threads_for(int L) { return L / 16 < 64 ? 64 : L / 16; }
 
 // Column transforms of grid_io (scratch) into grid_out; grid_out == grid_io
 // leaves the second pass in place (permuted rows). band: the N packed band rows
@@ -914,28 +916,41 @@ void colfft(ri_ctx *c, cx<T> *grid_io, cx<T> *grid_out, const cx<T> *tw, bool in
 
 }  // namespace
 
-// Row transforms pad LDS by one element per 32 (fewer bank conflicts) when it fits.
-template <typename T>
-bool row_pad(ri_ctx *c) { return sizeof(cx<T>) * (size_t)(c->Np + c->Np / 32) <= (size_t)c->dev.lds_per_block; }
-
-template <typename T>
-size_t row_lds(ri_ctx *c) { return sizeof(cx<T>) * (size_t)(row_pad<T>(c) ? c->Np + c->Np / 32 : c->Np); }
+// f(integral_constant<int, log2 N'>) for the context's N'.
+template <typename F>
+void with_log(int logNp, F &&f) {
+    switch (logNp) {
+        case 5: return f(std::integral_constant<int, 5>{});
+        case 6: return f(std::integral_constant<int, 6>{});
+        case 7: return f(std::integral_constant<int, 7>{});
+        case 8: return f(std::integral_constant<int, 8>{});
+        case 9: return f(std::integral_constant<int, 9>{});
+        case 10: return f(std::integral_constant<int, 10>{});
+        case 11: return f(std::integral_constant<int, 11>{});
+        case 12: return f(std::integral_constant<int, 12>{});
+        case 13: return f(std::integral_constant<int, 13>{});
+        default: throw Error(RI_EUNSUPPORTED, "image side outside 16 .. 4096");
+    }
+}
 
 // Z and the row FFTs of x into dst (rows as k_zpad_rowfft places them).
 template <typename T>
 void launch_zpad_rows(ri_ctx *c, Prec<T> &p, const T *x, cx<T> *dst, const cx<T> *chirp, int rowmask,
                       const Clear<T> &z, hipStream_t s) {
-    if (row_pad<T>(c))
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_zpad_rowfft<T, true>), dim3(c->N), dim3(threads_for(c->Np)),
-                           row_lds<T>(c), s, x, dst, p.icorr, p.tw, c->N, c->logNp, chirp, rowmask, z);
-    else
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_zpad_rowfft<T, false>), dim3(c->N), dim3(threads_for(c->Np)),
-                           row_lds<T>(c), s, x, dst, p.icorr, p.tw, c->N, c->logNp, chirp, rowmask, z);
+    with_log(c->logNp, [&](auto LOG) {
+        using F = RowFft<T, decltype(LOG)::value>;
+        if (chirp)
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_zpad_rowfft<T, decltype(LOG)::value, true>), dim3(c->N), dim3(F::NT),
+                               F::LDS, s, x, dst, p.icorr, p.tw, chirp, rowmask, z);
+        else
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_zpad_rowfft<T, decltype(LOG)::value, false>), dim3(c->N), dim3(F::NT),
+                               F::LDS, s, x, dst, p.icorr, p.tw, chirp, rowmask, z);
+    });
 }
 
 template <typename T>
 void require_row_fits(ri_ctx *c) {
-    if (sizeof(cx<T>) * (size_t)c->Np > (size_t)c->dev.lds_per_block)
+    if (sizeof(cx<T>) * (size_t)(c->Np + c->Np / 32) > (size_t)c->dev.lds_per_block)
         throw Error(RI_EUNSUPPORTED, "grid row does not fit the workgroup LDS");
 }
 
@@ -963,12 +978,15 @@ void adj_fft_crop(ri_ctx *c, Prec<T> &p, T *x, hipStream_t s) {
     for (int st = 0; st < c->P; ++st) {
         const cx<T> *ch = c->P > 1 ? p.chirp + (size_t)st * c->N * c->N : nullptr;
         colfft<T>(c, p.gridA + (size_t)st * Np * Np, p.gridB, p.tw, true, false, true, s);
-        if (row_pad<T>(c))
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_irowfft_crop<T, true>), dim3(c->N), dim3(threads_for(Np)),
-                               row_lds<T>(c), s, p.gridB, x, p.icorr, p.tw, c->N, c->logNp, ch, st > 0 ? 1 : 0);
-        else
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_irowfft_crop<T, false>), dim3(c->N), dim3(threads_for(Np)),
-                               row_lds<T>(c), s, p.gridB, x, p.icorr, p.tw, c->N, c->logNp, ch, st > 0 ? 1 : 0);
+        with_log(c->logNp, [&](auto LOG) {
+            using F = RowFft<T, decltype(LOG)::value>;
+            if (ch)
+                hipLaunchKernelGGL(HIP_KERNEL_NAME(k_irowfft_crop<T, decltype(LOG)::value, true>), dim3(c->N),
+                                   dim3(F::NT), F::LDS, s, p.gridB, x, p.icorr, p.tw, ch, st > 0 ? 1 : 0);
+            else
+                hipLaunchKernelGGL(HIP_KERNEL_NAME(k_irowfft_crop<T, decltype(LOG)::value, false>), dim3(c->N),
+                                   dim3(F::NT), F::LDS, s, p.gridB, x, p.icorr, p.tw, ch, st > 0 ? 1 : 0);
+        });
     }
 }
 
@@ -999,12 +1017,11 @@ void fwd_half_fft(ri_ctx *c, Prec<T> &p, const T *x, const Clear<T> &z, hipStrea
     const int N = c->N, Np = c->Np;
     ProfScope prof(c, PROF_FFT, s);
     cx<T> *scr = half_scratch<T>(c, p);
-    if (row_pad<T>(c))
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_half_rows<T, true>), dim3(N / 2), dim3(threads_for(Np)), row_lds<T>(c),
-                           s, x, scr, p.icorr, p.tw, N, c->logNp, z);
-    else
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_half_rows<T, false>), dim3(N / 2), dim3(threads_for(Np)),
-                           row_lds<T>(c), s, x, scr, p.icorr, p.tw, N, c->logNp, z);
+    with_log(c->logNp, [&](auto LOG) {
+        using F = RowFft<T, decltype(LOG)::value>;
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_half_rows<T, decltype(LOG)::value>), dim3(c->N / 2), dim3(F::NT), F::LDS, s,
+                           x, scr, p.icorr, p.tw, z);
+    });
     half_cols<T>(c, p, scr, p.gridB, false, s);
 }
 
@@ -1014,12 +1031,11 @@ void adj_half_fft(ri_ctx *c, Prec<T> &p, T *x, hipStream_t s) {
     ProfScope prof(c, PROF_FFT, s);
     cx<T> *scr = half_scratch<T>(c, p);
     half_cols<T>(c, p, p.gridA, scr, true, s);
-    if (row_pad<T>(c))
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_half_irows<T, true>), dim3(N / 2), dim3(threads_for(Np)),
-                           row_lds<T>(c), s, scr, x, p.icorr, p.tw, N, c->logNp);
-    else
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_half_irows<T, false>), dim3(N / 2), dim3(threads_for(Np)),
-                           row_lds<T>(c), s, scr, x, p.icorr, p.tw, N, c->logNp);
+    with_log(c->logNp, [&](auto LOG) {
+        using F = RowFft<T, decltype(LOG)::value>;
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_half_irows<T, decltype(LOG)::value>), dim3(c->N / 2), dim3(F::NT), F::LDS, s,
+                           scr, x, p.icorr, p.tw);
+    });
 }
 
 // Whole plane of one real image into gridB, all passes in place there (rows
