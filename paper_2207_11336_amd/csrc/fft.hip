@@ -323,24 +323,16 @@ struct FullCol {
     }
 };
 
-template <typename T, int LOGNP>
-__global__ void __launch_bounds__((FullCol<T, LOGNP>::NT))
-k_colfft(const cx<T> *in, cx<T> *out, const cx<T> *__restrict__ tw, int N, int band_in, int band_out, int inv_) {
+// The stripe's columns: point row of column col from ld(row, col), frequency k1 + N1 k2 to st(k1, k2, col, value).
+template <typename T, int LOGNP, typename Load, typename Store>
+__device__ __forceinline__ void full_cols(cx<T> *s, const cx<T> *__restrict__ tw, bool inv, Load &&ld, Store &&st) {
     using C = FullCol<T, LOGNP>;
-    extern __shared__ unsigned char smem_raw[];
-    cx<T> *s = reinterpret_cast<cx<T> *>(smem_raw);
-    constexpr int NP = C::NP, N1 = C::N1, N2 = C::N2, RA = C::RA, RA2 = C::RA2, RB = C::RB, RB2 = C::RB2;
-    const bool inv = inv_ != 0, permuted = out == in;
-    const int nb = gridDim.x, b = (nb & 7) ? (int)blockIdx.x : (int)(blockIdx.x & 7) * (nb >> 3) + (blockIdx.x >> 3);
-    const int x0 = b * C::CW;
+    constexpr int N1 = C::N1, N2 = C::N2, RA = C::RA, RA2 = C::RA2, RB = C::RB, RB2 = C::RB2;
     cx<T> v[16];
     C::template groups<RA>(v, [&](int q, int col, cx<T> *u) {
         const int j = q & (N1 / RA - 1), n2 = q / (N1 / RA);
 #pragma unroll
-        for (int r = 0; r < RA; ++r) {
-            const int row = n2 + N2 * (j + r * (N1 / RA));
-            u[r] = (!band_in || in_band(row, N, NP)) ? in[(size_t)row * NP + x0 + col] : mk<T>((T)0, (T)0);
-        }
+        for (int r = 0; r < RA; ++r) u[r] = ld(n2 + N2 * (j + r * (N1 / RA)), col);
     });
     auto four_step = [&](cx<T> *u, int R, int n2, int k0, int dk) {
 #pragma unroll
@@ -371,10 +363,6 @@ k_colfft(const cx<T> *in, cx<T> *out, const cx<T> *__restrict__ tw, int N, int b
         });
         __syncthreads();
     }
-    auto store = [&](int k1, int k2, int col, cx<T> val) {
-        const int k = k1 + N1 * k2, row = permuted ? N2 * k1 + k2 : k;
-        if (!band_out || in_band(row, N, NP)) out[(size_t)row * NP + x0 + col] = val;
-    };
     C::template groups<RB>(v, [&](int q, int col, cx<T> *u) {
         const int k1 = q & (N1 - 1), j = q >> C::LOG1;
 #pragma unroll
@@ -382,7 +370,7 @@ k_colfft(const cx<T> *in, cx<T> *out, const cx<T> *__restrict__ tw, int N, int b
         dft_reg<T, RB, MUL_COLS>(u, inv);
         if (RB2 == 1) {
 #pragma unroll
-            for (int r = 0; r < RB; ++r) store(k1, r, col, u[r]);
+            for (int r = 0; r < RB; ++r) st(k1, r, col, u[r]);
         }
     });
     if constexpr (RB2 > 1) {
@@ -400,9 +388,34 @@ k_colfft(const cx<T> *in, cx<T> *out, const cx<T> *__restrict__ tw, int N, int b
             C::template twiddle<RB2>(u, tw, j * N1, inv);
             dft_reg<T, RB2, MUL_COLS>(u, inv);
 #pragma unroll
-            for (int r = 0; r < RB2; ++r) store(k1, j + 16 * r, col, u[r]);
+            for (int r = 0; r < RB2; ++r) st(k1, j + 16 * r, col, u[r]);
         });
     }
+}
+
+// First column of the workgroup's stripe: neighbouring stripes on one XCD.
+__device__ __forceinline__ int stripe_x0(int cw) {
+    const int nb = gridDim.x;
+    return ((nb & 7) ? (int)blockIdx.x : (int)(blockIdx.x & 7) * (nb >> 3) + (blockIdx.x >> 3)) * cw;
+}
+
+template <typename T, int LOGNP>
+__global__ void __launch_bounds__((FullCol<T, LOGNP>::NT))
+k_colfft(const cx<T> *in, cx<T> *out, const cx<T> *__restrict__ tw, int N, int band_in, int band_out, int inv) {
+    using C = FullCol<T, LOGNP>;
+    extern __shared__ unsigned char smem_raw[];
+    constexpr int NP = C::NP;
+    const bool permuted = out == in;
+    const int x0 = stripe_x0(C::CW);
+    full_cols<T, LOGNP>(
+        reinterpret_cast<cx<T> *>(smem_raw), tw, inv != 0,
+        [&](int row, int col) {
+            return (!band_in || in_band(row, N, NP)) ? in[(size_t)row * NP + x0 + col] : mk<T>((T)0, (T)0);
+        },
+        [&](int k1, int k2, int col, cx<T> val) {
+            const int k = k1 + C::N1 * k2, row = permuted ? C::N2 * k1 + k2 : k;
+            if (!band_out || in_band(row, N, NP)) out[(size_t)row * NP + x0 + col] = val;
+        });
 }
 
 // ---------------------------------------------------------------------------
@@ -657,14 +670,11 @@ __device__ __forceinline__ int fresh(int v) {
     return v;
 }
 
-// log2 of the columns per workgroup. FP32: 8 up to N = 512 (small images want
-// wide row segments: 8.9 against 11.1 us for the adjoint pass at N = 128), 4 above
-// (two workgroups per CU: 19 against 22.7 us at N = 1024, 59 against 61 at 2048,
-// 192 with 4 against 234 with 2 at 4096). FP64: 4 (10.2 against 15.8 us at
-// N = 256 and 22 + 13 against 21 + 17 us for both passes at 1024 with 2), and 2
-// at N = 4096, whose columns then fill 139 KB of LDS.
+// log2 of the columns per workgroup: 4 (FP32, N' = 4096: 59 us against 61 with 8; 8192: 192
+// against 234 with 2; FP64 forward at N = 256 and 1024: with 2 columns 15.8 against
+// 10.2 and 17 against 13 us), 2 in FP64 at N = 4096, whose columns then fill 139 KB of LDS.
 template <typename T>
-constexpr int half_log_cw(int logN) { return sizeof(T) == 4 ? (logN <= 9 ? 3 : 2) : (logN <= 11 ? 2 : 1); }
+constexpr int half_log_cw(int logN) { return sizeof(T) == 8 && logN > 11 ? 1 : 2; }
 template <typename T>
 constexpr int half_threads(int logN) {
     const int n = 1 << (logN + half_log_cw<T>(logN) - 4);
@@ -837,17 +847,60 @@ k_half_icols(const cx<T> *__restrict__ Y, cx<T> *__restrict__ scr, const cx<T> *
     });
 }
 
+// k_half_icols up to N' = 2048 by whole columns (full_cols): the N' / 16 threads of
+// a column do one transform where the two parities' N / 16 did two in turn. In us, FP32
+// at N' = 256, 1024 and 2048: 8.7 -> 6.4, 16.3 -> 10.4, 19.0 -> 14.1; FP64 at 512 and 2048:
+// 9.8 -> 9.0, 21.8 -> 19.5. Larger columns would leave one workgroup per CU.
+template <typename T, int LOGNP>
+__global__ void __launch_bounds__((FullCol<T, LOGNP>::NT))
+k_half_icols_full(const cx<T> *__restrict__ Y, cx<T> *__restrict__ scr, const cx<T> *__restrict__ tw, int pitch) {
+    using C = FullCol<T, LOGNP>;
+    extern __shared__ unsigned char smem_raw[];
+    constexpr int NP = C::NP, N = NP / 2;
+    cx<T> *s = reinterpret_cast<cx<T> *>(smem_raw);
+    const int x0 = stripe_x0(C::CW);
+    auto st = [&](int k1, int k2, int col, cx<T> v) {
+        const int n = k1 + C::N1 * k2;     // wanted: n in [-N/2, N/2) mod N'
+        if (in_band(n, N, NP)) at32(scr, (unsigned)((n & (N - 1)) * scratch_pitch(N) + x0 + col)) = v;
+    };
+    if (x0 != 0) {
+        full_cols<T, LOGNP>(s, tw, true, [&](int ky, int col) { return at32(Y, (unsigned)(ky * pitch + x0 + col)); }, st);
+    } else {
+        // every lane loads what column 0 needs: no load waits behind a branch
+        full_cols<T, LOGNP>(
+            s, tw, true,
+            [&](int ky, int col) {
+                const int km = (NP - ky) & (NP - 1);
+                const cx<T> a = at32(Y, (unsigned)(ky * pitch + col)), m = at32(Y, (unsigned)(km * pitch));
+                const cx<T> b = at32(Y, (unsigned)(ky * pitch + N)), bm = at32(Y, (unsigned)(km * pitch + N));
+                const cx<T> h0 = mk<T>((T)0.5 * (a.x + m.x), (T)0.5 * (a.y - m.y));
+                const cx<T> hn = mk<T>((T)0.5 * (b.x + bm.x), (T)0.5 * (b.y - bm.y));
+                return col == 0 ? mk<T>(h0.x - hn.y, h0.y + hn.x) : a;
+            },
+            st);
+    }
+}
+
 // The two column launches of image side N = 2^logN (16 .. 4096).
 template <typename T, int LOGN>
 void half_cols_launch(ri_ctx *c, Prec<T> &p, const cx<T> *in, cx<T> *out, bool inv, hipStream_t s) {
     using C = ColFft<T, LOGN>;
     const int stripes = C::N / C::CW, pitch = half_pitch(C::N);
-    if (inv)
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_half_icols<T, LOGN>), dim3(stripes), dim3(C::NT), C::LDS, s, in, out, p.tw,
-                           pitch);
-    else
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_half_cols<T, LOGN>), dim3(2 * stripes), dim3(C::NT), C::LDS, s, in, out,
-                           p.tw, pitch);
+    if constexpr (LOGN <= 10) {
+        using F = FullCol<T, LOGN + 1>;
+        if (inv)
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_half_icols_full<T, LOGN + 1>), dim3(C::N / F::CW), dim3(F::NT), F::LDS, s,
+                               in, out, p.tw, pitch);
+    } else {
+        if (inv)
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_half_icols<T, LOGN>), dim3(stripes), dim3(C::NT), C::LDS, s, in, out,
+                               p.tw, pitch);
+    }
+    if constexpr (std::is_same<T, double>::value) {   // FP32 images go forwards by the whole plane
+        if (!inv)
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_half_cols<T, LOGN>), dim3(2 * stripes), dim3(C::NT), C::LDS, s, in, out,
+                               p.tw, pitch);
+    }
 }
 
 template <typename T>
@@ -1057,11 +1110,12 @@ void operator_fft(ri_ctx *c, Prec<T> &p, bool folded, const T *x, const Clear<T>
     if (c->P > 1) {   // each stack's image is complex (its phase screen)
         fwd_zpad_fft<T>(c, p, x, s);
         clear<T>(z, s);
-    } else if (folded) {
-        fwd_half_fft<T>(c, p, x, z, s);
-    } else {
-        fwd_full_fft<T>(c, p, x, z, s);
+        return;
     }
+    if constexpr (std::is_same<T, double>::value) {
+        if (folded) return fwd_half_fft<T>(c, p, x, z, s);
+    }
+    fwd_full_fft<T>(c, p, x, z, s);
 }
 
 template <typename T>
