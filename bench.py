@@ -473,7 +473,7 @@ def run_pnp(args, R, synth, ctx, noise, x_true, L, tau40):
             "denoiser_roofline": {"bound": "mfma", "achieved": den_tfs, "peak": BF16_PEAK_TFS, "unit": "TFLOP/s",
                                   "frac": den_tfs / BF16_PEAK_TFS,
                                   "flops_per_application": cnn_flops(nf * tside * tside),
-                                  "kernels": "k_conv_in, 7 x k_conv64<0>, k_conv64<2>, k_conv_sum (one application)"},
+                                  "kernels": "k_conv_in, 7 x k_conv64<0>, k_conv64_proj, k_conv_sum (one application)"},
             "fne_norm_patches": fne_patches, "fne_norm_fixed_point": fne_fixed}
 
 
