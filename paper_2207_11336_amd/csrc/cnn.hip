@@ -891,14 +891,14 @@ __global__ void __launch_bounds__(512) k_dw64(const uint16_t *__restrict__ dpre,
 
 // Sum over rows r < nrows of part[r * stride + e] for the workgroup's E consecutive
 // elements: 1024 / E threads per element take every (1024 / E)-th row with
-// eight loads in flight, then the threads' sums meet in LDS (fixed order).
+// eight loads in flight, then the threads' sums meet in LDS (fixed order); summed in FP64.
 // Valid in the first E threads.
 template <int E>
 __device__ __forceinline__ float reduce_rows(const float *__restrict__ part, int nrows, int stride, int e, int count,
-                                             float (*red)[E]) {
+                                             double (*red)[E]) {
     constexpr int G = 1024 / E;
     const int grp = threadIdx.x / E, le = threadIdx.x % E;
-    float s8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    double s8[8] = {};
     if (e < count) {
         int r = grp;
         for (; r + 7 * G < nrows; r += 8 * G)
@@ -911,7 +911,7 @@ __device__ __forceinline__ float reduce_rows(const float *__restrict__ part, int
         __syncthreads();
         if (grp < h) red[grp][le] += red[grp + h][le];
     }
-    return red[0][le];
+    return (float)red[0][le];
 }
 
 // dW[o][c][t] and db[o] from the per-workgroup partials of k_dw64: 9 us for 256 rows
@@ -919,7 +919,7 @@ __device__ __forceinline__ float reduce_rows(const float *__restrict__ part, int
 __global__ void __launch_bounds__(1024) k_dw64_reduce(const float *__restrict__ part, int nwg, float *__restrict__ dW,
                                                       float *__restrict__ db) {
     constexpr int E = 64;
-    __shared__ float red[1024 / E][E];
+    __shared__ double red[1024 / E][E];
     const int e = blockIdx.x * E + threadIdx.x % E;
     const float s = reduce_rows<E>(part, nwg, DW_PART, e, DW_PART, red);
     if (threadIdx.x >= E) return;
@@ -990,7 +990,7 @@ __global__ void __launch_bounds__(256) k_dw_in(const float *__restrict__ z, cons
 __global__ void __launch_bounds__(1024) k_reduce_rows(const float *__restrict__ part, int nrows, int stride, int count,
                                                       float *__restrict__ out) {
     constexpr int E = 16;
-    __shared__ float red[1024 / E][E];
+    __shared__ double red[1024 / E][E];
     const int e = blockIdx.x * E + threadIdx.x % E;
     const float s = reduce_rows<E>(part, nrows, stride, e, count, red);
     if (threadIdx.x < E && e < count) out[e] = s;
