@@ -915,7 +915,8 @@ __device__ __forceinline__ float reduce_rows(const float *__restrict__ part, int
 }
 
 // dW[o][c][t] and db[o] from the per-workgroup partials of k_dw64: 9 us for 256 rows
-// (21 with one thread per element, which left most of the device idle).
+// with FP32 sums (21 with one thread per element, which left most of the device
+// idle); FP64 sums add about 3 us.
 __global__ void __launch_bounds__(1024) k_dw64_reduce(const float *__restrict__ part, int nwg, float *__restrict__ dW,
                                                       float *__restrict__ db) {
     constexpr int E = 64;
