@@ -280,7 +280,8 @@ ri_status ri_sara_reweight(ri_ctx *ctx, const void *x, double rho, ri_stream str
 /* The dictionary itself: coef = Psi^dagger x and x = Psi coef, coef dev
  * [9][N][N] (slot 0 the Dirac basis, slot p the Daubechies wavelet with p
  * vanishing moments in the usual pyramid layout: each level's low-low block in
- * the top-left corner, then its three detail blocks), both scaled by 1/3. */
+ * the top-left corner, then its three detail blocks), both scaled by 1/3. x may
+ * lie inside coef. */
 ri_status ri_sara_analysis(ri_ctx *ctx, const void *x, void *coef, ri_stream stream);
 ri_status ri_sara_synthesis(ri_ctx *ctx, const void *coef, void *x, ri_stream stream);
 

@@ -397,10 +397,10 @@ k_syn(T *v9, const T *__restrict__ low, T *__restrict__ out, const T *__restrict
 }
 
 // The finest level's sum over the bases where their planes were written one by
-// one, with the Dirac slot.
+// one, with the Dirac slot (x may be the first of the planes).
 template <typename T, int MODE>
-__global__ void __launch_bounds__(256) k_syn_sum(const T *__restrict__ planes, T *v9, const T *__restrict__ w9,
-                                                 const T *__restrict__ z, T *__restrict__ x, int64_t n, T scale, T thr) {
+__global__ void __launch_bounds__(256) k_syn_sum(const T *planes, T *v9, const T *__restrict__ w9,
+                                                 const T *__restrict__ z, T *x, int64_t n, T scale, T thr) {
     const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (p >= n) return;
     T sum = 0;
@@ -531,11 +531,28 @@ void dispatch_tile(ri_ctx *c, int n, bool finest, F &&launch) {
     else launch(integral_constant<int, 1>{}, no{}, no{});
 }
 
+// A caller may transform in place, the image lying inside the coefficients. Tiles
+// of one launch read what others of it write then, so such an image passes
+// through a work array.
+template <typename T>
+bool inside(const T *x, const T *coef9, int N) {
+    const size_t NN = (size_t)N * N;
+    return x + NN > coef9 && x < coef9 + 9 * NN;
+}
+template <typename T>
+void copy_image(T *out, const T *x, int N, hipStream_t s) {
+    axpby<T>(out, x, (T)1, nullptr, (T)0, (int64_t)N * N, s);
+}
+
 // Psi^dagger x into dst9 (FIN selects the dual update, the weights or the plain coefficients).
 template <typename T, int FIN>
 void analysis(ri_ctx *c, const T *x, T *dst9, T par, bool dirac, hipStream_t s) {
     SaraState &st = c->sara;
     const int N = c->N;
+    if (FIN == FIN_COEF && inside<T>(x, dst9, N)) {
+        copy_image<T>((T *)st.tmp, x, N, s);   // the second level's output, free until then
+        x = (T *)st.tmp;
+    }
     const T scale = (T)(1.0 / 3.0);
     T *const buf[2] = {(T *)st.work, (T *)st.tmp};   // the low-low blocks of even and odd levels
     const T *w9 = (const T *)st.w;
@@ -565,6 +582,7 @@ void synthesis(ri_ctx *c, T *v9, const T *z, T *x, T thr, hipStream_t s) {
     const T scale = (T)(1.0 / 3.0);
     T *const buf[2] = {(T *)st.work, (T *)st.tmp};   // the blocks of even and odd levels
     const T *w9 = (const T *)st.w;
+    T *const dst = MODE == SYN_PLAIN && inside<T>(x, v9, N) ? buf[0] : x;   // free at the finest level
     for (int l = LEVELS - 1; l >= 0; --l) {
         const int n = N >> l, coarsest = l == LEVELS - 1 ? 1 : 0;
         auto launch = [&](auto Sc, auto ALLBc, auto SMALLc) {
@@ -572,13 +590,14 @@ void synthesis(ri_ctx *c, T *v9, const T *z, T *x, T thr, hipStream_t s) {
             constexpr bool ALLB = decltype(ALLBc)::value;
             hipLaunchKernelGGL(HIP_KERNEL_NAME(k_syn<T, ALLB ? MODE : (int)SYN_LEVEL, S, decltype(SMALLc)::value>),
                                dim3(cdiv(n, 2 * TC), cdiv(n, 2 * KB * S), ALLB ? 1 : NW), dim3(128 * S), 0, s, v9,
-                               buf[(l + 1) & 1], ALLB ? x : buf[l & 1], w9, z, N, n, coarsest, scale, thr);
+                               buf[(l + 1) & 1], ALLB ? dst : buf[l & 1], w9, z, N, n, coarsest, scale, thr);
             if (l == 0 && !ALLB)
                 hipLaunchKernelGGL(HIP_KERNEL_NAME(k_syn_sum<T, MODE>), dim3(cdiv(N * N, 256)), dim3(256), 0, s, buf[0],
-                                   v9, w9, z, x, (int64_t)N * N, scale, thr);
+                                   v9, w9, z, dst, (int64_t)N * N, scale, thr);
         };
         dispatch_tile(c, n, l == 0, launch);
     }
+    if (dst != x) copy_image<T>(x, dst, N, s);
 }
 
 }  // namespace
