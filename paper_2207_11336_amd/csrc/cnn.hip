@@ -658,8 +658,9 @@ __device__ __forceinline__ void sum_waves(const float *part, int count, float *_
 // row `block` of part (577 floats), summed over blocks by k_reduce_rows.
 // dpre: thread t takes channels 8 (t % 8) .. +7 (their weights in registers) of one
 // pixel, 32 pixels a pass, so a wave stores eight whole pixels. dW: lane c of
-// wave w takes channel c over its patch rows, each activation read once for
-// all nine taps against a 3 x 3 window of g that slides along the row. Bound by
+// wave w takes channel c over its patch rows, a row's activations read once for
+// all nine taps; only products of the block's own pixels p are formed (a zero g
+// beside the block times an infinite activation would be NaN). Bound by
 // VALU and LDS: 30 us for 16 x 128^2 pixels (82 with one (c, t) pair per
 // thread, which re-read the patch for every tap).
 __global__ void __launch_bounds__(256) k_out_backward(const float *__restrict__ g, const uint16_t *__restrict__ act,
@@ -669,19 +670,15 @@ __global__ void __launch_bounds__(256) k_out_backward(const float *__restrict__ 
     extern __shared__ uint4 smem4[];
     uint16_t *patch = reinterpret_cast<uint16_t *>(smem4);          // act patch [18*18][PADC]
     float *gp = reinterpret_cast<float *>(patch + 18 * 18 * PADC);  // g patch [18][18]
-    float *gz = gp + 18 * 18;                                       // g of the block, two zeros around it [20][20]
-    float *ws = gz + 20 * 20;                                       // [64][9]
+    float *ws = gp + 18 * 18;                                       // [64][9]
     float *red = reinterpret_cast<float *>(smem4);                  // at the end, over the patch: the waves' dW [4][577]
     const int b = blockIdx.z, y0 = blockIdx.y * 16, x0 = blockIdx.x * 16, tid = threadIdx.x;
     const size_t img = (size_t)b * H * W;
     float *prow = part + ((size_t)(blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * (CH * 9 + 1);
     load_patch_lds(patch, act, img, y0, x0, H, W, tid);
-    for (int e = tid; e < 20 * 20; e += 256) {
-        const int py = e / 20 - 1, px = e % 20 - 1, y = y0 - 1 + py, x = x0 - 1 + px;
-        const bool in = (unsigned)py < 18u && (unsigned)px < 18u && (unsigned)y < (unsigned)H && (unsigned)x < (unsigned)W;
-        const float v = in ? g[img + (size_t)y * W + x] : 0.f;
-        if ((unsigned)py < 18u && (unsigned)px < 18u) gp[py * 18 + px] = v;
-        gz[e] = (py >= 1 && py < 17 && px >= 1 && px < 17) ? v : 0.f;
+    for (int e = tid; e < 18 * 18; e += 256) {
+        const int py = e / 18, px = e - py * 18, y = y0 - 1 + py, x = x0 - 1 + px;
+        gp[e] = (y >= 0 && y < H && x >= 0 && x < W) ? g[img + (size_t)y * W + x] : 0.f;
     }
     for (int e = tid; e < CH * 9; e += 256) ws[e] = bfround(wl_[e]);
     __syncthreads();
@@ -716,21 +713,22 @@ __global__ void __launch_bounds__(256) k_out_backward(const float *__restrict__ 
                 make_uint4(r[0] | (r[1] << 16), r[2] | (r[3] << 16), r[4] | (r[5] << 16), r[6] | (r[7] << 16));
         }
     }
-    // dW[c][3 dy + dx] += act[py][px] g[py - dy][px - dx] over the patch pixels (g zero outside the block)
-    const int c = tid & 63, w = tid >> 6;
+    // dW[c][3 dy + dx] += act[py][px] g[py - dy][px - dx] over the patch pixels with p = (py - dy, px - dx) in the block
+    const int c = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     float acc[9] = {};
     for (int py = w; py < 18; py += 4) {
-        float win[3][3] = {};   // win[dy][dx] = g[py - dy][px - dx]: gz row py + 2 - dy, column px + 2 - dx
+        float a[18];
 #pragma unroll
-        for (int px = 0; px < 18; ++px) {
-            const float a = bf2f(patch[(py * 18 + px) * PADC + c]);
+        for (int px = 0; px < 18; ++px) a[px] = bf2f(patch[(py * 18 + px) * PADC + c]);
 #pragma unroll
-            for (int dy = 0; dy < 3; ++dy) {
-                win[dy][2] = win[dy][1];
-                win[dy][1] = win[dy][0];
-                win[dy][0] = gz[(py + 2 - dy) * 20 + px + 2];
+        for (int dy = 0; dy < 3; ++dy) {
+            if ((unsigned)(py - dy) >= 16u) continue;
+            const float *gr = gp + (py - dy + 1) * 18 + 1;
 #pragma unroll
-                for (int dx = 0; dx < 3; ++dx) acc[3 * dy + dx] = fmaf(a, win[dy][dx], acc[3 * dy + dx]);
+            for (int x = 0; x < 16; ++x) {
+                const float gv = gr[x];
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx) acc[3 * dy + dx] = fmaf(a[x + dx], gv, acc[3 * dy + dx]);
             }
         }
     }
@@ -753,7 +751,10 @@ __global__ void __launch_bounds__(256) k_out_backward(const float *__restrict__ 
 // from LDS transposed, and the activation rows of the three vertical taps stay
 // in registers from one step to the next, so 36 products take 14 reads. LDS
 // holds the pixels as in memory (128 B each), their 32-byte quarters swizzled
-// by the column so that a read's 16 pixels spread over all banks. At the end the
+// by the column so that a read's 16 pixels spread over all banks. A block at the
+// right edge may have 16 columns only (w is a multiple of 16): the other 16 pixels
+// of a step are zeros in both operands, also where the left tap of pixel 16 meets
+// the image's last column (an infinite activation there would give NaN). At the end the
 // teams' sums meet in LDS, one row of partials per workgroup.
 // Bound by MFMA and the staging latency: 31 us per layer at 16 x 128^2
 // (77 with operands transposed by 2-byte LDS stores, three shifted copies).
@@ -773,10 +774,11 @@ __device__ __forceinline__ int dw_off(int row, int width, int x, int c) {
 }
 // MFMA fragment of 16 channels (rows or columns) and 32 pixels of a row (K; lane
 // group g holds pixels 4 g .. +3 and 16 + 4 g .. +3, the same order for both
-// operands): p points at the lane's first four channels and pixel.
-__device__ __forceinline__ bf16x8 dw_frag(const unsigned char *p) {
+// operands): p points at the lane's first four channels and pixel. Pixels 16 .. 31
+// are those of memory where keep is -1, zeros where it is 0.
+__device__ __forceinline__ bf16x8 dw_frag(const unsigned char *p, short keep = -1) {
     const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4 *)p);
-    const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4 *)(p + 16 * CH * 2));
+    const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4 *)(p + 16 * CH * 2)) & keep;
     const short v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
     return __builtin_bit_cast(bf16x8, v);
 }
@@ -804,6 +806,7 @@ __global__ void __launch_bounds__(512) k_dw64(const uint16_t *__restrict__ dpre,
     const BlockWalk walk(blockIdx.x, gridDim.x, nblocks / 2);   // h is a multiple of 16: blocks come in pairs
     for (int pair = walk.begin; pair < walk.end; pair += walk.step) {
         const int blk = 2 * pair + team;
+        const short keep = (blk % nbx + 1) * DWB_W <= W ? -1 : 0;   // for the left tap
         __syncthreads();
         {
             const int b = blk / (nbx * nby), rem = blk - b * nbx * nby, by = rem / nbx;
@@ -833,12 +836,13 @@ __global__ void __launch_bounds__(512) k_dw64(const uint16_t *__restrict__ dpre,
 #pragma unroll
             for (int r = 0; r < 2; ++r)
 #pragma unroll
-                for (int dx = 0; dx < 3; ++dx) rows[r][dx] = dw_frag(pa[dx] + r * DWP_W * CH * 2);
+                for (int dx = 0; dx < 3; ++dx) rows[r][dx] = dw_frag(pa[dx] + r * DWP_W * CH * 2, dx == 0 ? keep : -1);
 #pragma unroll
             for (int r = 0; r < DWB_H; ++r) {
                 bf16x8 a[4];
 #pragma unroll
-                for (int dx = 0; dx < 3; ++dx) rows[(r + 2) % 3][dx] = dw_frag(pa[dx] + (r + 2) * DWP_W * CH * 2);
+                for (int dx = 0; dx < 3; ++dx)
+                    rows[(r + 2) % 3][dx] = dw_frag(pa[dx] + (r + 2) * DWP_W * CH * 2, dx == 0 ? keep : -1);
 #pragma unroll
                 for (int o = 0; o < 4; ++o) a[o] = dw_frag(pd[o] + r * DWB_W * CH * 2);
 #pragma unroll
@@ -1183,7 +1187,7 @@ void *cnn_alloc(ri_cnn *n, size_t bytes) {
 
 size_t conv64_proj_lds() { return (size_t)CP_ROWS * CP_COLS * PADC * 2 + (size_t)WPK * 16 + CH * 4; }
 size_t convout_lds() { return (size_t)18 * 18 * PADC * 2 + 9 * CH * 4; }
-size_t outbwd_lds() { return (size_t)18 * 18 * PADC * 2 + (18 * 18 + 20 * 20 + CH * 9) * 4; }
+size_t outbwd_lds() { return (size_t)18 * 18 * PADC * 2 + (18 * 18 + CH * 9) * 4; }
 size_t dw64_lds() { return std::max<size_t>(2 * DW_TEAM_BYTES, sizeof(float) * DW_PART); }
 
 void check_shape(const ri_cnn *n, int B, int h, int w) {
