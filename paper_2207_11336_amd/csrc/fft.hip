@@ -1099,7 +1099,7 @@ template <typename T>
 void fwd_full_fft(ri_ctx *c, Prec<T> &p, const T *x, const Clear<T> &z, hipStream_t s) {
     ProfScope prof(c, PROF_FFT, s);
     cx<T> *band = nullptr;
-    if (sizeof(T) == 4 && c->logNp == 13) band = p.gridA + (size_t)c->Np * half_pitch(c->N);
+    if (packs_band<T>(c)) band = p.gridA + (size_t)c->Np * half_pitch(c->N);
     launch_zpad_rows<T>(c, p, x, band ? band : p.gridB, nullptr, band ? c->N - 1 : c->Np - 1, z, s);
     colfft<T>(c, p.gridB, p.gridB, p.tw, false, true, false, s, band);
 }

@@ -37,13 +37,12 @@ template <typename T>
 void gradient_in_workspace(ri_ctx *c, unsigned char *ws, const T *x, const void *y, T *g, double *r2,
                            hipStream_t s) {
     using namespace ri;
-    const size_t grid_bytes = up(sizeof(cx<T>) * (size_t)c->P * c->Np * c->Np);
     int32_t *counter = reinterpret_cast<int32_t *>(ws);
     double *part = reinterpret_cast<double *>(ws + kAlign);
     Prec<T> p = ctx_prec<T>(c);   // the context's tables; its grids are replaced below
     unsigned char *grids = ws + kAlign + up(sizeof(double) * (size_t)c->n_partials);
     p.gridA = reinterpret_cast<cx<T> *>(grids);
-    p.gridB = reinterpret_cast<cx<T> *>(grids + grid_bytes);
+    p.gridB = reinterpret_cast<cx<T> *>(grids + up(sizeof(cx<T>) * grid_a_cells<T>(c)));
     // data: none, the context's stored copy (internal order), or the caller's
     // vector read in place through the permutation (no staging copy)
     const cx<T> *y_sorted = nullptr, *y_user = nullptr;
@@ -64,9 +63,14 @@ void gradient_in_workspace(ri_ctx *c, unsigned char *ws, const T *x, const void 
 
 namespace ri {
 
+template <typename T>
+static size_t grids_bytes(const ri_ctx *c) {
+    return up(sizeof(cx<T>) * grid_a_cells<T>(c)) + up(sizeof(cx<T>) * grid_b_cells(c));
+}
+
 size_t noalloc_scratch_bytes(const ri_ctx *c) {
-    const size_t cxb = c->d.precision == 64 ? 16 : 8;
-    return kAlign + up(sizeof(double) * (size_t)c->n_partials) + 2 * up(cxb * (size_t)c->P * c->Np * c->Np);
+    return kAlign + up(sizeof(double) * (size_t)c->n_partials) +
+           (c->d.precision == 64 ? grids_bytes<double>(c) : grids_bytes<float>(c));
 }
 
 // Called by ri_create with the context's device current: the workspace's

@@ -448,11 +448,8 @@ void ensure_prec(ri_ctx *c, Prec<T> &p) {
     std::vector<cx<T>> wt(nt);
     for (size_t i = 0; i < nt; ++i) wt[i] = mk<T>((T)c->wtaps64[2 * i], (T)c->wtaps64[2 * i + 1]);
     p.wtaps = upload(c, wt.data(), nt);
-    const size_t ng = (size_t)c->P * Np * Np;
-    // half-plane grid and the N packed band rows of the forward transform (N' = 8192)
-    const size_t behind = sizeof(T) == 4 && c->P == 1 && c->logNp == 13 ? (size_t)16 * Np : 0;
-    p.gridA = (cx<T> *)dev_alloc(c, sizeof(cx<T>) * (ng + behind));
-    p.gridB = (cx<T> *)dev_alloc(c, sizeof(cx<T>) * ng);
+    p.gridA = (cx<T> *)dev_alloc(c, sizeof(cx<T>) * grid_a_cells<T>(c));
+    p.gridB = (cx<T> *)dev_alloc(c, sizeof(cx<T>) * grid_b_cells(c));
     if (c->P > 1) {
         // phase screens c_s(n) = exp(-2 pi i w_s (sqrt(1 - l^2 - m^2) - 1)), FP64 arithmetic
         const double dl = c->d.cell_rad;

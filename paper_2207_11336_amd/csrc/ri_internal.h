@@ -249,6 +249,14 @@ template <typename T> struct Clear {
 // product (arbitrary complex grids, N' x N').
 template <typename T> void fwd_zpad_fft(ri_ctx *c, Prec<T> &p, const T *x, hipStream_t s);
 template <typename T> void adj_fft_crop(ri_ctx *c, Prec<T> &p, T *x, hipStream_t s);
+// Cells of p.gridA and p.gridB: one N' x N' plane per w-stack, and in gridA, at
+// N' = 8192 in FP32 without w-stacking, the forward transform's N packed band rows
+// behind the half-plane output grid, N' half_pitch + N N' = N'^2 + 16 N' cells.
+inline size_t grid_b_cells(const ri_ctx *c) { return (size_t)c->P * c->Np * c->Np; }
+template <typename T> bool packs_band(const ri_ctx *c) { return sizeof(T) == 4 && c->P == 1 && c->logNp == 13; }
+template <typename T> size_t grid_a_cells(const ri_ctx *c) {
+    return grid_b_cells(c) + (packs_band<T>(c) ? (size_t)16 * c->Np : 0);
+}
 // Row pitch of a half-plane grid (columns kx = 0 .. N) of a real image.
 inline int half_pitch(int N) { return N >= 32 ? N + 16 : N + 8; }
 // What the tile launch of one pass needs zeroed: the output grid of p.gridA
