@@ -34,6 +34,7 @@
 // level 59 us analysis and 56 us synthesis, the three others 78 us).
 #include <cmath>
 #include <complex>
+#include <limits>
 #include <utility>
 
 #include "ri_internal.h"
@@ -416,7 +417,12 @@ inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 // ---------------------------------------------------------------------------
 using cld = std::complex<long double>;
 
-// Roots of sum_k a[k] y^k (degree d = a.size() - 1 >= 1) by Durand-Kerner.
+// Roots of sum_k a[k] y^k (degree d = a.size() - 1 >= 1) by Durand-Kerner: until a
+// sweep moves no root by more than a few roundings of its size (about 1; 13 sweeps
+// at most for the filters here), and eight sweeps more, in which the last
+// roundings settle (the filters come out the same to the last bit after 2000).
+// Waiting for a step below 1e-24, which long double never takes, cost the first
+// prox of every context 8.8 ms of host time.
 std::vector<cld> poly_roots(const std::vector<long double> &a) {
     const int d = (int)a.size() - 1;
     std::vector<cld> r(d);
@@ -428,7 +434,7 @@ std::vector<cld> poly_roots(const std::vector<long double> &a) {
         for (int k = d; k >= 0; --k) v = v * y + a[k];
         return v / a[d];
     };
-    for (int it = 0; it < 2000; ++it) {
+    for (int it = 0, settled = 0; it < 2000 && settled < 8; ++it) {
         long double moved = 0;
         for (int i = 0; i < d; ++i) {
             cld den = 1;
@@ -438,7 +444,7 @@ std::vector<cld> poly_roots(const std::vector<long double> &a) {
             r[i] -= step;
             moved = std::max(moved, std::abs(step));
         }
-        if (moved < 1e-24L) break;
+        if (moved <= 4 * std::numeric_limits<long double>::epsilon()) ++settled;
     }
     return r;
 }
