@@ -427,8 +427,18 @@ k_colfft(const cx<T> *in, cx<T> *out, const cx<T> *__restrict__ tw, int N, int b
 // decimation in frequency, natural order in, bit-reversed out; twiddles come
 // from the FP64-computed table.
 // ---------------------------------------------------------------------------
-template <typename T, int P>
+//
+// SPELL (64 points): with the products' roundings spelled out as the compiler contracts
+// them in k_colpass_a_reg<float, 128, 2>: a.y b.y is rounded by itself in every real
+// part; in the imaginary part of input j, stage by stage, a.y b.x where bit j is set
+// here, else a.x b.y. The pattern has no meaning of its own (the order in which that
+// kernel's values arise); it is what a kernel has to follow to give the same
+// visibilities to the last bit.
+constexpr uint64_t kPassAyBx[6] = {0, 0xFE00000000ull, 0xFE000E00FE0000ull, 0x60E0E0E020E0E00ull, 0x2220222022202220ull, 0};
+
+template <typename T, int P, bool SPELL = false>
 __device__ __forceinline__ void fftp_reg(cx<T> *v, const cx<T> *__restrict__ tw, int tw_mul, bool inv) {
+    static_assert(!SPELL || P == 64, "the pattern is that of 64 points");
     static_for<ilog2(P)>([&](auto St) {
         constexpr int span = (P / 2) >> decltype(St)::value;
         static_for<P>([&](auto J) {
@@ -441,7 +451,8 @@ __device__ __forceinline__ void fftp_reg(cx<T> *v, const cx<T> *__restrict__ tw,
                 if constexpr (e != 0) {
                     cx<T> w = tw[e * tw_mul];
                     if (inv) w.y = -w.y;
-                    d = d * w;
+                    if constexpr (!SPELL) d = d * w;
+                    else d = mulr<false, !((kPassAyBx[decltype(St)::value] >> j) & 1)>(d, w);
                 }
                 v[j + span] = d;
             }
@@ -510,9 +521,12 @@ __global__ void __launch_bounds__(64) k_colpass_a_reg(cx<T> *__restrict__ grid, 
 // side N = N'/2: points 32..95 are zero): the first radix-2 stage only selects
 // and twists, so a lane holds one 64-point half, the even or (blockIdx.z = 1)
 // the odd frequencies, and no value crosses lanes (the two halves write rows that
-// the other reads, hence out of place, from the N packed band rows). The stage's
-// products are those of fft_lanes<T, 128, 2>. At N' = 8192 in FP32: 231 us, against
-// 321 us with two lanes per column (average of both directions).
+// the other reads, hence out of place, from the N packed band rows). All products
+// round as in k_colpass_a_reg<float, 128, 2> (fftp_reg's SPELL; left to itself the
+// compiler rounds the real part's other product where an input is negated, and other
+// imaginary products: 85% of the visibilities at N = 4096 then differ in their last bits
+// from those of the other kernel, and ||r||^2 by up to 2e-9). At N' = 8192 in FP32:
+// 231 us, against 321 us with two lanes per column (average of both directions).
 template <typename T>
 __global__ void __launch_bounds__(64) k_colpass_a_band(const cx<T> *in, cx<T> *out, const cx<T> *__restrict__ tw,
                                                        int logNp) {
@@ -527,14 +541,14 @@ __global__ void __launch_bounds__(64) k_colpass_a_band(const cx<T> *in, cx<T> *o
         static_for<64>([&](auto I) {
             constexpr int i = decltype(I)::value;
             cx<T> d = i < 32 ? v[i] : mk<T>(-v[i].x, -v[i].y);
-            if constexpr (i != 0) d = d * tw[i * (Np / 128)];
+            if constexpr (i != 0) d = mulr<false, true>(d, tw[i * (Np / 128)]);
             v[i] = d;
         });
-    fftp_reg<T, 64>(v, tw, Np / 64, false);
+    fftp_reg<T, 64, true>(v, tw, Np / 64, false);
     static_for<64>([&](auto I) {
         constexpr int i = decltype(I)::value;
         const int k1 = brev(i, 6) * 2 + odd;
-        out[(size_t)(n2 + N2 * k1) * Np + c] = v[i] * tw[n2 * k1];
+        out[(size_t)(n2 + N2 * k1) * Np + c] = mulr<false, true>(v[i], tw[n2 * k1]);
     });
 }
 
