@@ -202,9 +202,10 @@ __device__ __forceinline__ void sched_interleave() {
 // Bound by the clock that the device holds under MFMA and HBM load (1.84 GHz at
 // 2048^2, MFMA busy half of the cycles, 1.1 GB per layer): 315 us per layer at
 // 2048^2 in both forms, 311 with alternating directions (about 265 us when all
-// activations are zero). Per network of ten layers, weights in LDS -> here:
-// 2.50 -> 2.44 ms at 2048^2, 688 -> 630 us at 1024^2, 223 -> 205 us at 512^2;
-// per training layer at 16 x 128^2 34 -> 27.5 us (MODE 1), 27 -> 25.5 (MODE 0).
+// activations are zero). Per network of ten layers, weights in LDS -> here, both builds
+// in turn on one box: 2.44 -> 2.44 ms at 2048^2 (no gain: the clock), 661 -> 613 us
+// at 1024^2, 209 -> 203 us at 512^2; per training layer at 16 x 128^2 34 -> 26.5 us
+// (MODE 1), 27 -> 24.5 (MODE 0).
 // ---------------------------------------------------------------------------
 constexpr int CV_PATCH = CP_ROWS * CP_COLS * CH * 2;      // bytes of a patch
 constexpr int CV_ROUNDS = (CP_CHUNKS + CNT - 1) / CNT;    // 16-byte chunks per thread
@@ -353,8 +354,9 @@ __global__ void __launch_bounds__(CNT) k_conv64(const uint16_t *__restrict__ in,
             }
             if (MODE == 1 && rp == 0) load_mask(y0 + r0 + 4);
         }
-        // the next patch is in LDS once at most this block's eight stores (and
-        // mask loads) are outstanding: loads and stores complete in order
+        // loads and stores complete in the order of their issue, and the second half
+        // row's four stores are the block's last: with no more than those outstanding
+        // the next patch, asked for before the products, is in LDS
         asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
         cur ^= 1;
     }
@@ -918,9 +920,9 @@ __device__ __forceinline__ float reduce_rows(const float *__restrict__ part, int
     return (float)red[0][le];
 }
 
-// dW[o][c][t] and db[o] from the per-workgroup partials of k_dw64: 9 us for 256 rows
-// with FP32 sums (21 with one thread per element, which left most of the device
-// idle); FP64 sums add about 3 us.
+// dW[o][c][t] and db[o] from the per-workgroup partials of k_dw64: 7.6 us for 256 rows
+// (8.8 with FP32 sums, 21 with one thread per element, which left most of the
+// device idle).
 __global__ void __launch_bounds__(1024) k_dw64_reduce(const float *__restrict__ part, int nwg, float *__restrict__ dW,
                                                       float *__restrict__ db) {
     constexpr int E = 64;

@@ -55,7 +55,11 @@ constexpr int ilog2(int R) { return R <= 1 ? 0 : 1 + ilog2(R / 2); }
 // into (left to itself it contracts a sum of two products either way, and shares
 // products where both parts of w are alike). XR: the real part's product that is
 // rounded by itself is a.x b.x, else a.y b.y; XI: the imaginary part's is a.x b.y,
-// else a.y b.x.
+// else a.y b.x. No choice is more accurate than another. Which one a product takes
+// (mul_root, the callers' arguments, kPassAyBx) follows the contractions that the
+// compiler chose in the kernels whose visibilities the FP32 transforms reproduce bit
+// for bit: ||Phi x - y||^2 is an FP64 sum, and other last bits of Phi x move it
+// by 2e-9 (one pass rounded otherwise) to 1e-7 (the half-plane form).
 template <bool XR, bool XI, typename T>
 __device__ __forceinline__ cx<T> mulr(cx<T> a, cx<T> b) {
     return mk<T>(XR ? fma(a.y, -b.y, a.x * b.x) : fma(a.x, b.x, -(a.y * b.y)),
@@ -864,7 +868,8 @@ k_half_icols(const cx<T> *__restrict__ Y, cx<T> *__restrict__ scr, const cx<T> *
 // k_half_icols up to N' = 2048 by whole columns (full_cols): the N' / 16 threads of
 // a column do one transform where the two parities' N / 16 did two in turn. In us, FP32
 // at N' = 256, 1024 and 2048: 8.7 -> 6.4, 16.3 -> 10.4, 19.0 -> 14.1; FP64 at 512 and 2048:
-// 9.8 -> 9.0, 21.8 -> 19.5. Larger columns would leave one workgroup per CU.
+// 9.8 -> 9.0, 21.8 -> 19.5. Not tried for larger columns (4 of 4096 points in FP32 fill
+// 139 KB of LDS, one workgroup per CU in either form).
 template <typename T, int LOGNP>
 __global__ void __launch_bounds__((FullCol<T, LOGNP>::NT))
 k_half_icols_full(const cx<T> *__restrict__ Y, cx<T> *__restrict__ scr, const cx<T> *__restrict__ tw, int pitch) {

@@ -183,10 +183,10 @@ void do_fb_step(ri_ctx *c, const T *x_in, const void *y, double gamma, int kind,
 
 // Main view at tile T (folded in FP64; in FP32 the forward transform of the
 // whole plane and each visibility's own side of it are kept, so that Phi x and
-// ||Phi x - y||^2 come out of the same roundings on every path; FP64 fractions when G is stored or the context is
-// FP64), plus the CSR G in that view's order. The holographic matrix and the
-// SARA state are grid- and image-level and do not depend on the view's
-// visibility order, so they are kept.
+// ||Phi x - y||^2 come out of the same roundings on every path; FP64 fractions
+// when G is stored or the context is FP64), plus the CSR G in that view's order.
+// The holographic matrix and the SARA state are grid- and image-level and do not
+// depend on the view's visibility order, so they are kept.
 void build_main_view(ri_ctx *c, int tile) {
     const bool f64frac = c->d.g_mode != RI_G_OTF || c->d.precision == 64;
     free_view(c, c->view);

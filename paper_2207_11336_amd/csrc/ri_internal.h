@@ -55,7 +55,7 @@ struct View {
     // conjugated, so that every window centre has c_u <= N and F Z x is needed
     // on half the plane only. REC_MIRROR marks it.
     bool folded = false;
-    int32_t *perm = nullptr;      // internal -> caller index | PERM_MIRROR when mirrored
+    int32_t *perm = nullptr;      // internal -> caller index | ~PERM_INDEX when mirrored
     uint2 *rec = nullptr;         // per visibility: ((c_v << 16) | c_u, plane | h << 16 | stack << 20 | REC_MIRROR)
     void *frac = nullptr;         // float[2] or double[2] per visibility (f_u, f_v)
     int frac_bytes = 0;           // 4 or 8

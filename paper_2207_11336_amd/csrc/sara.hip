@@ -28,10 +28,11 @@
 // Bound: memory. A sub-iteration cannot do without reading and writing the nine
 // dual planes and reading the nine weights (470 MB in FP32 at 2048^2 with z and
 // x: 97 us at the rate of a copy). One pass per level and both directions in LDS
-// leave the low-low blocks as the only other traffic; with a pass per direction
-// and a plane in between for every basis a sub-iteration moved 1.45 GB in 16
-// launches and took 370 us, this form moves 0.75 GB in 8 and takes 193 us (finest
-// level 59 us analysis and 56 us synthesis, the three others 78 us).
+// leave the low-low blocks and the tiles' borders as the only other traffic; with a
+// pass per direction and a plane in between for every basis a sub-iteration moved
+// 1.53 GB (counted) in 16 launches and took 370 us, this form moves 0.92 GB in 8 and
+// takes 189 us (finest level 59 us analysis and 56 us synthesis, the three others
+// 75 us).
 #include <cmath>
 #include <complex>
 #include <limits>
