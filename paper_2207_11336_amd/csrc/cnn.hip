@@ -13,8 +13,8 @@
 // Lane l holds A[l%16][8(l/16)..+7], B[8(l/16)..+7][l%16] and receives
 // D[4(l/16)..+3][l%16], so the epilogue stores four consecutive channels of
 // one pixel. Blocks are dealt to XCDs in contiguous ranges so neighbouring blocks
-// (which share halo rows) meet in the same L2; every other forward layer walks
-// its blocks backwards.
+// (which share halo rows) meet in the same L2; on large images every other forward
+// layer walks its blocks backwards.
 // The same kernel computes the backward data pass with the weights flipped in
 // space and transposed in channels, and a ReLU-mask epilogue.
 // Weight gradients: MFMA with K = pixels; both operands are staged in LDS as they
@@ -1218,6 +1218,13 @@ void forward(ri_cnn *n, const float *z, float *D, int B, int h, int w, const Cnn
     const int L = n->L, nbx = w / 16, nby = (h + CB_ROWS - 1) / CB_ROWS, nb = nbx * nby * B;
     const int64_t plane = (int64_t)B * h * w;
     auto A = [&](int l) { return n->training ? n->act[l] : n->act[l & 1]; };
+    // Every other layer backwards where a layer's input and output together exceed the
+    // 256 MB of the memory-side cache (from 1024^2 pixels on): it then starts on what the
+    // cache still holds. Below, a block is best read by the XCD whose L2 wrote it, which
+    // the other direction prevents. Per network of ten layers, alternating / not, in us:
+    // 256^2 130 / 108, sixteen of 64^2 129 / 107, 1280^2 1022 / 1044, 1536^2 1399 / 1432,
+    // 2048^2 2459 / 2491, eight of 576^2 1589 / 1638; 1024^2 is the same either way.
+    const bool alternate = 2 * plane * CH * (int64_t)sizeof(uint16_t) > (int64_t)256 << 20;
     hipLaunchKernelGGL(k_conv_in, grid, dim3(256), 0, s, z, A(0), n->params + n->off[0], n->params + n->off[1], geo,
                        h, w, (const uint16_t *)nullptr);
     for (int l = 1; l <= L - 2; ++l) {
@@ -1225,11 +1232,11 @@ void forward(ri_cnn *n, const float *z, float *D, int B, int h, int w, const Cnn
         if (n->training || l < L - 2)
             hipLaunchKernelGGL(HIP_KERNEL_NAME(k_conv64<0>), dim3(persistent_grid(n, nb)), dim3(CNT), conv64_lds(), s,
                                A(l - 1), A(l), wl, n->params + n->off[2 * l + 1], (const uint16_t *)nullptr, geo, h,
-                               w, nbx, nby, nb, l & 1);
+                               w, nbx, nby, nb, alternate ? l & 1 : 0);
         else
             hipLaunchKernelGGL(k_conv64_proj, dim3(persistent_grid(n, nb)), dim3(CNT), conv64_proj_lds(), s, A(l - 1),
                                wl, n->params + n->off[2 * l + 1], geo, h, w, nbx, nby, nb,
-                               reinterpret_cast<const uint4 *>(n->wproj), n->S, plane, l & 1);
+                               reinterpret_cast<const uint4 *>(n->wproj), n->S, plane, alternate ? l & 1 : 0);
     }
     if (n->training && D == nullptr) {
         // only the activations are wanted
