@@ -147,7 +147,9 @@ __device__ __forceinline__ void lds_dma16(u32x4 rs, unsigned char *base, unsigne
                  : "s"(__builtin_amdgcn_readfirstlane(at)), "v"(off), "s"(rs)
                  : "memory", "m0");
 }
-__device__ __forceinline__ void lds_dma_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+// Until at most N of the transfers (and other vector memory accesses) issued last are outstanding.
+template <int N = 0>
+__device__ __forceinline__ void lds_dma_wait() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 
 constexpr int CNW = 8;                                   // waves per workgroup (2 per SIMD)
 constexpr int CNT = 64 * CNW;                             // threads per workgroup
@@ -206,9 +208,14 @@ __device__ __forceinline__ void sched_interleave() {
 // in turn on one box: 2.44 -> 2.44 ms at 2048^2 (no gain: the clock), 661 -> 613 us
 // at 1024^2, 209 -> 203 us at 512^2; per training layer at 16 x 128^2 34 -> 26.5 us
 // (MODE 1), 27 -> 24.5 (MODE 0).
+// The weights reach the registers through LDS, once per workgroup: with each wave
+// loading its own (295 KB per workgroup) a launch of one block per workgroup was
+// mostly that. Networks of ten layers, before -> after: one 16^2 image 89 -> 80 us, 200
+// of them 103 -> 95, 512^2 215 -> 196, 1024^2 666 -> 627.
 // ---------------------------------------------------------------------------
 constexpr int CV_PATCH = CP_ROWS * CP_COLS * CH * 2;      // bytes of a patch
 constexpr int CV_ROUNDS = (CP_CHUNKS + CNT - 1) / CNT;    // 16-byte chunks per thread
+static_assert(WPK % CNT == 0 && WPK * 16 <= CV_PATCH, "the weights pass through a patch's LDS");
 size_t conv64_lds() { return 2 * (size_t)CV_PATCH; }
 
 // Byte offset of 16-byte chunk q of the patch pixel in column x.
@@ -243,13 +250,23 @@ __global__ void __launch_bounds__(CNT) k_conv64(const uint16_t *__restrict__ in,
     const int g = lane >> 4, j = lane & 15, hf = wave & 1, r0 = (wave >> 1) * 8;
     const BlockWalk walk(blockIdx.x, gridDim.x, nblocks, rev != 0);
     if (walk.begin >= walk.end) return;
+    // the layer's weights once per workgroup to the second patch's place, and from there
+    // to the registers of the waves while the first patch is on its way
+    const uint64_t wp = reinterpret_cast<uint64_t>(wpk);
+    const u32x4 wrs = {(unsigned)wp, (unsigned)(wp >> 32), WPK * 16u, 0x00020000u};
+#pragma unroll
+    for (int k = 0; k < WPK / CNT; ++k)
+        lds_dma16(wrs, lds + CV_PATCH + (k * CNT + wave * 64) * 16, (unsigned)(tid + k * CNT) * 16u);
     conv_patch_dma(lds, in, walk.at(walk.begin), nbx, nby, H, W, tid, wave);
+    lds_dma_wait<CP_CHUNKS / CNT>();   // at least so many transfers of the patch were issued after the weights'
+    __syncthreads();
+    const uint4 *wl = reinterpret_cast<const uint4 *>(lds + CV_PATCH);
     bf16x8 wa[18][2];   // [(2 dx + kb) * 3 + dy][channel tile 2 hf + m]
 #pragma unroll
     for (int st = 0; st < 18; ++st)
 #pragma unroll
         for (int m = 0; m < 2; ++m)
-            wa[st][m] = as_bf16x8(wpk[((((st % 3) * 3 + st / 6) * 2 + (st / 3) % 2) * 4 + 2 * hf + m) * 64 + lane]);
+            wa[st][m] = as_bf16x8(wl[((((st % 3) * 3 + st / 6) * 2 + (st / 3) % 2) * 4 + 2 * hf + m) * 64 + lane]);
     floatx4 bb[2];
 #pragma unroll
     for (int m = 0; m < 2; ++m)
@@ -1219,11 +1236,11 @@ void forward(ri_cnn *n, const float *z, float *D, int B, int h, int w, const Cnn
     const int64_t plane = (int64_t)B * h * w;
     auto A = [&](int l) { return n->training ? n->act[l] : n->act[l & 1]; };
     // Every other layer backwards where a layer's input and output together exceed the
-    // 256 MB of the memory-side cache (from 1024^2 pixels on): it then starts on what the
+    // 256 MB of the memory-side cache (above 1024^2 pixels): it then starts on what the
     // cache still holds. Below, a block is best read by the XCD whose L2 wrote it, which
     // the other direction prevents. Per network of ten layers, alternating / not, in us:
-    // 256^2 130 / 108, sixteen of 64^2 129 / 107, 1280^2 1022 / 1044, 1536^2 1399 / 1432,
-    // 2048^2 2459 / 2491, eight of 576^2 1589 / 1638; 1024^2 is the same either way.
+    // 256^2 120 / 100, two of 256^2 154 / 116, 384^2 193 / 169, 512^2 198 / 196, 1024^2
+    // 627 / 629, 1280^2 1022 / 1044, 1536^2 1399 / 1432, 2048^2 2459 / 2491.
     const bool alternate = 2 * plane * CH * (int64_t)sizeof(uint16_t) > (int64_t)256 << 20;
     hipLaunchKernelGGL(k_conv_in, grid, dim3(256), 0, s, z, A(0), n->params + n->off[0], n->params + n->off[1], geo,
                        h, w, (const uint16_t *)nullptr);
