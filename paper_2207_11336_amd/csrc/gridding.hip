@@ -196,8 +196,9 @@ __device__ __forceinline__ void global_add(T *p, T v) {
 // Tap l (0 .. 2h) of plane pl; of a mirrored visibility the conjugate of tap 2h - l.
 template <typename T>
 __device__ __forceinline__ cx<T> wtap(const TileArgs<T> &a, int pl, int h, int l, bool mir) {
-    cx<T> w = a.wtaps[(size_t)pl * (2 * a.hmax + 1) + a.hmax + (mir ? h - l : l - h)];
-    if (mir) w.y = -w.y;
+    const bool cj = MAY_FOLD<T> && mir;
+    cx<T> w = a.wtaps[(size_t)pl * (2 * a.hmax + 1) + a.hmax + (cj ? h - l : l - h)];
+    if (cj) w.y = -w.y;
     return w;
 }
 
@@ -369,8 +370,12 @@ k_tiles(TileArgs<T> a) {
         };
         auto put_vis = [&](cx<T> v, int mm) {
             const int32_t p = a.perm[mm];
-            if (p < 0) v.y = -v.y;
-            a.yout[p & PERM_INDEX] = v;
+            if constexpr (MAY_FOLD<T>) {
+                if (p < 0) v.y = -v.y;
+                a.yout[p & PERM_INDEX] = v;
+            } else {
+                a.yout[p] = v;
+            }
         };
         uint2 rec_n = make_uint2(0u, 0u);
         T f_n = (T)0;
@@ -866,6 +871,7 @@ TileArgs<T> make_args(ri_ctx *c, const View &v, Prec<T> &p) {
     a.logNp = c->logNp;
     a.hmax = c->hmax;
     a.Nh = c->N;
+    if (v.folded && !MAY_FOLD<T>) throw Error(RI_EUNSUPPORTED, "a folded view in single precision");
     a.xhalf = v.folded;
     a.xpitch = v.folded ? half_pitch(c->N) : c->Np;
     if (c->P == 1 && !v.folded) {
