@@ -364,7 +364,11 @@ k_tiles(TileArgs<T> a) {
         // kernel's registers within four waves
         auto ydata = [&](int mm) -> cx<T> {
             if (OP == OP_GRID) return data_at(a.yuser, a.perm[mm]);
-            if (a.ysorted) return a.ysorted[mm];
+            if (a.ysorted) {
+                const cx<T> v = a.ysorted[mm];
+                asm volatile("");   // keeps the two loads apart (merged, both wait for the permutation's)
+                return v;
+            }
             if (a.yuser) return data_at(a.yuser, a.perm[mm]);
             return mk<T>((T)0, (T)0);
         };
