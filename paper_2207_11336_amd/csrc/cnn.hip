@@ -205,13 +205,13 @@ __device__ __forceinline__ void sched_interleave() {
 // 2048^2, MFMA busy half of the cycles, 1.1 GB per layer): 315 us per layer at
 // 2048^2 in both forms, 311 with alternating directions (about 265 us when all
 // activations are zero). Per network of ten layers, weights in LDS -> here, both builds
-// in turn on one box: 2.44 -> 2.44 ms at 2048^2 (no gain: the clock), 661 -> 613 us
-// at 1024^2, 209 -> 203 us at 512^2; per training layer at 16 x 128^2 34 -> 26.5 us
-// (MODE 1), 27 -> 24.5 (MODE 0).
+// in turn on one box: 2.48 -> 2.46 ms at 2048^2 (little gained: the clock), 680 -> 629 us
+// at 1024^2, 214 -> 197 us at 512^2; per training layer at 16 x 128^2 34 -> 25.6 us
+// (MODE 1), 27 -> 24 (MODE 0).
 // The weights reach the registers through LDS, once per workgroup: with each wave
 // loading its own (295 KB per workgroup) a launch of one block per workgroup was
 // mostly that. Networks of ten layers, before -> after: one 16^2 image 89 -> 80 us, 200
-// of them 103 -> 95, 512^2 215 -> 196, 1024^2 666 -> 627.
+// of them 103 -> 95, 512^2 207 -> 197, 1024^2 644 -> 631.
 // ---------------------------------------------------------------------------
 constexpr int CV_PATCH = CP_ROWS * CP_COLS * CH * 2;      // bytes of a patch
 constexpr int CV_ROUNDS = (CP_CHUNKS + CNT - 1) / CNT;    // 16-byte chunks per thread
